@@ -59,12 +59,12 @@ def kernel_hash():
     return h.hexdigest()[:16]
 
 
-SOR_SRC = os.path.join(ROOT, "paper_1708_08741_amd", "csrc", "k_potential.hip")
+SOR_SRC = os.path.join(ROOT, "paper_1708_08741_amd", "csrc", "sor_tile_impl.h")
 
 
 def sor_traffic():
-    """HBM bytes of one FP32 one-pass SOR iteration (k_sor_march) from the
-    committed counter summary, if it was taken on the current SOR source;
+    """HBM bytes of one FP32 SOR iteration (k_sor_tile, two per launch) from
+    the committed counter summary, if it was taken on the current SOR source;
     else None."""
     try:
         d = json.load(open(TRAFFIC_FILE))
@@ -74,8 +74,8 @@ def sor_traffic():
     if d.get("sor_kernel_sha") != sha:
         return None
     for k, e in d.get("other_kernels", {}).items():
-        if k.startswith("k_sor_march<float"):
-            return e.get("hbm_bytes_per_launch")
+        if k.startswith("k_sor_tile<float") and e.get("iterations_per_launch"):
+            return e.get("hbm_bytes_per_launch") / e["iterations_per_launch"]
     return None
 
 
@@ -610,9 +610,9 @@ def main():
         it_ms = r["solve_ms"] / args.sor_iters
         one, rows, planes, waves = r["shape"]
         if one:
-            label = (f"k_sor_march: one pass per iteration on colour-split psi, from one buffer "
-                     f"into the other; workgroups of {waves} wavefronts hold whole rows, "
-                     f"{rows} rows per thread, marching through chunks of {planes} z planes")
+            label = (f"k_sor_tile: one pass for one or two iterations on colour-split psi, from one "
+                     f"buffer into the other; whole rows of {waves} wavefronts, {rows} row per "
+                     f"wavefront, marching through up to {planes} z planes")
         else:
             label = (f"k_sor_half_vec: one colour per launch, two per iteration, {rows} rows "
                      f"per thread, chunks of {planes} z planes")

@@ -182,8 +182,8 @@ int lbmep_get_solver_stats(lbmep_lattice *L, int32_t *iters, double res[2]);
 /* How a solve of L iterates (for labels of measurements): shape[0] = 1 for
  * the one-pass iteration (even nx, rows of at most 2048 cells), 0 for one
  * in-place launch per colour; shape[1] = rows per thread and shape[2] =
- * planes per workgroup of the one-pass iteration (of the in-place
- * half-sweep otherwise); shape[3] = wavefronts per row (one-pass) or per
+ * planes per workgroup of the one-pass iteration (nz where a workgroup takes
+ * an equal share of all planes; of the in-place half-sweep otherwise); shape[3] = wavefronts per row (one-pass) or per
  * tile along x (in-place).  Errors: EINVAL (null, no solver configured). */
 int lbmep_get_solver_shape(const lbmep_lattice *L, int32_t shape[4]);
 

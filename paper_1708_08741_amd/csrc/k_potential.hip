@@ -24,10 +24,13 @@
 // psi is stored colour-split for even nx (psi_slot: colour k's cells at
 // [k Ns / 2, k Ns / 2 + N / 2), cell c at c >> 1), in cell order for odd nx.
 //
-// Two implementations of an iteration, bitwise identical:
-//   * one pass per iteration (even nx, rows of up to 2048 cells; the
-//     default): k_sor_march from psi into a second buffer, every cell of
-//     both colours in one z-march (see k_sor_march);
+// Three implementations of an iteration, bitwise identical:
+//   * one pass for one or two iterations (even nx, rows of a colour in at
+//     most four wavefronts; the default): k_sor_tile from psi into a second
+//     buffer (sor_tile_impl.h);
+//   * one pass per iteration (the other even rows of up to 2048 cells):
+//     k_sor_march from psi into a second buffer, every cell of both colours
+//     in one z-march (see k_sor_march);
 //   * one launch per colour, in place: for even nx k_sor_half_vec, whose
 //     workgroups march through chunks of z planes with the other colour's
 //     three-plane window in registers (the other colour read once, the own
@@ -38,6 +41,8 @@
 // The residual's L2 norm is the root mean square over the unknowns, summed
 // in a fixed order (per-thread strided sums, a block tree, one block over
 // the blocks), so it is reproducible run to run.
+#include <algorithm>
+
 #include "lbmep_internal.h"
 
 namespace lbmep {
@@ -64,7 +69,8 @@ template <typename CT>
 __device__ __forceinline__ void dha_row(const Grid &g, int x, int y, int z, uint8_t fl,
                                         const CT *psi, const uint8_t *flag,
                                         const uint32_t *owner, const double *zeta, CT kappa2,
-                                        CT &diag, CT &rhs, CT &sum, uint8_t *unknown = nullptr) {
+                                        CT &diag, CT &rhs, CT &sum, uint8_t *unknown = nullptr,
+                                        const CT *bnd = nullptr) {
     diag = CT(6.0) + kappa2;
     rhs = CT(0);
     sum = CT(0);
@@ -109,8 +115,9 @@ __device__ __forceinline__ void dha_row(const Grid &g, int x, int y, int z, uint
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         // Dirichlet value of an obstacle neighbour: zeta of its particle,
-        // or psi's value there
+        // or psi's value there (kept in bnd while a solve holds 0 in psi)
         bv[k] = pv[k];
+        if (bnd && !zeta && !edge[k] && (fs[k] & kObst)) bv[k] = bnd[psi_slot(g, s[k], oc)];
         if (zeta && !edge[k] && (fs[k] & kObst) && !(fs[k] & kWall)) {
             const uint32_t po = owner[s[k]];
             if (po != kNone) bv[k] = (CT)zeta[po];
@@ -762,7 +769,7 @@ __global__ void __launch_bounds__(kNearBlock) k_sor_near(SorArgs a, int colour, 
 // residual: per-thread strided sums of r^2 and of the unknowns, a block tree,
 // one FP64 pair per block
 template <typename CT>
-__global__ void __launch_bounds__(kResBlock) k_dha_residual(SorArgs a) {
+__global__ void __launch_bounds__(kResBlock) k_dha_residual(SorArgs a, const CT *bnd) {
     if (a.ctl->done) return;
     const Grid &g = a.g;
     const CT *psi = static_cast<const CT *>(a.psi);
@@ -775,7 +782,8 @@ __global__ void __launch_bounds__(kResBlock) k_dha_residual(SorArgs a) {
         const size_t yz = c / (size_t)g.nx;
         const int y = (int)(yz % (size_t)g.ny), z = (int)(yz / (size_t)g.ny);
         CT diag, rhs, sum;
-        dha_row<CT>(g, x, y, z, fl, psi, a.flag, a.owner, a.zeta, (CT)a.kappa2, diag, rhs, sum);
+        dha_row<CT>(g, x, y, z, fl, psi, a.flag, a.owner, a.zeta, (CT)a.kappa2, diag, rhs, sum,
+                    nullptr, bnd);
         const double r = (double)(rhs + sum - diag * psi[psi_slot(g, c, (uint32_t)((x + y + z) & 1))]);
         ss += r * r;
         n += 1.0;
@@ -1361,6 +1369,14 @@ __global__ void __launch_bounds__(256) k_dirichlet_restore(SorArgs a, CT *p0, CT
     }
 }
 
+}  // namespace
+}  // namespace lbmep
+
+#include "sor_tile_impl.h"
+
+namespace lbmep {
+namespace {
+
 template <typename CT>
 __global__ void k_to_f64(Grid g, const CT *psi, double *out) {
     const size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1399,7 +1415,9 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
     const bool vec = (g.nx % 2) == 0;
     // one pass per iteration: even nx, whole rows in one workgroup, a second
     // buffer; rows per thread: the largest of mrw, mrw / 2, ... dividing ny
-    const bool march = fused && vec && hx <= 64 * kMarchMaxWaves && a0.psi2 != nullptr;
+    const TilePlan tp = tile_plan<CT>(a0, fused);
+    const bool tile = tp.shape.V > 0;
+    const bool march = !tile && fused && vec && hx <= 64 * kMarchMaxWaves && a0.psi2 != nullptr;
     const uint32_t mthreads = 64u * (uint32_t)((hx + 63) / 64);
     // windows of more than 4 rows per thread spill in a kernel bounded for
     // 1024 threads; bounded for 256 (rows of up to 512 cells) 8 rows fit in
@@ -1425,10 +1443,17 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
     }
     hipLaunchKernelGGL(k_sor_begin, dim3(1), dim3(64), 0, s, a.ctl);
     const bool dirichlet = march && a0.zeta && a0.owner;  // obstacle cells hold zeta meanwhile
+    // the tile passes keep the solid cells' values in save
+    const CT *bnd = tile ? static_cast<const CT *>(a0.save) : nullptr;
     // per-solve passes over the entries: rows of hx entries, then y and z
     const dim3 egrid((uint32_t)((hx + 255) / 256), (uint32_t)((g.ny + kPrepRows - 1) / kPrepRows),
                      (uint32_t)g.nz);
-    if (march) {
+    if (tile) {
+        const size_t words = sor_ibits_words_per_colour(g.N);
+        hipLaunchKernelGGL(k_interior_bits_split, dim3((uint32_t)((words + 255) / 256)), dim3(256),
+                           0, s, g, a.flag, a.ibits);
+        if (a0.solids || !g.per[0] || !g.per[1] || !g.per[2]) launch_tile_prepare<CT>(a, s);
+    } else if (march) {
         // what k_sor_march assumes of its launch: whole rows in one workgroup
         // (at most kMarchMaxWaves wavefronts), rows per thread dividing ny
         if (mthreads > 64u * kMarchMaxWaves || hx < 1 || g.ny % mrw != 0 || myb < 1 || !a0.codes ||
@@ -1464,11 +1489,26 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
         hipLaunchKernelGGL((k_nlist_rows<CT>), dim3(kNearGrid), dim3(kNearBlock), 0, s, a);
     }
     if (with_res) {
-        hipLaunchKernelGGL((k_dha_residual<CT>), dim3(nres), dim3(kResBlock), 0, s, a);
+        hipLaunchKernelGGL((k_dha_residual<CT>), dim3(nres), dim3(kResBlock), 0, s, a, bnd);
         hipLaunchKernelGGL(k_dha_finalize, dim3(1), dim3(kResBlock), 0, s, a, nres, 1);
     }
+    // iterations of the tile pass that starts with iteration it: two, up to
+    // the next residual or poll
+    auto pass_iters = [&](int it) {
+        int left = max_iter - it + 1;
+        if (with_res)
+            left = std::min(left, std::min(check_every - (it - 1) % check_every, 64 - (it - 1) % 64));
+        return left >= 2 && tp.pairs ? 2 : 1;
+    };
     for (int it = 1; it <= max_iter; ++it) {
-        if (march) {
+        if (tile) {
+            const int k = pass_iters(it);
+            const CT *src = static_cast<const CT *>(a.psi);
+            CT *dst = static_cast<CT *>(a.psi == a0.psi ? a0.psi2 : a0.psi);
+            launch_tile_pass<CT>(a, src, dst, k, s);
+            a.psi = dst;
+            it += k - 1;
+        } else if (march) {
             const CT *src = static_cast<const CT *>(a.psi);
             CT *dst = static_cast<CT *>(a.psi == a0.psi ? a0.psi2 : a0.psi);
 #define LBMEP_SOR_MARCH(RW, W)                                                                 \
@@ -1508,7 +1548,7 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
             }
         }
         if (with_res && (it % check_every == 0 || it == max_iter)) {
-            hipLaunchKernelGGL((k_dha_residual<CT>), dim3(nres), dim3(kResBlock), 0, s, a);
+            hipLaunchKernelGGL((k_dha_residual<CT>), dim3(nres), dim3(kResBlock), 0, s, a, bnd);
             hipLaunchKernelGGL(k_dha_finalize, dim3(1), dim3(kResBlock), 0, s, a, nres, 0);
         }
         if (with_res && it % 64 == 0 && it < max_iter) {
@@ -1521,6 +1561,9 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
     }
     // the obstacle cells' own values back, in both buffers (the result is in
     // either)
+    if (tile && a0.solids)
+        launch_tile_solid<CT>(a, static_cast<CT *>(a0.psi), static_cast<CT *>(a0.psi2),
+                              static_cast<const CT *>(a0.save), s);
     if (dirichlet)
         hipLaunchKernelGGL((k_dirichlet_restore<CT>), egrid, dim3(256), 0, s, a,
                            static_cast<CT *>(a0.psi), static_cast<CT *>(a0.psi2),
@@ -1529,7 +1572,7 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
     if (e != hipSuccess) return e;
     // the one-pass iterations alternate buffers: which one holds the result
     *swapped = 0;
-    if (march) {
+    if (march || tile) {
         int32_t iters = max_iter;
         if (with_res) {
             e = hipMemcpyAsync(&iters, &a.ctl->iters, sizeof iters, hipMemcpyDeviceToHost, s);
@@ -1537,6 +1580,15 @@ hipError_t sor_solve_typed(const SorArgs &a0, int max_iter, int check_every, boo
             if (e != hipSuccess) return e;
         }
         *swapped = iters & 1;
+        if (tile) {
+            // the passes of `iters` iterations (a stop is at a residual, so
+            // at the end of a pass)
+            int n = 0;
+            for (int it = 1; it <= iters; ++it, ++n) {
+                it += pass_iters(it) - 1;
+            }
+            *swapped = n & 1;
+        }
     }
     return hipSuccess;
 }
@@ -1552,6 +1604,15 @@ hipError_t launch_sor_solve(int precision, const SorArgs &a, int max_iter, int c
     if (precision == LBMEP_FP64)
         return sor_solve_typed<double>(a, max_iter, check_every, fused, s, swapped);
     return sor_solve_typed<float>(a, max_iter, check_every, fused, s, swapped);
+}
+
+bool sor_tile_shape(int precision, const Grid &g, uint32_t mzc, int32_t shape[3]) {
+    const TileShape t = precision == LBMEP_FP64 ? tile_shape<double>(g) : tile_shape<float>(g);
+    if (t.V == 0) return false;
+    shape[0] = 1;
+    shape[1] = mzc > 0 ? (int32_t)std::min((uint32_t)g.nz, mzc) : (int32_t)g.nz;
+    shape[2] = t.nwx;
+    return true;
 }
 
 hipError_t launch_potential_pack(int precision, const Grid &g, const void *in, int in_dtype,

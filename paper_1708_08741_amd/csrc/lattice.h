@@ -96,7 +96,7 @@ struct lbmep_lattice {
     int sor_xcd = 1;  // XCD-contiguous tile order
     int sor_rows = 8; // rows per thread of the tile (4, 8; set per precision)
     int sor_near_blocks = 0;  // workgroups of the SOR's boundary list part (0: default)
-    int sor_mzc = 16; // planes per workgroup of the one-pass SOR iteration
+    int sor_mzc = 0;  // planes per workgroup of the one-pass SOR iteration (0: by grid)
     int sor_mrw = 4;  // rows per thread of the one-pass SOR iteration (set per precision)
     int xcd_swizzle = 1;
     int sweep_wgcu = -1;  // sweep: workgroups per CU (0: no cap, -1: per precision and force)

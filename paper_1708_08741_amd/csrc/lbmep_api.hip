@@ -768,6 +768,7 @@ static SorArgs sor_args(const lbmep_lattice *L) {
     a.save = L->sor_save;
     a.mzc = (uint32_t)L->sor_mzc;
     a.mrw = (uint32_t)L->sor_mrw;
+    a.solids = L->np > 0 || L->has_walls;
     return a;
 }
 
@@ -810,7 +811,7 @@ int lbmep_set_potential_solver(lbmep_lattice *L, double kappa2, double omega, in
         if (dev_alloc(L, (void **)&L->sor_nscratch, 4 * sor_nscratch_entries(L->g.N)) != hipSuccess)
             return fail(LBMEP_ENOMEM, "solver list scratch");
         if (dev_alloc(L, &L->sor_nrow, 2 * compute_bytes(L->precision) *
-                                           sor_nlist_entries(L->g.N)) != hipSuccess ||
+                                           sor_nrow_entries(L->g.N)) != hipSuccess ||
             dev_alloc(L, (void **)&L->sor_nmask, sor_nlist_entries(L->g.N)) != hipSuccess ||
             dev_alloc(L, (void **)&L->sor_ibits, 6 * 4 * sor_ibits_words_per_colour(L->g.N)) !=
                 hipSuccess)
@@ -834,7 +835,7 @@ int lbmep_set_potential_solver(lbmep_lattice *L, double kappa2, double omega, in
         L->psi2_bytes = need;
     }
     if (L->sor_fused && !L->sor_codes &&
-        dev_alloc(L, (void **)&L->sor_codes, 4 * (L->g.N / 2 + 1)) != hipSuccess)
+        dev_alloc(L, (void **)&L->sor_codes, 4 * (L->g.N / 2 + 16)) != hipSuccess)
         return fail(LBMEP_ENOMEM, "solver row codes");
     L->sor_kappa2 = kappa2;
     L->sor_omega = omega;
@@ -884,12 +885,14 @@ int lbmep_get_solver_shape(const lbmep_lattice *L, int32_t shape[4]) {
     if (!L || !shape) return fail(LBMEP_EINVAL, "null argument");
     if (!L->sor_set) return fail(LBMEP_EINVAL, "no potential solver configured");
     const bool one = L->sor_fused && L->g.nx % 2 == 0 && L->g.nx <= 2048;
-    if (one) {
+    if (one && sor_tile_shape(L->precision, L->g, (uint32_t)L->sor_mzc, shape + 1)) {
+        shape[0] = 1;
+    } else if (one) {
         int rw = L->sor_mrw >= 4 ? 4 : (L->sor_mrw >= 2 ? 2 : 1);  // as the solve picks it
         while (L->g.ny % rw) rw >>= 1;
         shape[0] = 1;
         shape[1] = rw;
-        shape[2] = L->sor_mzc;
+        shape[2] = L->sor_mzc > 0 ? L->sor_mzc : 16;
         shape[3] = (L->g.nx / 2 + 63) / 64;
     } else {
         shape[0] = 0;

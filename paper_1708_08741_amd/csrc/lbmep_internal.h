@@ -287,7 +287,8 @@ struct SorArgs {
     uint32_t near_blocks;      // workgroups of the boundary list part (0: default; % 8 == 0)
     uint32_t *codes;           // one-pass iteration: per entry the codes of its two cells
     void *save;                // one-pass iteration: obstacle cells' values (Ns compute values)
-    uint32_t mzc;              // planes per workgroup of the one-pass iteration (>= 1)
+    uint32_t mzc;              // planes per workgroup of the one-pass iteration (0: as measured best)
+    int solids;                // there may be wall or obstacle cells
     uint32_t mrw;              // rows per thread of the one-pass iteration (1, 2, 4)
     float rdiag[13];           // FP32: 1 / (6 + kappa^2 + k), k = -6 .. 6, correctly rounded
 };
@@ -295,6 +296,9 @@ constexpr int kSorPartials = 8192;
 // the boundary lists are built per segment of kNearSeg cells
 constexpr int kNearSeg = 8192;
 inline size_t sor_nlist_entries(size_t N) { return N + 2; }
+// the list rows; the tile passes keep the rows of all boundary cells there,
+// colour by colour, each padded to 16 entries
+inline size_t sor_nrow_entries(size_t N) { return N + 64; }
 inline size_t sor_nscratch_entries(size_t N) { return 4 * ((N + kNearSeg - 1) / kNearSeg) + 2; }
 // interior bitmaps of the two colours (even nx): 32 entries per word
 __host__ __device__ inline size_t sor_ibits_words_per_colour(size_t N) { return (N / 2 + 31) / 32; }
@@ -305,6 +309,9 @@ __host__ __device__ inline size_t sor_ibits_words_per_colour(size_t N) { return 
 // (even nx, rows of up to 2048 cells): one pass per iteration from psi into
 // psi2 and back; *swapped = 1 when the result ends in psi2 (the caller swaps
 // the buffers).  Otherwise one launch per colour in place.
+// shape of the one-pass iteration for get_solver_shape: rows per thread,
+// planes per workgroup, wavefronts per row (false: not the tile form)
+bool sor_tile_shape(int precision, const Grid &g, uint32_t mzc, int32_t shape[3]);
 hipError_t launch_sor_solve(int precision, const SorArgs &a, int max_iter, int check_every,
                             bool fused, hipStream_t s, int *swapped);
 hipError_t launch_potential_to_f64(int precision, const Grid &g, const void *psi, double *out,

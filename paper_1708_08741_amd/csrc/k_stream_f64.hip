@@ -7,25 +7,26 @@
 namespace lbmep {
 
 hipError_t launch_sweep_f64(int mode, int force_mode, const SweepArgs &a, int block_x,
-                            int cpt, hipStream_t s) {
-    return sweep::launch_typed<double>(mode, force_mode, a, block_x, cpt, s);
+                            int cpt, const MapSetArgs *ms, hipStream_t s) {
+    return sweep::launch_typed<double>(mode, force_mode, a, block_x, cpt, ms, s);
 }
 
-hipError_t launch_near_f64(const SweepArgs &a, int wall_blocks, hipStream_t s) {
-    return sweep::launch_near_typed<double>(a, wall_blocks, s);
+hipError_t launch_parts_f64(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {
+    return sweep::launch_parts_typed<double>(a, q, s);
 }
 
 hipError_t launch_sweep_packed_f64(int force_mode, const PackTable &t, hipStream_t s) {
     return sweep::launch_sweep_packed_typed<double>(force_mode, t, s);
 }
 
-hipError_t launch_near_packed_f64(const PackTable &t, hipStream_t s) {
-    return sweep::launch_near_packed_typed<double>(t, s);
+hipError_t launch_parts_packed_f64(const PackTable &t, uint32_t lds, hipStream_t s) {
+    return sweep::launch_parts_packed_typed<double>(t, lds, s);
 }
 
 int near_wall_blocks(const Grid &g, bool walls) { return sweep::near_wall_blocks(g.N, walls); }
+uint32_t near_lds() { return sweep::kNearLds; }
 int near_blocks(int np, const Grid &g, bool walls) {
-    return (int)sweep::near_particle_blocks(np) + sweep::near_wall_blocks(g.N, walls);
+    return np + sweep::near_wall_blocks(g.N, walls);
 }
 
 }  // namespace lbmep

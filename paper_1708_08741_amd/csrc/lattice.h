@@ -45,12 +45,16 @@ struct lbmep_lattice {
     uint32_t *pcount_buf[2] = {nullptr, nullptr};
     int lcur = 0;                     // list buffer of the current level
     uint32_t pcap = 0;                // list capacity per particle
-    uint32_t halo_cap = 0;            // LDS bytes of the classification's staged box
+    uint32_t box_rows = 0;            // rows of the classification's box in LDS
     size_t plist_entries = 0;         // allocated entries
-    uint32_t *owner[2] = {nullptr, nullptr};
-    double *Xheld[2] = {nullptr, nullptr};  // positions of the level each map holds
+    // maps of the previous, the current and (moving particles) the next level
+    // by turns: map[cur_owner] is the current level's, the one before it
+    // (old_map) the previous level's, the one after it (next_map) empty until
+    // the next level is mapped.  A fixed map needs two.
+    lbmep::LevelMap map[3] = {};
+    uint32_t *wallbits = nullptr;     // wall cells, one bit per cell
     int cur_owner = 0;
-    int ft_buf = 0;  // owner/position buffer of the last streamed time level
+    int ft_buf = 0;  // map of the last streamed time level
     int np = 0;
     size_t np_cap = 0;
     double *X0 = nullptr, *R = nullptr, *U = nullptr, *W = nullptr, *FM = nullptr;
@@ -101,13 +105,9 @@ struct lbmep_lattice {
     int xcd_swizzle = 1;
     int sweep_wgcu = -1;  // sweep: workgroups per CU (0: no cap, -1: per precision and force)
     int sweep_nt = 2;  // streaming hints of the sweep: 0 none, 1 loads + stores, 2 stores
-    // overlapped stepping (moving particles, prescribed kinematics): the
-    // kinematics, mapping and classification of level n + 1 run on a second
-    // stream during the exchange of level n
+    // overlapped stepping (moving particles): two sets of link lists, so that
+    // the classification of level n + 1 runs beside the exchange of level n
     bool overlap = false;
-    hipStream_t stream2 = nullptr;
-    hipEvent_t ev_sweep = nullptr, ev_chain = nullptr;
-    bool chain_pending = false;
     bool timing = false;
     std::vector<hipEvent_t> ev;
     size_t ev_used = 0;
@@ -155,6 +155,8 @@ SweepArgs sweep_args_state(const lbmep_lattice *L, int cur, int cur_owner);
 SweepArgs sweep_args(const lbmep_lattice *L);
 // gather the post-stream state into the spare grid (after a step)
 int materialize(lbmep_lattice *L);
+inline int old_map(int c) { return c == 0 ? 2 : c - 1; }
+inline int next_map(int c) { return c == 2 ? 0 : c + 1; }
 // host bookkeeping of one completed step (the grid / map buffers flip)
 void advance_state(lbmep_lattice *L);
 

@@ -94,10 +94,12 @@ ParticleArgs particle_args(const lbmep_lattice *L) {
     pa.R = L->R;
     pa.U = L->U;
     pa.W = L->W;
+    pa.flag = L->flag;
+    pa.wallbits = L->has_walls ? L->wallbits : nullptr;
     pa.plist = L->plist_buf[L->lcur];
     pa.pcount = L->pcount_buf[L->lcur];
     pa.pcap = L->pcap;
-    pa.halo_cap = L->halo_cap;
+    pa.box_rows = L->box_rows;
     return pa;
 }
 
@@ -108,20 +110,22 @@ int remap_all(lbmep_lattice *L) {
     L->lcur = 0;
     const ParticleArgs pa = particle_args(L);
     if (L->np > 0) {
-        for (int b = 0; b < 2; ++b) {
-            HIP_TRY(launch_fill_u32(L->owner[b], kNone, L->g.N, s));
-            HIP_TRY(launch_positions(pa, L->level, L->Xheld[b], s));
-            HIP_TRY(launch_map_set(pa, L->Xheld[b], L->flag, L->owner[b], s));
+        for (int b = 0; b < 3; ++b) {
+            if (!L->map[b].owner) continue;
+            HIP_TRY(launch_fill_u32(L->map[b].owner, kNone, L->g.N, s));
+            HIP_TRY(launch_fill_u32(L->map[b].bits, 0u, map_words(L->g.N), s));
         }
+        // the current and the previous level; the next one's stays empty
+        if (L->has_walls) HIP_TRY(launch_wall_bits(L->g, L->flag, L->wallbits, s));
+        HIP_TRY(launch_map_set(pa, L->level, L->map[0], s));
+        HIP_TRY(launch_map_set(pa, L->level, L->map[2], s));
         L->cur_owner = 0;
         L->ft_buf = 0;
         HIP_TRY(launch_fill_f64(L->FM, 0.0, 18 * (size_t)L->np, s));
     }
-    HIP_TRY(launch_classify_all(L->g, L->flag, L->wallmask, L->np > 0 ? L->owner[0] : nullptr, s));
+    HIP_TRY(launch_classify_all(L->g, L->flag, L->wallmask, L->np > 0 ? L->map[0].owner : nullptr, s));
     HIP_TRY(launch_wall_list(L->g, L->wallmask, L->wall_list, L->wall_count, L->wall_scratch, s));
-    if (L->np > 0)
-        HIP_TRY(launch_classify_boxes(pa, L->Xheld[0], L->Xheld[0], L->flag, L->owner[0],
-                                      L->owner[0], s));
+    if (L->np > 0) HIP_TRY(launch_classify_boxes(pa, L->map[0], L->map[0], s));
     return LBMEP_OK;
 }
 
@@ -158,10 +162,10 @@ SweepArgs sweep_args_state(const lbmep_lattice *L, int cur, int co) {
     a.flag = L->flag;
     a.nearmask = L->wallmask;
     const bool parts = L->np > 0;
-    a.owner = parts ? L->owner[co] : nullptr;
-    a.owner_old = parts ? L->owner[1 - co] : nullptr;
-    a.Xc = parts ? L->Xheld[co] : nullptr;
-    a.Xold = parts ? L->Xheld[1 - co] : nullptr;
+    a.owner = parts ? L->map[co].owner : nullptr;
+    a.owner_old = parts ? L->map[old_map(co)].owner : nullptr;
+    a.Xc = parts ? L->map[co].X : nullptr;
+    a.Xold = parts ? L->map[old_map(co)].X : nullptr;
     a.U = L->U;
     a.W = L->W;
     a.FM = parts ? L->FM : nullptr;
@@ -203,8 +207,10 @@ void advance_state(lbmep_lattice *L) {
     L->cur = 1 - L->cur;
     L->pmode = true;
     if (L->np > 0 && L->cfg.move_particles) {
-        L->cur_owner = 1 - L->cur_owner;
-        if (L->overlap) L->lcur ^= 1;
+        L->cur_owner = next_map(L->cur_owner);
+        // with dynamics the classification follows the exchange and may
+        // rewrite the lists in place
+        if (L->overlap && !L->dynamic) L->lcur ^= 1;
     }
     L->level += 1;
 }
@@ -215,7 +221,7 @@ int materialize(lbmep_lattice *L) {
     if (!L->pmode) return LBMEP_OK;
     SweepArgs a = sweep_args(L);
     a.FM = nullptr;
-    HIP_TRY(launch_sweep(L->precision, kSweepReadout, kForceNone, a, L->block_x, 1, L->stream));
+    HIP_TRY(launch_sweep(L->precision, kSweepReadout, kForceNone, a, L->block_x, 1, nullptr, L->stream));
     L->cur = 1 - L->cur;
     L->pmode = false;
     return LBMEP_OK;
@@ -227,9 +233,9 @@ void free_particles(lbmep_lattice *L) {
     dev_free(L, L->U);
     dev_free(L, L->W);
     dev_free(L, L->FM);
-    for (int b = 0; b < 2; ++b) {
-        dev_free(L, L->Xheld[b]);
-        L->Xheld[b] = nullptr;
+    for (int b = 0; b < 3; ++b) {
+        dev_free(L, L->map[b].X);
+        L->map[b].X = nullptr;
     }
     for (int b = 0; b < 2; ++b) {
         dev_free(L, L->pcount_buf[b]);
@@ -246,7 +252,8 @@ size_t lattice_bytes(const lbmep_config *cfg, int32_t n_particles, double r_max,
     size_t b = 2 * (size_t)Q * Ns * storage_bytes(cfg->precision);  // two population grids
     b += round_up(N, 4096) + 4 * round_up(N, 4096) + 4 * N;      // flags, wall masks, wall list
     if (n_particles > 0) {
-        b += 2 * 4 * N + (size_t)n_particles * (16 + 6 * 3) * 8;  // maps, particle table
+        // maps of three levels (owners and bits), wall bits, particle table
+        b += 3 * (4 * N + 4 * map_words(N)) + 4 * map_words(N) + (size_t)n_particles * (16 + 7 * 3) * 8;
         b += (size_t)n_particles * (8 * (size_t)link_capacity(r_max) + 4);  // link lists
         if (overlap)  // overlapped stepping: the next level's link lists
             b += (size_t)n_particles * (8 * (size_t)link_capacity(r_max) + 4);
@@ -324,12 +331,6 @@ int destroy_lattice(lbmep_lattice *L, bool sync) {
     if (!L) return LBMEP_OK;
     hipSetDevice(L->cfg.device);
     if (sync) hipStreamSynchronize(L->stream);
-    if (L->stream2) {
-        hipStreamSynchronize(L->stream2);
-        hipStreamDestroy(L->stream2);
-        hipEventDestroy(L->ev_sweep);
-        hipEventDestroy(L->ev_chain);
-    }
     dev_free(L, L->f[0]);
     dev_free(L, L->f[1]);
     dev_free(L, L->flag);
@@ -338,7 +339,11 @@ int destroy_lattice(lbmep_lattice *L, bool sync) {
     dev_free(L, L->wall_count);
     dev_free(L, L->wall_scratch);
     for (int b = 0; b < 2; ++b) dev_free(L, L->plist_buf[b]);
-    for (int b = 0; b < 2; ++b) dev_free(L, L->owner[b]);
+    for (int b = 0; b < 3; ++b) {
+        dev_free(L, L->map[b].owner);
+        dev_free(L, L->map[b].bits);
+    }
+    dev_free(L, L->wallbits);
     dev_free(L, L->force);
     dev_free(L, L->red);
     dev_free(L, L->zeta);
@@ -374,7 +379,8 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
     L->cfg = *cfg;
     L->stream = (hipStream_t)cfg->stream;
     // overlapped stepping for a lattice of its own with moving particles
-    // (LBMEP_STEP_OVERLAP=0: every step in one stream, for comparisons)
+    // (LBMEP_STEP_OVERLAP=0: the classification after the exchange, in the
+    // same workgroups, for comparisons)
     L->overlap = heap == nullptr && cfg->move_particles;
     if (const char *e = std::getenv("LBMEP_STEP_OVERLAP")) L->overlap = L->overlap && std::atoi(e) != 0;
     L->precision = cfg->precision;
@@ -407,9 +413,12 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
     // order (every XCD streams the same planes; 3.71 ms, XCD-contiguous 256:
     // 4.05-4.13), FP16 with 512-cell segments in hardware order (1.99 ms in
     // three repeats against 2.16-2.21 with 256 XCD-contiguous), FP64 with
-    // 128-cell segments in XCD-contiguous order (7.75 ms; hardware 7.86)
+    // 128-cell segments.  FP64 in XCD-contiguous against hardware order: 7.61
+    // / 7.98 ms at 512^3 and 5.20 / 5.39 at 384 x 512^2, but 0.925 / 0.857 at
+    // 256 x 200 x 300, 1.81 / 1.64 at 384^2 x 200, 5.03 / 4.67 at 512 x 400^2
+    // and 7.03 / 6.79 at 600 x 500 x 400: the line is drawn at 10^8 cells
     L->block_x = L->precision == LBMEP_FP64 ? 128 : L->precision == LBMEP_FP16DEV ? 512 : 256;
-    L->xcd_swizzle = L->precision == LBMEP_FP64;
+    L->xcd_swizzle = L->precision == LBMEP_FP64 && g.N >= (size_t)100000000;
     L->cpt = 1;
     if (const char *e = std::getenv("LBMEP_CPT")) {
         const int c = std::atoi(e);
@@ -569,11 +578,19 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
     rc = materialize(L);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(L->stream));
-    if (n > 0 && !L->owner[0]) {
-        for (int b = 0; b < 2; ++b)
-            if (dev_alloc(L, (void **)&L->owner[b], 4 * L->g.N) != hipSuccess)
-                return fail(LBMEP_ENOMEM, "owner field allocation failed");
+    // maps of the current (0) and the previous level (2), with moving
+    // particles of the next (1)
+    for (int b = 0; n > 0 && b < 3; ++b) {
+        if (L->map[b].owner || (b == 1 && !L->cfg.move_particles)) continue;
+        if (dev_alloc(L, (void **)&L->map[b].owner, 4 * L->g.N) != hipSuccess ||
+            dev_alloc(L, (void **)&L->map[b].bits, 4 * map_words(L->g.N)) != hipSuccess) {
+            dev_free(L, L->map[b].owner);
+            L->map[b].owner = nullptr;
+            return fail(LBMEP_ENOMEM, "owner field allocation failed");
+        }
     }
+    if (n > 0 && !L->wallbits && dev_alloc(L, (void **)&L->wallbits, 4 * map_words(L->g.N)) != hipSuccess)
+        return fail(LBMEP_ENOMEM, "wall bitmap allocation failed");
     const int nlists = L->overlap ? 2 : 1;
     if ((size_t)n > L->np_cap) {
         free_particles(L);
@@ -581,8 +598,8 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
         bool ok = dev_alloc(L, (void **)&L->X0, b) == hipSuccess && dev_alloc(L, (void **)&L->U, b) == hipSuccess &&
                   dev_alloc(L, (void **)&L->W, b) == hipSuccess && dev_alloc(L, (void **)&L->R, b / 3) == hipSuccess &&
                   dev_alloc(L, (void **)&L->FM, 6 * b) == hipSuccess;
-        for (int r = 0; r < 2; ++r)
-            ok = ok && dev_alloc(L, (void **)&L->Xheld[r], b) == hipSuccess;
+        for (int r = 0; r < 3; ++r)
+            ok = ok && dev_alloc(L, (void **)&L->map[r].X, b) == hipSuccess;
         for (int r = 0; r < nlists; ++r)
             ok = ok && dev_alloc(L, (void **)&L->pcount_buf[r], 4 * (size_t)n) == hipSuccess;
         if (!ok) {
@@ -610,7 +627,7 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
         L->plist_entries = (size_t)n * pcap;
     }
     L->pcap = pcap;
-    L->halo_cap = n > 0 ? halo_capacity(rmax) : 0;
+    L->box_rows = n > 0 ? box_row_capacity(rmax) : 0;
     // boundary values of the potential and the dynamics belong to the
     // particle table they were given with
     dev_free(L, L->zeta);
@@ -747,7 +764,7 @@ static SorArgs sor_args(const lbmep_lattice *L) {
     a.psi = L->force;
     a.psi2 = L->psi2;
     a.flag = L->flag;
-    a.owner = L->np > 0 ? L->owner[L->cur_owner] : nullptr;
+    a.owner = L->np > 0 ? L->map[L->cur_owner].owner : nullptr;
     a.zeta = L->zeta;
     a.kappa2 = L->sor_kappa2;
     a.omega = L->sor_omega;
@@ -961,7 +978,7 @@ int lbmep_get_particles(lbmep_lattice *L, double *X, double *U, double *W) {
     if (rc) return rc;
     if (L->np == 0) return LBMEP_OK;
     const size_t b = 3 * (size_t)L->np * sizeof(double);
-    HIP_TRY(hipMemcpyAsync(X, L->Xheld[L->cur_owner], b, hipMemcpyDeviceToHost, L->stream));
+    HIP_TRY(hipMemcpyAsync(X, L->map[L->cur_owner].X, b, hipMemcpyDeviceToHost, L->stream));
     HIP_TRY(hipMemcpyAsync(U, L->U, b, hipMemcpyDeviceToHost, L->stream));
     HIP_TRY(hipMemcpyAsync(W, L->W, b, hipMemcpyDeviceToHost, L->stream));
     int32_t fast = 0;
@@ -1060,19 +1077,13 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
     int rc = set_device(L);
     if (rc) return rc;
     hipStream_t s = L->stream;
-    const ParticleArgs pa = particle_args(L);
     const bool solve = L->force_mode == kForcePotential && L->sor_set && L->sor_iters > 0;
-    // overlapped stepping: prescribed kinematics (the next level's positions
-    // do not depend on this step's forces)
-    const bool ov = L->overlap && L->np > 0 && L->cfg.move_particles && !L->dynamic;
-    if (ov && !L->stream2) {
-        HIP_TRY(hipStreamCreateWithFlags(&L->stream2, hipStreamNonBlocking));
-        HIP_TRY(hipEventCreateWithFlags(&L->ev_sweep, hipEventDisableTiming));
-        HIP_TRY(hipEventCreateWithFlags(&L->ev_chain, hipEventDisableTiming));
-    }
+    // the next level's map: with prescribed kinematics it is set in the
+    // sweep's launch and classified beside the exchange; with dynamics its
+    // positions follow from the exchange
+    const bool moving = L->np > 0 && L->cfg.move_particles;
+    const bool dyn = moving && L->dynamic;
     for (int32_t it = 0; it < nsteps; ++it) {
-        // the sweep needs the flags, map and lists of its level
-        if (ov && L->chain_pending) HIP_TRY(hipStreamWaitEvent(s, L->ev_chain, 0));
         // the EDL potential of this level's map, before the collision that
         // uses its force
         if (solve) {
@@ -1098,64 +1109,44 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
                          : L->sweep_nt == 1 ? kSweepPullNT
                          : L->sweep_nt == 2 ? kSweepPullNTS
                                             : kSweepPull;
-        HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x, L->cpt, s));
-        if (L->timing) HIP_TRY(hipEventRecord(e1, s));
-        if (ov) HIP_TRY(hipEventRecord(L->ev_sweep, s));
-        // bounce-back slots and momentum exchange next to solid cells
-        HIP_TRY(launch_near(L->precision, a, near_wall_blocks(L->g, L->has_walls), s));
-        if (L->dynamic && L->np > 0) {
-            // the particles move under this step's force and torque
-            DynArgs d;
-            d.g = L->g;
-            d.np = L->np;
-            d.acc = L->FM;
-            d.X = L->Xheld[L->cur_owner];
-            d.R = L->R;
-            d.q = L->q;
-            d.U = L->U;
-            d.W = L->W;
-            d.X0 = L->X0;
-            d.rho_p = L->rho_p;
-            for (int k = 0; k < 3; ++k) d.E[k] = L->Edyn[k];
-            d.too_fast = L->too_fast;
-            HIP_TRY(launch_dynamics(d, s));
-        }
-        if (L->np > 0 && L->cfg.move_particles) {
-            // kinematics, re-mapping and classification of the next level
-            const int b = 1 - L->cur_owner;
-            // the next level's link lists: the other buffer when overlapped
-            ParticleArgs pn = pa;
-            pn.plist = L->plist_buf[L->overlap ? L->lcur ^ 1 : L->lcur];
-            pn.pcount = L->pcount_buf[L->overlap ? L->lcur ^ 1 : L->lcur];
-            if (ov) {
-                // on the second stream once the sweep has read the previous
-                // map, the positions and the flags, while the exchange runs
-                // (it reads the current link lists, positions and
-                // post-collision state only): clear the map held two levels
-                // back, map and classify the next level
-                hipStream_t s2 = L->stream2;
-                HIP_TRY(hipStreamWaitEvent(s2, L->ev_sweep, 0));
-                HIP_TRY(launch_advance(pn, L->level + 1, L->Xheld[b], L->owner[b], s2));
-                HIP_TRY(launch_map_set(pn, L->Xheld[b], L->flag, L->owner[b], s2));
-                HIP_TRY(launch_classify_boxes(pn, L->Xheld[L->cur_owner], L->Xheld[b], L->flag,
-                                              L->owner[b], L->owner[L->cur_owner], s2));
-                HIP_TRY(hipEventRecord(L->ev_chain, s2));
-                L->chain_pending = true;
+        const int c = L->cur_owner;
+        PartsArgs q{};
+        q.wall_blocks = near_wall_blocks(L->g, L->has_walls);
+        q.pa = particle_args(L);
+        MapSetArgs ms{};
+        if (moving) {
+            const bool split = L->overlap && !dyn;
+            q.mode = dyn ? kPartsDyn : split ? kPartsSplit : kPartsOne;
+            // the next level's link lists
+            q.pa.plist = L->plist_buf[split ? L->lcur ^ 1 : L->lcur];
+            q.pa.pcount = L->pcount_buf[split ? L->lcur ^ 1 : L->lcur];
+            q.old = L->map[old_map(c)];
+            q.cur = L->map[c];
+            q.next = L->map[next_map(c)];
+            q.level = L->level + 1;
+            if (dyn) {
+                // the particles move under this step's force and torque
+                q.dyn.q = L->q;
+                q.dyn.U = L->U;
+                q.dyn.W = L->W;
+                q.dyn.X0 = L->X0;
+                q.dyn.rho_p = L->rho_p;
+                for (int k = 0; k < 3; ++k) q.dyn.E[k] = L->Edyn[k];
+                q.dyn.too_fast = L->too_fast;
             } else {
-                // clear the map buffer b held two levels back, move to
-                // level + 1
-                HIP_TRY(launch_advance(pn, L->level + 1, L->Xheld[b], L->owner[b], s));
-                HIP_TRY(launch_map_set(pn, L->Xheld[b], L->flag, L->owner[b], s));
-                HIP_TRY(launch_classify_boxes(pn, L->Xheld[L->cur_owner], L->Xheld[b], L->flag,
-                                              L->owner[b], L->owner[L->cur_owner], s));
+                ms.pa = q.pa;
+                ms.next = q.next;
+                ms.level = q.level;
             }
         }
+        HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x, L->cpt,
+                             moving && !dyn ? &ms : nullptr, s));
+        if (L->timing) HIP_TRY(hipEventRecord(e1, s));
+        // bounce-back slots and momentum exchange next to solid cells, and the
+        // next level's flags and link lists
+        HIP_TRY(launch_parts(L->precision, a, q, s));
+        if (dyn) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
         advance_state(L);
-    }
-    // later work on the lattice's stream follows the last classification
-    if (L->chain_pending) {
-        HIP_TRY(hipStreamWaitEvent(s, L->ev_chain, 0));
-        L->chain_pending = false;
     }
     return LBMEP_OK;
 }
@@ -1184,8 +1175,8 @@ int lbmep_get_macro(lbmep_lattice *L, double *rho, double *u, int on_device) {
         }
     }
     hipError_t e = launch_macro(L->precision, L->force_mode, L->g, L->f[L->cur], L->flag,
-                                L->np > 0 ? L->owner[L->cur_owner] : nullptr,
-                                L->np > 0 ? L->Xheld[L->cur_owner] : nullptr, L->U, L->W, L->force,
+                                L->np > 0 ? L->map[L->cur_owner].owner : nullptr,
+                                L->np > 0 ? L->map[L->cur_owner].X : nullptr, L->U, L->W, L->force,
                                 L->E, L->keps, L->force_mode == kForcePotential ? L->zeta : nullptr,
                                 drho, du, L->stream);
     if (e == hipSuccess && !on_device) {
@@ -1210,7 +1201,7 @@ int lbmep_get_particle_ft(lbmep_lattice *L, double *F, double *M) {
     if (rc) return rc;
     std::vector<double> h(6 * (size_t)L->np);
     double *out = L->FM + 12 * (size_t)L->np;
-    HIP_TRY(launch_finalize_ft(L->np, L->FM, L->Xheld[L->ft_buf], out, L->stream));
+    HIP_TRY(launch_finalize_ft(L->np, L->FM, L->map[L->ft_buf].X, out, L->stream));
     HIP_TRY(hipMemcpyAsync(h.data(), out, h.size() * sizeof(double), hipMemcpyDeviceToHost,
                            L->stream));
     HIP_TRY(hipStreamSynchronize(L->stream));
@@ -1238,7 +1229,7 @@ int lbmep_get_map(lbmep_lattice *L, uint8_t *flags, int32_t *owner) {
     }
     if (owner) {
         if (L->np > 0) {
-            HIP_TRY(hipMemcpyAsync(owner, L->owner[L->cur_owner], 4 * N, hipMemcpyDeviceToHost,
+            HIP_TRY(hipMemcpyAsync(owner, L->map[L->cur_owner].owner, 4 * N, hipMemcpyDeviceToHost,
                                    L->stream));
             HIP_TRY(hipStreamSynchronize(L->stream));
         } else {

@@ -156,19 +156,36 @@ struct ParticleArgs {
     int moving;
     int dynamic;       // Newton-Euler dynamics: X0 holds the current positions
     const double *X0, *R, *U, *W;
+    uint8_t *flag;     // cell flags (rewritten by the classification)
+    const uint32_t *wallbits;  // wall cells, one bit per cell; null without walls
     uint2 *plist;      // link lists written by the classification
     uint32_t *pcount;
     uint32_t pcap;
-    uint32_t halo_cap; // LDS bytes of the classification's staged box (one per cell)
+    uint32_t box_rows; // halo rows of a particle's box that the classification keeps in LDS
 };
+
+// the map of one time level: owner of every obstacle cell (kNone elsewhere),
+// the obstacle cells as one bit per cell (map_words words), and the particle
+// centres (3n)
+struct LevelMap {
+    uint32_t *owner;
+    uint32_t *bits;
+    double *X;
+};
+// words of a bitmap of N cells (two more are read past the last cell's)
+__host__ __device__ inline size_t map_words(size_t N) { return (N + 31) / 32 + 2; }
+
+// threads of the workgroups that work on one particle each in a step
+constexpr int kPartThreads = 512;
 
 // link-list capacity per particle for radii up to r_max: the cells whose
 // centre lies within one cell (per axis) of the ball, (2 ceil(R) + 3)^3
 uint32_t link_capacity(double r_max);
-// LDS bytes that stage the classification box of a particle of radius up to
-// r_max moving less than one cell per step, with its halo: (2 ceil(R) + 9)^3,
-// at most 32768 (larger boxes are classified from global memory)
-uint32_t halo_capacity(double r_max);
+// halo rows (of one bit per cell) of the classification box of a particle of
+// radius up to r_max moving less than one cell per step, and the LDS bytes of
+// the classification with them
+uint32_t box_row_capacity(double r_max);
+uint32_t classify_lds(uint32_t box_rows);
 
 // ---------------------------------------------------------------------------
 // Packed launches: one dispatch runs a kernel of the step for several
@@ -178,15 +195,55 @@ uint32_t halo_capacity(double r_max);
 // ---------------------------------------------------------------------------
 constexpr int kMaxPack = 64;
 
-struct LatticeDev {
-    // sweep arguments by state = cur | cur_owner << 1 (which population grid
-    // is the source, which owner map / positions are the current level's)
-    SweepArgs sweep[4];
+// Newton-Euler update of every particle from the step's accumulators: U, W
+// in place, X0 = the next level's positions; *too_fast = 1 when a velocity
+// component reaches one cell per step
+struct DynArgs {
+    const double *q;     // charges or null
+    double *U, *W, *X0;
+    double rho_p;
+    double E[3];
+    int32_t *too_fast;
+};
+
+// what a step's particle workgroups do after the sweep
+enum PartsMode {
+    kPartsNear = 0,   // bounce-back slots and momentum exchange only (fixed map)
+    kPartsSplit = 1,  // the exchange, and in other workgroups the classification
+                      // of the next level and the emptying of the previous
+                      // level's map (two sets of link lists)
+    kPartsOne = 2,    // the same, one workgroup per particle (one set of lists)
+    kPartsDyn = 3     // the exchange, the particle's dynamics, its cells of the
+                      // next level's map, the emptying of the previous level's
+};
+struct PartsArgs {
+    int mode;
+    int wall_blocks;      // workgroups of the wall links
+    ParticleArgs pa;      // with the link lists of the next level
+    LevelMap old, cur, next;
+    int64_t level;        // the next level
+    DynArgs dyn;
+};
+// mapping of the next level in the launch of the sweep: kMapThreads threads
+// per particle, the workgroups in groups of eight spread evenly among the
+// sweep's
+constexpr int kMapThreads = 64;
+struct MapSetArgs {
+    uint32_t groups;      // groups of eight workgroups; 0: none
+    uint32_t stride;      // every stride-th group of eight workgroups
     ParticleArgs pa;
-    uint8_t *flag;
-    uint32_t *owner[2];
-    double *Xheld[2];
+    LevelMap next;
+    int64_t level;
+};
+
+struct LatticeDev {
+    // sweep arguments by state = cur + 2 cur_owner (which population grid
+    // is the source, which map is the current level's)
+    SweepArgs sweep[6];
+    ParticleArgs pa;
+    LevelMap map[3];
     int wall_blocks;  // workgroups of the wall links in the exchange kernel
+    uint32_t map_blocks;  // workgroups of the packed sweep that map the next level
 };
 
 struct PackTable {
@@ -194,8 +251,8 @@ struct PackTable {
     int xcd_swizzle;
     uint32_t start[kMaxPack + 1];  // first workgroup of each entry; start[n] = total
     const LatticeDev *d[kMaxPack];
-    uint32_t state[kMaxPack];      // cur | cur_owner << 1 before the step
-    int64_t level[kMaxPack];       // kinematic level being advanced to (particle kernels)
+    uint32_t state[kMaxPack];      // cur + 2 cur_owner before the step
+    int64_t level[kMaxPack];       // kinematic level being advanced to
 };
 
 // entry of the workgroup b (the last entry whose first block is <= b)
@@ -215,15 +272,19 @@ __device__ __forceinline__ int pack_find(const PackTable &t, uint32_t b) {
 constexpr int kPackBlockX = 128;
 
 // kernels (host-side launchers); each returns hipError_t of the launch
+// (ms: the next level's mapping in the same launch, or null)
 hipError_t launch_sweep(int precision, int mode, int force_mode, const SweepArgs &a, int block_x,
-                        int cpt, hipStream_t s);
+                        int cpt, const MapSetArgs *ms, hipStream_t s);
 
-// bounce-back slots and momentum exchange after a sweep: one workgroup per
-// particle over its link list, then wall_blocks workgroups over the wall list
-hipError_t launch_near(int precision, const SweepArgs &a, int wall_blocks, hipStream_t s);
+// after a sweep: bounce-back slots and momentum exchange, one workgroup per
+// particle over its link list and q.wall_blocks workgroups over the wall
+// list, with the next level's map as q.mode says
+hipError_t launch_parts(int precision, const SweepArgs &a, const PartsArgs &q, hipStream_t s);
 int near_wall_blocks(const Grid &g, bool walls);
 // all workgroups of the exchange kernel (particles, then wall links)
 int near_blocks(int np, const Grid &g, bool walls);
+// LDS bytes of the exchange
+uint32_t near_lds();
 // compact list, in cell order, of the cells with a wall link (wallmask != 0);
 // scratch of wall_list_scratch(g) entries
 int wall_list_blocks(const Grid &g);
@@ -328,37 +389,19 @@ int invariants_blocks(const Grid &g);
 
 // particles
 hipError_t launch_positions(const ParticleArgs &pa, int64_t level, double *X, hipStream_t s);
-hipError_t launch_map_clear(const ParticleArgs &pa, const double *X, uint32_t *owner,
-                            hipStream_t s);
-hipError_t launch_map_set(const ParticleArgs &pa, const double *X, const uint8_t *flag,
-                          uint32_t *owner, hipStream_t s);
+// positions at `level` into m.X and the particles' cells into the emptied map m
+hipError_t launch_map_set(const ParticleArgs &pa, int64_t level, const LevelMap &m, hipStream_t s);
+hipError_t launch_wall_bits(const Grid &g, const uint8_t *flag, uint32_t *bits, hipStream_t s);
 // classify cells (flags + wall-link masks) over the whole grid
 hipError_t launch_classify_all(const Grid &g, uint8_t *flag, uint32_t *wallmask,
                                const uint32_t *owner, hipStream_t s);
-// classify around every particle (union of the boxes at Xold and Xnew,
-// grown by one cell), marking uncovered cells for the refill in the sweep,
-// and write each particle's link list
-hipError_t launch_classify_boxes(const ParticleArgs &pa, const double *Xold, const double *Xnew,
-                                 uint8_t *flag, const uint32_t *owner_new,
-                                 const uint32_t *owner_old, hipStream_t s);
+// classify around every particle (union of the boxes of the two levels, grown
+// by one cell), marking uncovered cells for the refill in the sweep, and
+// write each particle's link list
+hipError_t launch_classify_boxes(const ParticleArgs &pa, const LevelMap &old, const LevelMap &now,
+                                 hipStream_t s);
 // final force and torque (6n: F then M per particle) from the 12n sweep
 // accumulators and the particle centres of the streamed time level
-// Newton-Euler update of every particle from the step's accumulators: U, W
-// in place, X0 = the next level's positions; *too_fast = 1 when a velocity
-// component reaches one cell per step
-struct DynArgs {
-    Grid g;
-    int np;
-    const double *acc;   // 12 per particle (F_dev, M_dev, K, T)
-    const double *X;     // current positions
-    const double *R;
-    const double *q;     // charges or null
-    double *U, *W, *X0;
-    double rho_p;
-    double E[3];
-    int32_t *too_fast;
-};
-hipError_t launch_dynamics(const DynArgs &d, hipStream_t s);
 hipError_t launch_finalize_ft(int np, const double *acc, const double *X, double *out,
                               hipStream_t s);
 // map read-out in the ABI encoding
@@ -370,14 +413,6 @@ hipError_t launch_import_flags(const Grid &g, const uint8_t *in, uint8_t *flag, 
 
 // packed launches (tables filled by the host; entries with no work omitted)
 hipError_t launch_sweep_packed(int precision, int force_mode, const PackTable &t, hipStream_t s);
-hipError_t launch_near_packed(int precision, const PackTable &t, hipStream_t s);
-// clear each particle's cells of the map held two levels back, then move it
-// to t.level (one workgroup per particle)
-hipError_t launch_advance_packed(const PackTable &t, hipStream_t s);
-hipError_t launch_map_set_packed(const PackTable &t, hipStream_t s);
-hipError_t launch_classify_packed(const PackTable &t, hipStream_t s);
-// single-lattice form of the advance kernel
-hipError_t launch_advance(const ParticleArgs &pa, int64_t level, double *X, uint32_t *owner,
-                          hipStream_t s);
+hipError_t launch_parts_packed(int precision, const PackTable &t, uint32_t lds, hipStream_t s);
 
 }  // namespace lbmep

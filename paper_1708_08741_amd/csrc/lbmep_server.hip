@@ -10,11 +10,10 @@
 // runs on its own stream while the resident simulations keep stepping.
 //
 // Resident simulations advance together in chunks of steps.  Every step of a
-// chunk is a short series of packed launches: one dispatch of each kernel of
-// the step (sweep, bounce-back / exchange, kinematics, mapping,
-// classification, NEAR-list scan) covers every resident lattice, each
-// workgroup finding its lattice through a block table in the kernel
-// arguments.  A simulation whose last step is in a chunk has its results
+// chunk is two packed launches per (precision, force mode): the sweep with the
+// mapping of the next level, and the bounce-back / exchange with its
+// classification, each over every resident lattice, a workgroup finding its
+// lattice through a block table in the kernel arguments.  A simulation whose last step is in a chunk has its results
 // (force and torque of the last step, FP64 mass / momentum of the final
 // state, optionally the fields) computed right after that chunk on the same
 // stream; when the host sees the completion event it copies them out and
@@ -197,6 +196,12 @@ void fail_request(Request *r, int code, const std::string &msg) {
     r->error = msg;
 }
 
+// workgroups of the packed sweep that map the next level of a lattice
+uint32_t map_blocks(const lbmep_lattice *L) {
+    const uint32_t per = kPackBlockX / kMapThreads;
+    return L->np > 0 && L->cfg.move_particles ? ((uint32_t)L->np + per - 1u) / per : 0u;
+}
+
 // build the lattice of a request on the set-up stream, take its first step
 // there (it starts from a post-stream state), and write its descriptor
 int admit(lbmep_server *S, Slot &slot, Request *r) {
@@ -228,17 +233,14 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     // device descriptor for the packed launches
     LatticeDev h{};
     for (int cur = 0; cur < 2; ++cur)
-        for (int co = 0; co < 2; ++co) {
+        for (int co = 0; co < 3; ++co) {
             SweepArgs a = sweep_args_state(L, cur, co);
             a.nxb = (L->g.nx + kPackBlockX - 1) / kPackBlockX;
-            h.sweep[cur | (co << 1)] = a;
+            h.sweep[cur + 2 * co] = a;
         }
     h.pa = particle_args(L);
-    h.flag = L->flag;
-    for (int b = 0; b < 2; ++b) {
-        h.owner[b] = L->owner[b];
-        h.Xheld[b] = L->Xheld[b];
-    }
+    for (int b = 0; b < 3; ++b) h.map[b] = L->map[b];
+    h.map_blocks = map_blocks(L);
     h.wall_blocks = near_wall_blocks(L->g, L->has_walls);
     LatticeDev *d = static_cast<LatticeDev *>(S->arena.alloc(sizeof(LatticeDev)));
     if (!d) return undo(fail(LBMEP_ENOMEM, "arena exhausted (descriptor)"));
@@ -274,7 +276,7 @@ int enqueue_readout(lbmep_server *S, Slot &slot) {
     lbmep_lattice *L = slot.L;
     hipStream_t s = S->main;
     if (L->np > 0)
-        LBMEP_HIP_TRY(launch_finalize_ft(L->np, L->FM, L->Xheld[L->ft_buf],
+        LBMEP_HIP_TRY(launch_finalize_ft(L->np, L->FM, L->map[L->ft_buf].X,
                                          L->FM + 12 * (size_t)L->np, s));
     int rc = materialize(L);
     if (rc) return rc;
@@ -284,8 +286,8 @@ int enqueue_readout(lbmep_server *S, Slot &slot) {
     if (slot.fields) {
         const size_t N = L->g.N;
         LBMEP_HIP_TRY(launch_macro(L->precision, L->force_mode, L->g, L->f[L->cur], L->flag,
-                                   L->np > 0 ? L->owner[L->cur_owner] : nullptr,
-                                   L->np > 0 ? L->Xheld[L->cur_owner] : nullptr, L->U, L->W,
+                                   L->np > 0 ? L->map[L->cur_owner].owner : nullptr,
+                                   L->np > 0 ? L->map[L->cur_owner].X : nullptr, L->U, L->W,
                                    L->force, L->E, L->keps, nullptr, slot.fields,
                                    slot.fields + N, s));
     }
@@ -346,25 +348,28 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
         for (int prec = LBMEP_FP64; prec <= LBMEP_FP16DEV; ++prec)
             for (int fm = kForceNone; fm <= kForceCharge; ++fm) {
                 PackTable ts{}, tn{};
+                uint32_t lds = near_lds();
                 ts.xcd_swizzle = 1;
                 auto flush = [&]() -> int {
                     if (ts.n == 0) return LBMEP_OK;
                     LBMEP_HIP_TRY(launch_sweep_packed(prec, fm, ts, s));
-                    LBMEP_HIP_TRY(launch_near_packed(prec, tn, s));
+                    LBMEP_HIP_TRY(launch_parts_packed(prec, tn, lds, s));
                     S->st.packed_launches += 2;
                     ts.n = tn.n = 0;
                     ts.start[0] = tn.start[0] = 0;
+                    lds = near_lds();
                     return LBMEP_OK;
                 };
                 for (Slot *sl : act) {
                     lbmep_lattice *L = sl->L;
                     if (L->precision != prec || L->force_mode != fm) continue;
-                    const uint32_t state = (uint32_t)(L->cur | (L->cur_owner << 1));
+                    const uint32_t state = (uint32_t)(L->cur + 2 * L->cur_owner);
                     const uint32_t nxb = (uint32_t)((L->g.nx + kPackBlockX - 1) / kPackBlockX);
-                    const uint32_t sb = nxb * (uint32_t)L->g.ny * (uint32_t)L->g.nz;
+                    const uint32_t sb = map_blocks(L) + nxb * (uint32_t)L->g.ny * (uint32_t)L->g.nz;
+                    if (map_blocks(L)) lds = std::max(lds, classify_lds(L->box_rows));
                     ts.d[ts.n] = tn.d[tn.n] = sl->d;
                     ts.state[ts.n] = tn.state[tn.n] = state;
-                    ts.level[ts.n] = tn.level[tn.n] = L->level;
+                    ts.level[ts.n] = tn.level[tn.n] = L->level + 1;
                     ts.start[ts.n + 1] = ts.start[ts.n] + sb;
                     tn.start[tn.n + 1] =
                         tn.start[tn.n] + (uint32_t)near_blocks(L->np, L->g, L->has_walls);
@@ -378,33 +383,6 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                 int rc = flush();
                 if (rc) return rc;
             }
-        // kinematics, re-mapping and classification (with the link lists)
-        // of every moving lattice
-        PackTable tp{};
-        auto flush_p = [&]() -> int {
-            if (tp.n == 0) return LBMEP_OK;
-            LBMEP_HIP_TRY(launch_advance_packed(tp, s));
-            LBMEP_HIP_TRY(launch_map_set_packed(tp, s));
-            LBMEP_HIP_TRY(launch_classify_packed(tp, s));
-            S->st.packed_launches += 3;
-            tp.n = 0;
-            return LBMEP_OK;
-        };
-        for (Slot *sl : act) {
-            lbmep_lattice *L = sl->L;
-            if (!(L->np > 0 && L->cfg.move_particles)) continue;
-            tp.d[tp.n] = sl->d;
-            tp.state[tp.n] = (uint32_t)(L->cur | (L->cur_owner << 1));
-            tp.level[tp.n] = L->level + 1;
-            tp.start[tp.n + 1] = tp.start[tp.n] + (uint32_t)L->np;
-            tp.n++;
-            if (tp.n == kMaxPack) {
-                int rc = flush_p();
-                if (rc) return rc;
-            }
-        }
-        int rc = flush_p();
-        if (rc) return rc;
         for (Slot *sl : act) {
             advance_state(sl->L);
             sl->to_enqueue -= 1;

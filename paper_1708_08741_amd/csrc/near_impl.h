@@ -12,14 +12,15 @@
 //
 // Work distribution: one workgroup per particle walks the particle's link
 // list (written by the classification: the fluid cells next to the particle
-// with the directions that hit it), one link per lane in direction-major
-// order, so the particle's position and velocities are uniform, no owner
+// with the directions that hit it), one link per lane, so the particle's
+// position and velocities are uniform, no owner
 // look-up is needed, and force and torque are summed over each wavefront in
 // a fixed order (DPP row butterflies), the wavefronts' sums are combined in
 // wavefront order through LDS after one barrier, and the result is stored
 // without atomics.  Links to wall cells come from a list built when the
 // walls are set.
 #pragma once
+#include "particles_impl.h"
 #include "sweep_impl.h"
 
 namespace lbmep {
@@ -104,24 +105,20 @@ __device__ __forceinline__ typename Storage<ST>::CT load_fstar(const SweepArgs &
     return Storage<ST>::load(at<ST>(base, (OFF)c * (OFF)sizeof(ST)));
 }
 
-// One link of particle p in direction q (1..18, known at run time): the
-// bounce-back slot and the momentum exchange into the lane's sums.
+// One link of particle p from cell (x, y, z) in direction q (1..18, known at
+// run time) with the post-collision value fq: the bounce-back slot and the momentum exchange
+// into the lane's sums.
 template <typename ST, typename OFF>
-__device__ __forceinline__ void particle_link(const SweepArgs &a, uint32_t c, int q,
-                                              const double Xp[3], const double Up[3],
+__device__ __forceinline__ void particle_link(const SweepArgs &a, int x, int y, int z, int q,
+                                              typename Storage<ST>::CT fq, const double Xp[3], const double Up[3],
                                               const double Wp[3], double acc[kAcc]) {
     using T = Storage<ST>;
-    using CT = typename T::CT;
     const Grid &g = a.g;
-    const int nx = g.nx, ny = g.ny;
     const int cx = dir_comp(kPackCx, q), cy = dir_comp(kPackCy, q), cz = dir_comp(kPackCz, q);
-    int sx = (int)(c % (uint32_t)nx) + cx;
-    int sy = (int)((c / (uint32_t)nx) % (uint32_t)ny) + cy;
-    int sz = (int)(c / ((uint32_t)nx * (uint32_t)ny)) + cz;
+    int sx = x + cx, sy = y + cy, sz = z + cz;
     wrap_axis(sx, g.nx, g.per[0]);  // an obstacle cell: always inside
     wrap_axis(sy, g.ny, g.per[1]);
     wrap_axis(sz, g.nz, g.per[2]);
-    const CT fq = load_fstar<ST, OFF>(a, q, c);
     // lever arm r = x_s - x_C (minimum image) and u_s = U + W x r
     const double r0 = min_image(((double)sx + 0.5) - Xp[0], g.nx, g.per[0]);
     const double r1 = min_image(((double)sy + 0.5) - Xp[1], g.ny, g.per[1]);
@@ -164,27 +161,32 @@ __device__ __forceinline__ void particle_link(const SweepArgs &a, uint32_t c, in
     store_slot<ST, OFF>(a, q, s, fq, mw);
 }
 
-// waves per particle in the exchange kernel (a 256-thread workgroup)
-constexpr int kNearWaves = 4;
-constexpr int kNearThreads = 64 * kNearWaves;
-// list entries per pass: their links (at most 18 each) are staged in LDS
-constexpr int kNearEntries = 128;
+constexpr int kPartWaves = kPartThreads / 64;
+// LDS of near_particle: per pass the cells of kPartThreads list entries and
+// their links (at most 18 each) as entry | direction, then the sums
+constexpr uint32_t kNearLds = kPartThreads * 12 + kPartThreads * (Q - 1) * 2 +
+                              (kPartWaves + 1) * kAcc * 8 + 64;
 
 // All links of particle p (its list from the classification: cells with the
 // directions whose neighbour is an obstacle cell of p), one workgroup: the
 // bounce-back slots and the momentum exchange, summed in a fixed order and
 // stored (no atomics: the result does not depend on scheduling).  The
-// workgroup takes 128 list entries per pass and lays their links out
-// direction by direction (per direction in list order, i.e. neighbouring
-// cells along x), then works through them 256 at a time, one link per lane:
-// every lane does useful work whatever the links per cell, and neighbouring
-// lanes load and store neighbouring values of one population.
+// workgroup takes one list entry per thread and pass and lays their links
+// out one after the other, then works through them one link per lane, three
+// per lane at a time with their loads issued together.  Bound by the chain
+// of dependent round trips (list, links, values), so a particle of radius 4
+// (about 300 entries, 1200 links) should fit one pass of one round: with 256
+// threads and 128 entries per pass it took three passes of two rounds.
+// Returns the 12 sums in LDS.
 template <typename ST, typename OFF>
-__device__ __forceinline__ void near_particle(const SweepArgs &a, uint32_t p) {
-    __shared__ uint32_t lcell[kNearEntries * (Q - 1)];
-    __shared__ uint8_t lq[kNearEntries * (Q - 1)];
-    __shared__ uint32_t qcnt[2][Q];  // per direction: links of each half of the pass
-    __shared__ double part[kNearWaves][kAcc];
+__device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint32_t p,
+                                                       unsigned char *lds) {
+    using CT = typename Storage<ST>::CT;
+    double *part = reinterpret_cast<double *>(lds);      // [kPartWaves + 1][kAcc]
+    uint32_t *ecell = reinterpret_cast<uint32_t *>(part + (kPartWaves + 1) * kAcc);
+    uint32_t *ex = ecell + kPartThreads, *eyz = ex + kPartThreads;  // its coordinates
+    uint32_t *wsum = eyz + kPartThreads;
+    uint16_t *link = reinterpret_cast<uint16_t *>(wsum + 16);
     const int tid = (int)threadIdx.x, lane = (int)__lane_id(), wave = tid / 64;
     const uint2 *list = a.plist + (size_t)p * a.pcap;
     const uint32_t n = a.pcount[p];
@@ -194,52 +196,88 @@ __device__ __forceinline__ void near_particle(const SweepArgs &a, uint32_t p) {
     double acc[kAcc];
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (uint32_t e0 = 0; e0 < n; e0 += kNearEntries) {
-        // waves 0 and 1 hold the pass's entries (one per lane); per direction
-        // a ballot gives each lane its rank and each wave its count
-        const uint32_t i = e0 + (uint32_t)tid;
-        const bool mine = wave < 2 && i < n;
-        const uint2 e = mine ? list[i] : make_uint2(0u, 0u);
-        uint32_t rank[Q - 1];
-#pragma unroll
-        for (int q = 1; q < Q; ++q) {
-            const unsigned long long b = __ballot((e.y >> (q - 1)) & 1u);
-            rank[q - 1] = (uint32_t)__popcll(b & below);
-            if (lane == 0 && wave < 2) qcnt[wave][q] = (uint32_t)__popcll(b);
+    for (uint32_t i0 = 0; i0 < n; i0 += kPartThreads) {
+        const uint32_t i = i0 + (uint32_t)tid;
+        const uint2 e = i < n ? list[i] : make_uint2(0u, 0u);
+        if (e.y) {  // one index decomposition per cell, not per link
+            const uint32_t row = e.x / (uint32_t)a.g.nx, z = row / (uint32_t)a.g.ny;
+            ecell[tid] = e.x;
+            ex[tid] = e.x - row * (uint32_t)a.g.nx;
+            eyz[tid] = (row - z * (uint32_t)a.g.ny) | z << 16;  // ny, nz <= 65535
         }
+        uint32_t total;
+        uint32_t pos = part::block_prefix((uint32_t)__popc(e.y), wsum, &total);
+        for (uint32_t m = e.y; m; m &= m - 1u) link[pos++] = (uint16_t)(tid << 5 | __ffs((int)m));
         __syncthreads();
-        // links in direction-major order: direction q starts after all links
-        // of the lower directions, wave 1's after wave 0's
-        uint32_t start = 0, total = 0;
+        constexpr int U = 3;
+        for (uint32_t k0 = (uint32_t)tid; k0 < total; k0 += U * kPartThreads) {
+            uint32_t en[U];
+            int q[U];
+            CT fq[U];
 #pragma unroll
-        for (int q = 1; q < Q; ++q) {
-            const uint32_t off = start + (wave == 1 ? qcnt[0][q] : 0u);
-            if (mine && ((e.y >> (q - 1)) & 1u)) {
-                lcell[off + rank[q - 1]] = e.x;
-                lq[off + rank[q - 1]] = (uint8_t)q;
+            for (int u = 0; u < U; ++u) {
+                const uint32_t k = k0 + (uint32_t)u * kPartThreads;
+                const uint32_t l = link[k < total ? k : k0];
+                en[u] = l >> 5;
+                q[u] = (int)(l & 31u);
+                fq[u] = load_fstar<ST, OFF>(a, q[u], ecell[en[u]]);
             }
-            start += qcnt[0][q] + qcnt[1][q];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k0 + (uint32_t)u * kPartThreads < total) {
+                    const uint32_t yz = eyz[en[u]];
+                    particle_link<ST, OFF>(a, (int)ex[en[u]], (int)(yz & 0xFFFFu), (int)(yz >> 16), q[u],
+                                           fq[u], Xp, Up, Wp, acc);
+                }
         }
-        total = start;
-        __syncthreads();
-        for (uint32_t k = (uint32_t)tid; k < total; k += kNearThreads)
-            particle_link<ST, OFF>(a, lcell[k], (int)lq[k], Xp, Up, Wp, acc);
-        __syncthreads();  // lcell, lq and qcnt are rewritten by the next pass
+        __syncthreads();  // the links are rewritten by the next pass
     }
     // wave sums, then the waves' sums in wave order: a fixed order
 #pragma unroll
     for (int k = 0; k < kAcc; ++k) {
         const double t = wave_sum_f64(acc[k]);
-        if (lane == 0) part[wave][k] = t;
+        if (lane == 0) part[wave * kAcc + k] = t;
     }
     __syncthreads();
-    if (threadIdx.x < kAcc && a.FM) {
-        double t = part[0][threadIdx.x];
+    double *sum = part + kPartWaves * kAcc;
+    if (tid < kAcc) {
+        double t = part[tid];
 #pragma unroll
-        for (int w = 1; w < kNearWaves; ++w) t += part[w][threadIdx.x];
-        a.FM[kAcc * (size_t)p + threadIdx.x] = t;
+        for (int w = 1; w < kPartWaves; ++w) t += part[w * kAcc + tid];
+        sum[tid] = t;
+        if (a.FM) a.FM[kAcc * (size_t)p + tid] = t;
     }
+    return sum;
+}
+
+// Newton-Euler update of particle p (Alg. "Electrophoresis Algorithm": the
+// hydrodynamic force and torque of the step and the force q E of the
+// applied field move the particle), one explicit step, velocities first:
+//     U += (F_h + q E) / m,  W += M_h / I,  X(n+1) = X(n) + U,
+// m = rho_p 4/3 pi R^3, I = 2/5 m R^2; F_h, M_h assembled from the 12 sums t
+// as k_finalize_ft does, in the same order; one component per thread
+__device__ __forceinline__ void move_particle(const ParticleArgs &pa, const DynArgs &d, uint32_t p,
+                                              const double *t, const double *Xp) {
+    if (threadIdx.x >= 3) return;
+    const int k = (int)threadIdx.x, k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+    const double F = t[k] + t[6 + k] / 18.0;
+    const double M = t[3 + k] + (t[9 + k] - (Xp[k1] * t[6 + k2] - Xp[k2] * t[6 + k1])) / 18.0;
+    const double R = pa.R[p];
+    const double m = d.rho_p * (4.0 / 3.0) * 3.14159265358979323846 * R * R * R;
+    const double I = 0.4 * m * R * R;
+    const double qp = d.q ? d.q[p] : 0.0;
+    const size_t i = 3 * (size_t)p + (size_t)k;
+    const int len = k == 0 ? pa.g.nx : k == 1 ? pa.g.ny : pa.g.nz;
+    const double u = d.U[i] + (F + qp * d.E[k]) / m;
+    d.U[i] = u;
+    d.W[i] = d.W[i] + M / I;
+    double x = Xp[k] + u;
+    if (pa.g.per[k]) {
+        x = x - (double)len * floor(x / (double)len);
+        if (x >= (double)len) x -= (double)len;
+    }
+    d.X0[i] = x;
+    if (!(fabs(u) < 1.0)) *d.too_fast = 1;
 }
 
 // Links to wall cells (a list fixed while the walls are): plain bounce-back
@@ -272,31 +310,70 @@ __device__ __forceinline__ void near_walls(const SweepArgs &a, uint32_t blk, uin
     }
 }
 
-// one particle per workgroup of the exchange kernel
-__host__ __device__ inline uint32_t near_particle_blocks(int np) { return (uint32_t)np; }
+// LDS of a particle workgroup: the exchange or the classification
+inline uint32_t parts_lds(int mode, uint32_t box_rows) {
+    const uint32_t c = classify_lds(box_rows);
+    return mode == kPartsNear || mode == kPartsDyn ? kNearLds : c > kNearLds ? c : kNearLds;
+}
 
-// workgroups [0, np): one particle each; the rest: the wall links
+// the particle workgroups of a step, blk of np (2 np when split) + wall
+// blocks.  The classification of the next level reads that level's map
+// (complete since the sweep's launch), the current one and the walls, and
+// writes flags and the next level's link lists; the exchange reads the
+// current lists and the post-collision state; nothing reads the previous
+// level's map any more: they run side by side.
 template <typename ST, typename OFF>
-__device__ __forceinline__ void near_block(const SweepArgs &a, uint32_t blk, uint32_t nblk) {
-    const uint32_t pb = near_particle_blocks(a.np);
-    if (blk < pb) {
-        near_particle<ST, OFF>(a, blk);
-    } else {
-        near_walls<ST, OFF>(a, blk - pb, nblk - pb);
+__device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs &q, uint32_t blk) {
+    extern __shared__ __align__(16) unsigned char part_lds[];
+    const uint32_t np = (uint32_t)a.np;
+    if (q.mode == kPartsSplit) {
+        if (blk < np) {  // first: these take longer
+            part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
+            part::map_clear(q.pa, (int)blk, q.old);
+            return;
+        }
+        blk -= np;
+    }
+    if (blk >= np) {
+        near_walls<ST, OFF>(a, blk - np, (uint32_t)q.wall_blocks);
+        return;
+    }
+    const double *sum = near_particle<ST, OFF>(a, blk, part_lds);
+    if (q.mode == kPartsOne) {
+        __syncthreads();  // part_lds is reused
+        part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
+        part::map_clear(q.pa, (int)blk, q.old);
+    } else if (q.mode == kPartsDyn) {
+        __syncthreads();
+        move_particle(q.pa, q.dyn, blk, sum, a.Xc + 3 * (size_t)blk);
+        __syncthreads();  // X0 is read by every thread
+        part::advance_set(q.pa, (int)blk, q.level, q.next, (int)threadIdx.x, (int)blockDim.x);
+        part::map_clear(q.pa, (int)blk, q.old);
     }
 }
 
 template <typename ST, typename OFF>
-__global__ void __launch_bounds__(256) k_near(SweepArgs a) {
-    near_block<ST, OFF>(a, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(kPartThreads, 4) k_parts(SweepArgs a, PartsArgs q) {
+    parts_block<ST, OFF>(a, q, blockIdx.x);
 }
 
+// one workgroup per particle for several lattices in one dispatch
 template <typename ST>
-__global__ void __launch_bounds__(256) k_near_packed(PackTable t) {
+__global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
     const int e = pack_find(t, blockIdx.x);
     const LatticeDev *d = t.d[e];
-    const SweepArgs a = d->sweep[t.state[e]];
-    near_block<ST, uint32_t>(a, blockIdx.x - t.start[e], t.start[e + 1] - t.start[e]);
+    const uint32_t st = t.state[e];
+    const SweepArgs a = d->sweep[st];
+    const uint32_t c = st >> 1;
+    PartsArgs q{};
+    q.mode = d->pa.moving && d->pa.np > 0 ? kPartsOne : kPartsNear;
+    q.wall_blocks = d->wall_blocks;
+    q.pa = d->pa;
+    q.old = d->map[c == 0 ? 2 : c - 1];
+    q.cur = d->map[c];
+    q.next = d->map[c == 2 ? 0 : c + 1];
+    q.level = t.level[e];
+    parts_block<ST, uint32_t>(a, q, blockIdx.x - t.start[e]);
 }
 
 // workgroups of the wall pass (0 without wall cells)
@@ -309,22 +386,23 @@ inline int near_wall_blocks(size_t N, bool walls) {
 }
 
 template <typename ST>
-hipError_t launch_near_packed_typed(const PackTable &t, hipStream_t s) {
+hipError_t launch_parts_packed_typed(const PackTable &t, uint32_t lds, hipStream_t s) {
     const uint32_t total = t.start[t.n];
     if (t.n == 0 || total == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_near_packed<ST>), dim3(total), dim3(256), 0, s, t);
+    hipLaunchKernelGGL((k_parts_packed<ST>), dim3(total), dim3(kPartThreads), lds, s, t);
     return hipGetLastError();
 }
 
 template <typename ST>
-hipError_t launch_near_typed(const SweepArgs &a, int wall_blocks, hipStream_t s) {
-    const unsigned blocks = near_particle_blocks(a.np) + (unsigned)wall_blocks;
+hipError_t launch_parts_typed(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {
+    const unsigned blocks = (unsigned)a.np * (q.mode == kPartsSplit ? 2u : 1u) + (unsigned)q.wall_blocks;
     if (blocks == 0) return hipSuccess;
+    const uint32_t lds = parts_lds(q.mode, q.pa.box_rows);
     const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);
     if (small)
-        hipLaunchKernelGGL((k_near<ST, uint32_t>), dim3(blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_parts<ST, uint32_t>), dim3(blocks), dim3(kPartThreads), lds, s, a, q);
     else
-        hipLaunchKernelGGL((k_near<ST, uint64_t>), dim3(blocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_parts<ST, uint64_t>), dim3(blocks), dim3(kPartThreads), lds, s, a, q);
     return hipGetLastError();
 }
 

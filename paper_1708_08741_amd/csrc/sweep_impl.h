@@ -26,6 +26,7 @@
 // Byte offsets are 32-bit (global loads/stores with a scalar base) whenever a
 // population array is smaller than 4 GiB.
 #pragma once
+#include "particles_impl.h"
 #include "potential_impl.h"
 
 namespace lbmep {
@@ -402,13 +403,26 @@ __device__ __forceinline__ void slip_pair(const SweepArgs &a, const int (&o)[3],
     *v = t;
 }
 
-// one thread per cell of free-slip face (ax, side)
+// one thread per cell of every free-slip face, the faces one after the other
+// (each slot belongs to one pair, so the faces need no order among them); one
+// launch instead of one per face: 6 x 10.7 us at 216 x 312 x 216
 template <typename ST>
-__global__ void __launch_bounds__(256) k_slip_swap(SweepArgs a, int ax, int side) {
+__global__ void __launch_bounds__(256) k_slip_swap(SweepArgs a) {
     const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
+    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int face = -1;
+    for (int f = 0; f < 6; ++f) {
+        if (!(a.slip & (1 << f))) continue;
+        const size_t cells = (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
+        if (i < cells) {
+            face = f;
+            break;
+        }
+        i -= cells;
+    }
+    if (face < 0) return;
+    const int ax = face / 2, side = face & 1;
     const int a1 = ax == 0 ? 1 : 0, a2 = ax == 2 ? 1 : 2;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)len[a1] * (size_t)len[a2]) return;
     int o[3];
     o[ax] = side ? len[ax] - 1 : 0;
     o[a1] = (int)(i % (size_t)len[a1]);
@@ -716,10 +730,34 @@ __device__ __forceinline__ void sweep_segment(const SweepArgs &a, uint32_t lb) {
     for (int r = 0; r < CPT; ++r) finish_cell<ST, FMODE, OFF, MODE>(a, x, y0 + r, z, c[r]);
 }
 
+// workgroup b of the next level's mapping: a particle per kMapThreads threads
+// (the rows of a ball of radius 4 are 11^2; fewer workgroups with several
+// particles take fewer of the sweep's places)
+__device__ __forceinline__ void map_particles(const ParticleArgs &pa, uint32_t b, int64_t level,
+                                              const LevelMap &m) {
+    const uint32_t p = b * (blockDim.x / kMapThreads) + threadIdx.x / kMapThreads;
+    if (p < (uint32_t)pa.np)
+        part::advance_set(pa, (int)p, level, m, (int)(threadIdx.x % kMapThreads), kMapThreads);
+}
+
+// nseg segments; with ms.groups, the next level's mapping runs in the same
+// launch: its workgroups come in groups of eight (so that a segment stays on
+// its XCD) spread evenly among the sweep's, which hides their few dependent
+// round trips behind the streaming (a launch of its own took 10 us at 128^3
+// and 36-85 us at 512^3 with 4096 particles)
 template <typename ST, int FMODE, typename OFF, int MODE, int CPT>
-__global__ void __launch_bounds__(512) k_sweep(SweepArgs a) {
-    const uint32_t lb = a.xcd_swizzle ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
-    sweep_segment<ST, FMODE, OFF, MODE, CPT>(a, lb);
+__global__ void __launch_bounds__(512) k_sweep(SweepArgs a, MapSetArgs ms, uint32_t nseg) {
+    uint32_t b = blockIdx.x;
+    if (ms.groups) {
+        const uint32_t g = b >> 3, m = g / ms.stride;
+        if (g - m * ms.stride == 0 && m < ms.groups) {
+            map_particles(ms.pa, 8u * m + (b & 7u), ms.level, ms.next);
+            return;
+        }
+        b -= 8u * min(ms.groups, (g + ms.stride - 1u) / ms.stride);
+        if (b >= nseg) return;
+    }
+    sweep_segment<ST, FMODE, OFF, MODE, CPT>(a, a.xcd_swizzle ? xcd_remap(b, nseg) : b);
 }
 
 // the gather sweep of several lattices in one dispatch
@@ -727,10 +765,19 @@ template <typename ST, int FMODE>
 __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
     const uint32_t gb = t.xcd_swizzle ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
     const int e = pack_find(t, gb);
-    const SweepArgs a = t.d[e]->sweep[t.state[e]];
+    const LatticeDev *d = t.d[e];
+    uint32_t b = gb - t.start[e];
+    // the entry's first workgroups map its next level
+    if (b < d->map_blocks) {
+        const uint32_t c = t.state[e] >> 1;
+        map_particles(d->pa, b, t.level[e], d->map[c == 2 ? 0 : c + 1]);
+        return;
+    }
+    b -= d->map_blocks;
+    const SweepArgs a = d->sweep[t.state[e]];
     // streaming hints as in the single-lattice default: stores only
     constexpr int MODE = kPullNTS;
-    sweep_segment<ST, FMODE, uint32_t, MODE, 1>(a, gb - t.start[e]);
+    sweep_segment<ST, FMODE, uint32_t, MODE, 1>(a, b);
 }
 
 template <typename ST>
@@ -751,7 +798,7 @@ hipError_t launch_sweep_packed_typed(int force_mode, const PackTable &t, hipStre
 // host launcher for one storage type; cpt = cells per thread (1 or 2)
 template <typename ST>
 hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x, int cpt,
-                        hipStream_t s) {
+                        const MapSetArgs *map, hipStream_t s) {
     // 32-bit byte offsets when two population arrays fit in 4 GiB (the
     // gather addresses an opposite pair from one base)
     const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);
@@ -759,25 +806,42 @@ hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x, int 
         // free-slip faces: the reflected values into the slots the gather
         // reads beyond those faces
         const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
-        for (int f = 0; f < 6; ++f) {
-            if (!(a.slip & (1 << f))) continue;
-            const int ax = f / 2;
-            const size_t cells = (size_t)len[ax == 0 ? 1 : 0] * (size_t)len[ax == 2 ? 1 : 2];
-            hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0,
-                               s, a, ax, f & 1);
-        }
+        size_t cells = 0;
+        for (int f = 0; f < 6; ++f)
+            if (a.slip & (1 << f))
+                cells += (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
+        hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, a);
     }
     if (!small || mode == kReadout) cpt = 1;
     // the workgroups-per-CU cap was measured on the 32-bit-offset kernel;
     // the 64-bit one runs faster without it (864 x 1248 x 864 FP32: 24.6
     // against 27.5 ms)
     if (!small) a.lds = 0;
+    // no more wavefronts than the row has cells for (101 cells in segments of
+    // 256: half the wavefronts would load and drop cells beyond the row)
+    const int full_x = block_x;
+    if (block_x > (a.g.nx + 63) / 64 * 64) block_x = (a.g.nx + 63) / 64 * 64;
+    // a.lds caps the workgroups per CU at their default width; narrower ones
+    // keep the same number of wavefronts (128^3 FP32, two wavefronts per row:
+    // 4 workgroups 77 us, 8 workgroups 64 us, none 65 us)
+    if (a.lds && block_x < full_x) a.lds = a.lds / (uint32_t)full_x * (uint32_t)block_x / 16 * 16;
     a.nxb = (a.g.nx + block_x - 1) / block_x;
     const size_t nblocks = (size_t)a.nxb * ((a.g.ny + cpt - 1) / cpt) * a.g.nz;
     const dim3 block(block_x, 1, 1);
-    const dim3 grid((unsigned)nblocks, 1, 1);
+    MapSetArgs ms{};
+    size_t total = nblocks;
+    if (map && map->pa.np > 0) {
+        ms = *map;
+        const uint32_t per = 8u * (uint32_t)(block_x / kMapThreads);
+        ms.groups = ((uint32_t)map->pa.np + per - 1u) / per;
+        const size_t groups = (nblocks + 7) / 8 + ms.groups;
+        ms.stride = (uint32_t)(groups / ms.groups);
+        total = 8 * groups;
+    }
+    const dim3 grid((unsigned)total, 1, 1);
+    const uint32_t nseg = (uint32_t)nblocks;
 #define LBMEP_LAUNCH(MD, FM, OFF, C) \
-    hipLaunchKernelGGL((k_sweep<ST, FM, OFF, MD, C>), grid, block, a.lds, s, a)
+    hipLaunchKernelGGL((k_sweep<ST, FM, OFF, MD, C>), grid, block, a.lds, s, a, ms, nseg)
 #define LBMEP_BY_FORCE(MD, OFF, C)                                           \
     do {                                                                     \
         if (force_mode == kForceNone) LBMEP_LAUNCH(MD, kForceNone, OFF, C);      \

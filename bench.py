@@ -38,9 +38,9 @@ DTYPE = {"fp64": "f64", "fp32dev": "f32", "fp16dev": "f32"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_stream_collide_512.json")
 # the gather / collide sweep instantiation timed per precision (storage type,
 # charge force, 32-bit offsets, streaming-hint mode, one cell per thread)
-SWEEP_KERNEL = {"fp32dev": "k_sweep<float, 2, unsigned int, 4, 1>",
-                "fp64": "k_sweep<double, 2, unsigned int, 4, 1>",
-                "fp16dev": "k_sweep<__half, 2, unsigned int, 4, 1>"}
+SWEEP_KERNEL = {"fp32dev": "k_sweep<float, 2, unsigned int, 4>",
+                "fp64": "k_sweep<double, 2, unsigned int, 4>",
+                "fp16dev": "k_sweep<__half, 2, unsigned int, 4>"}
 KERNEL_SRC = os.path.join(ROOT, "paper_1708_08741_amd", "csrc", "sweep_impl.h")
 # the sweep's launch shape (segment width, block order, population stride) is
 # set in the API source: counters taken on other settings do not apply

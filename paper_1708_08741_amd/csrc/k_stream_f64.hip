@@ -7,8 +7,8 @@
 namespace lbmep {
 
 hipError_t launch_sweep_f64(int mode, int force_mode, const SweepArgs &a, int block_x,
-                            int cpt, const MapSetArgs *ms, hipStream_t s) {
-    return sweep::launch_typed<double>(mode, force_mode, a, block_x, cpt, ms, s);
+                            const MapSetArgs *ms, hipStream_t s) {
+    return sweep::launch_typed<double>(mode, force_mode, a, block_x, ms, s);
 }
 
 hipError_t launch_parts_f64(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {

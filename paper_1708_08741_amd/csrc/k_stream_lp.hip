@@ -6,14 +6,14 @@
 namespace lbmep {
 
 hipError_t launch_sweep_f64(int mode, int force_mode, const SweepArgs &a, int block_x,
-                            int cpt, const MapSetArgs *ms, hipStream_t s);
+                            const MapSetArgs *ms, hipStream_t s);
 
 hipError_t launch_sweep(int precision, int mode, int force_mode, const SweepArgs &a, int block_x,
-                        int cpt, const MapSetArgs *ms, hipStream_t s) {
-    if (precision == LBMEP_FP64) return launch_sweep_f64(mode, force_mode, a, block_x, cpt, ms, s);
+                        const MapSetArgs *ms, hipStream_t s) {
+    if (precision == LBMEP_FP64) return launch_sweep_f64(mode, force_mode, a, block_x, ms, s);
     if (precision == LBMEP_FP32DEV)
-        return sweep::launch_typed<float>(mode, force_mode, a, block_x, cpt, ms, s);
-    return sweep::launch_typed<__half>(mode, force_mode, a, block_x, cpt, ms, s);
+        return sweep::launch_typed<float>(mode, force_mode, a, block_x, ms, s);
+    return sweep::launch_typed<__half>(mode, force_mode, a, block_x, ms, s);
 }
 
 hipError_t launch_parts_f64(const SweepArgs &a, const PartsArgs &q, hipStream_t s);

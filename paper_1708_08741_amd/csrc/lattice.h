@@ -94,7 +94,6 @@ struct lbmep_lattice {
     double *red = nullptr;
     int red_blocks = 0;
     int block_x = 128;
-    int cpt = 1;  // cells per thread of the sweep (consecutive rows)
     int sor_zc = 8;   // planes per workgroup of the SOR's interior half-sweep (set per precision)
     int sor_wx = 4;   // waves along x of its workgroup tile (1, 2, 4)
     int sor_xcd = 1;  // XCD-contiguous tile order
@@ -102,7 +101,7 @@ struct lbmep_lattice {
     int sor_near_blocks = 0;  // workgroups of the SOR's boundary list part (0: default)
     int sor_mzc = 0;  // planes per workgroup of the one-pass SOR iteration (0: by grid)
     int sor_mrw = 4;  // rows per thread of the one-pass SOR iteration (set per precision)
-    int xcd_swizzle = 1;
+    int xcd_swizzle = 0;
     int sweep_wgcu = -1;  // sweep: workgroups per CU (0: no cap, -1: per precision and force)
     int sweep_nt = 2;  // streaming hints of the sweep: 0 none, 1 loads + stores, 2 stores
     // overlapped stepping (moving particles): two sets of link lists, so that

@@ -176,7 +176,8 @@ SweepArgs sweep_args_state(const lbmep_lattice *L, int cur, int co) {
     a.ae = L->ae;
     a.ao = L->ao;
     a.tf = trt_f32_constants(L);
-    a.nxb = 0;
+    a.mx = (uint64_t(1) << 63) / (uint64_t)L->g.nx + 1;
+    a.my = (uint64_t(1) << 63) / (uint64_t)L->g.ny + 1;
     a.xcd_swizzle = L->xcd_swizzle;
     a.slip = L->slip;
     // measured at 512^3 (4096 moving spheres, two repeats): a cap of 4
@@ -221,7 +222,7 @@ int materialize(lbmep_lattice *L) {
     if (!L->pmode) return LBMEP_OK;
     SweepArgs a = sweep_args(L);
     a.FM = nullptr;
-    HIP_TRY(launch_sweep(L->precision, kSweepReadout, kForceNone, a, L->block_x, 1, nullptr, L->stream));
+    HIP_TRY(launch_sweep(L->precision, kSweepReadout, kForceNone, a, L->block_x, nullptr, L->stream));
     L->cur = 1 - L->cur;
     L->pmode = false;
     return LBMEP_OK;
@@ -402,28 +403,23 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
         delete L;
         return fail(LBMEP_EINVAL, "odd relaxation rate outside ]-2,0[");
     }
-    // launch shape of the sweep: x-segments of block_x threads (whole
-    // wavefronts), cpt cells per thread on consecutive rows, dealt onto XCDs
-    // in contiguous runs, streaming (non-temporal) hints on its loads and
-    // stores (every value is read once and written once per step);
-    // LBMEP_BLOCK_X, LBMEP_CPT, LBMEP_XCD_SWIZZLE and LBMEP_SWEEP_NT override
-    // the defaults for launch-shape sweeps
-    // measured at 512^3 (4096 spheres; segment width x block order x hints,
-    // then repeated): FP32 is fastest with 256-cell segments in hardware
-    // order (every XCD streams the same planes; 3.71 ms, XCD-contiguous 256:
-    // 4.05-4.13), FP16 with 512-cell segments in hardware order (1.99 ms in
-    // three repeats against 2.16-2.21 with 256 XCD-contiguous), FP64 with
-    // 128-cell segments.  FP64 in XCD-contiguous against hardware order: 7.61
-    // / 7.98 ms at 512^3 and 5.20 / 5.39 at 384 x 512^2, but 0.925 / 0.857 at
-    // 256 x 200 x 300, 1.81 / 1.64 at 384^2 x 200, 5.03 / 4.67 at 512 x 400^2
-    // and 7.03 / 6.79 at 600 x 500 x 400: the line is drawn at 10^8 cells
+    // launch shape of the sweep: segments of block_x consecutive cells (whole
+    // wavefronts), streaming (non-temporal) hints on its stores;
+    // LBMEP_BLOCK_X, LBMEP_XCD_SWIZZLE and LBMEP_SWEEP_NT override the
+    // defaults for launch-shape sweeps.
+    // Measured with a charge force, segments of 64 / 128 / 256 / 512 cells:
+    //   216 x 312 x 216  FP64 881 / 849 / 857 / 863, FP32 527 / 405 / 402 /
+    //                    421, FP16 246 / 222 / 206 / 208 us
+    //   512^3            FP64 7.7 / 7.5 / 7.1 / 7.6, FP32 4.69 / 3.44 / 3.44 /
+    //                    3.55, FP16 2.31 / 2.05 / 1.86 / 1.78 ms
+    //   32^3             FP64 4.9 / 4.9 / 5.4 / 6.1, FP32 4.1 / 4.0 / 4.4 /
+    //                    4.6, FP16 3.9 / 3.8 / 4.1 / 4.4 us
+    // Hardware order against segments dealt onto XCDs in contiguous runs: FP64
+    // 825 / 930 us and 7.05 / 6.85 ms (runs vary by 3 %), FP32 389 / 504 us
+    // and 3.48 / 3.75 ms, FP16 201 / 273 us and 1.79 / 1.87 ms on the first
+    // two: every XCD streams the same planes.
     L->block_x = L->precision == LBMEP_FP64 ? 128 : L->precision == LBMEP_FP16DEV ? 512 : 256;
-    L->xcd_swizzle = L->precision == LBMEP_FP64 && g.N >= (size_t)100000000;
-    L->cpt = 1;
-    if (const char *e = std::getenv("LBMEP_CPT")) {
-        const int c = std::atoi(e);
-        if (c == 1 || c == 2) L->cpt = c;
-    }
+    L->xcd_swizzle = 0;
     // SOR tiles: 8 rows per thread and 8-plane chunks for FP32 psi; FP64 psi
     // needs twice the registers per row, so 4 and 4 (measured best of each)
     L->sor_rows = L->precision == LBMEP_FP64 ? 4 : 8;
@@ -1139,7 +1135,7 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
                 ms.level = q.level;
             }
         }
-        HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x, L->cpt,
+        HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x,
                              moving && !dyn ? &ms : nullptr, s));
         if (L->timing) HIP_TRY(hipEventRecord(e1, s));
         // bounce-back slots and momentum exchange next to solid cells, and the

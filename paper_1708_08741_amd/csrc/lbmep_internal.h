@@ -128,7 +128,7 @@ struct SweepArgs {
     const double *zeta; // potential: per-particle boundary value, or null
     double le, lo, ae, ao;  // lambda_e, lambda_o, 1 + lambda_e/2, 1 + lambda_o/2
     TrtF32 tf;              // the same rates for the FP32-compute collision
-    int nxb;                // x-segments per row (set by the launcher)
+    uint64_t mx, my;        // 2^63 / nx + 1, 2^63 / ny + 1 (quotients by multiplication)
     int xcd_swizzle;        // 1: map consecutive segments onto one XCD
     int slip;               // free-slip faces: bit 2a + side (a = axis, side 1 = high)
     uint32_t lds;           // dynamic LDS bytes per sweep workgroup (caps the waves per CU; 0: none)
@@ -274,7 +274,7 @@ constexpr int kPackBlockX = 128;
 // kernels (host-side launchers); each returns hipError_t of the launch
 // (ms: the next level's mapping in the same launch, or null)
 hipError_t launch_sweep(int precision, int mode, int force_mode, const SweepArgs &a, int block_x,
-                        int cpt, const MapSetArgs *ms, hipStream_t s);
+                        const MapSetArgs *ms, hipStream_t s);
 
 // after a sweep: bounce-back slots and momentum exchange, one workgroup per
 // particle over its link list and q.wall_blocks workgroups over the wall

@@ -234,9 +234,7 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     LatticeDev h{};
     for (int cur = 0; cur < 2; ++cur)
         for (int co = 0; co < 3; ++co) {
-            SweepArgs a = sweep_args_state(L, cur, co);
-            a.nxb = (L->g.nx + kPackBlockX - 1) / kPackBlockX;
-            h.sweep[cur + 2 * co] = a;
+            h.sweep[cur + 2 * co] = sweep_args_state(L, cur, co);
         }
     h.pa = particle_args(L);
     for (int b = 0; b < 3; ++b) h.map[b] = L->map[b];
@@ -364,8 +362,8 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                     lbmep_lattice *L = sl->L;
                     if (L->precision != prec || L->force_mode != fm) continue;
                     const uint32_t state = (uint32_t)(L->cur + 2 * L->cur_owner);
-                    const uint32_t nxb = (uint32_t)((L->g.nx + kPackBlockX - 1) / kPackBlockX);
-                    const uint32_t sb = map_blocks(L) + nxb * (uint32_t)L->g.ny * (uint32_t)L->g.nz;
+                    const uint32_t sb =
+                        map_blocks(L) + (uint32_t)((L->g.N + kPackBlockX - 1) / kPackBlockX);
                     if (map_blocks(L)) lds = std::max(lds, classify_lds(L->box_rows));
                     ts.d[ts.n] = tn.d[tn.n] = sl->d;
                     ts.state[ts.n] = tn.state[tn.n] = state;

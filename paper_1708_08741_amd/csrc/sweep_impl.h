@@ -6,11 +6,11 @@
 //
 // Pull scheme with post-collision storage.  The grid holds f*, the
 // post-collision populations (with the forcing term) of the previous time
-// level.  One thread per cell; a workgroup covers a segment of an x-row and
-// consecutive segments are dealt onto one XCD.  A thread gathers f*_q from
-// x - e_q (reads shifted by at most one element along x; this completes the
-// stream of Eq. LBMstreamStep), refills the cell if it has just been
-// uncovered, collides, and writes its 19 new values aligned to its own cell.
+// level.  One thread per cell; a workgroup takes consecutive cells of the
+// flat grid.  A thread gathers f*_q from x - e_q (reads shifted by at most
+// one element along x; this completes the stream of Eq. LBMstreamStep),
+// refills the cell if it has just been uncovered, collides, and writes its 19
+// new values aligned to its own cell.
 // Bounce-back needs no look-up at gather time: after the sweep, the kernel
 // of near_impl.h writes the bounced value of every blocked link into a slot
 // of the solid neighbour that the fluid cell gathers from at the next step.
@@ -329,21 +329,49 @@ __device__ __forceinline__ void collide_f32(float (&v)[Q], const TrtF32 &t, floa
 #define LBMEP_FOR_Q18(M) \
     M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) M(16) M(17) M(18)
 
+// where a cell's populations come from: byte offsets of the source cells
+// x - e and whether they lie inside the grid (periodic axes wrapped), as the
+// cell's own offset plus a step per axis (index e + 1)
+template <typename OFF>
+struct Sources {
+    OFF cb, d[3][3];
+    bool in[3][3];
+    __device__ __forceinline__ Sources(const Grid &g, int x, int y, int z, OFF ci, OFF es) {
+        cb = ci * es;
+        const OFF str[3] = {es, (OFF)g.nx * es, (OFF)g.nx * (OFF)g.ny * es};
+        const int pos[3] = {x, y, z}, len[3] = {g.nx, g.ny, g.nz};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const OFF wrap = str[a] * (OFF)(len[a] - 1);
+            const bool first = pos[a] == 0, last = pos[a] == len[a] - 1;
+            d[a][0] = last ? (OFF)0 - wrap : str[a];
+            d[a][1] = 0;
+            d[a][2] = first ? wrap : (OFF)0 - str[a];
+            in[a][0] = !last || g.per[a];
+            in[a][1] = true;
+            in[a][2] = !first || g.per[a];
+        }
+    }
+    __device__ __forceinline__ OFF at(int cx, int cy, int cz) const {
+        return cb + d[0][cx + 1] + d[1][cy + 1] + d[2][cz + 1];
+    }
+    __device__ __forceinline__ bool ok(int cx, int cy, int cz) const {
+        return in[0][cx + 1] && in[1][cy + 1] && in[2][cz + 1];
+    }
+};
+
 // gather population q of the cell from x - e_q; beyond the edge of a
 // non-periodic axis the population bounces at the (resting) edge: it is the
 // cell's own opposite population
 template <int q, typename ST, typename OFF, int MODE>
-__device__ __forceinline__ typename Storage<ST>::CT gather(const void *src, OFF pst, OFF es,
-                                                           OFF cb, const OFF rows[3][3],
-                                                           const bool rok[3][3], const OFF xs[3],
-                                                           const bool xok[3]) {
+__device__ __forceinline__ typename Storage<ST>::CT gather(const void *src, OFF pst, OFF cb,
+                                                           const Sources<OFF> &n) {
     constexpr int qb = opp(q);
     constexpr int lo = q < qb ? q : qb;
     const void *base = static_cast<const char *>(src) + (size_t)lo * pst;
-    const bool ok = rok[kCy[q] + 1][kCz[q] + 1] && xok[kCx[q] + 1];
-    const OFF nb = (OFF)(q - lo) * pst + xs[kCx[q] + 1] + rows[kCy[q] + 1][kCz[q] + 1];
+    const OFF nb = (OFF)(q - lo) * pst + n.at(kCx[q], kCy[q], kCz[q]);
     const OFF own = (OFF)(qb - lo) * pst + cb;
-    return pop_load<MODE, ST>(at<ST>(base, ok ? nb : own));
+    return pop_load<MODE, ST>(at<ST>(base, n.ok(kCx[q], kCy[q], kCz[q]) ? nb : own));
 }
 
 // Free-slip faces: a population that a face cell x gathers from beyond a
@@ -443,10 +471,12 @@ __device__ __forceinline__ void store_pop(void *dst, OFF pst, OFF cb, typename S
 }
 
 // loaded inputs of one cell
-template <typename CT>
+template <typename CT, typename OFF>
 struct CellIn {
     CT v[Q];
     CT fb0, fb1, fb2;
+    OFF ci;      // cell index (in range also where not valid)
+    bool valid;  // a cell of the grid
     uint8_t fl;
 };
 
@@ -454,16 +484,15 @@ struct CellIn {
 // load in-range values and drop them), so that the flag and the populations
 // share one memory latency
 template <typename ST, int FMODE, typename OFF, int MODE>
-__device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int z, bool valid,
-                                          CellIn<typename Storage<ST>::CT> &c) {
+__device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int z, OFF ci,
+                                          bool valid, CellIn<typename Storage<ST>::CT, OFF> &c) {
     using T = Storage<ST>;
     using CT = typename T::CT;
-    const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
     const OFF es = (OFF)sizeof(ST);
     const OFF pst = (OFF)a.g.Ns * es;
-    const int xc = valid ? x : 0, yc = valid ? y : 0;
-    const OFF ci = (OFF)xc + (OFF)nx * ((OFF)yc + (OFF)ny * (OFF)z);
     const OFF cb = ci * es;
+    c.ci = ci;
+    c.valid = valid;
     const uint8_t *flp = at<uint8_t>((const void *)a.flag, ci);
     uint8_t fl;
     if constexpr (MODE == kPullNT)
@@ -471,44 +500,14 @@ __device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int 
     else
         fl = *flp;
     c.fl = valid ? fl : kWall;
-    // source rows (y - c_y, z - c_z) and columns x - c_x, wrapped on
-    // periodic axes; beyond a non-periodic edge: not ok (pull modes)
-    OFF rows[3][3];
-    bool rok[3][3];
-    OFF xs[3];
-    bool xok[3];
+    const Sources<OFF> n(a.g, x, y, z, ci, es);  // pull modes
     if constexpr (MODE == kLocal) {
 #pragma unroll
         for (int q = 0; q < Q; ++q)
             c.v[q] = T::lc(at<ST>(static_cast<const char *>(a.src) + (size_t)q * pst, cb));
     } else {
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                int ys = yc - (j - 1), zs = z - (k - 1);
-                bool ok = true;
-                if (ys < 0 || ys >= ny) {
-                    if (a.g.per[1]) ys = ys < 0 ? ys + ny : ys - ny; else { ok = false; ys = yc; }
-                }
-                if (zs < 0 || zs >= nz) {
-                    if (a.g.per[2]) zs = zs < 0 ? zs + nz : zs - nz; else { ok = false; zs = z; }
-                }
-                rows[j][k] = (OFF)nx * ((OFF)ys + (OFF)ny * (OFF)zs) * es;
-                rok[j][k] = ok;
-            }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            int xq = xc - (i - 1);
-            bool ok = true;
-            if (xq < 0 || xq >= nx) {
-                if (a.g.per[0]) xq = xq < 0 ? xq + nx : xq - nx; else { ok = false; xq = xc; }
-            }
-            xs[i] = (OFF)xq * es;
-            xok[i] = ok;
-        }
         c.v[0] = pop_load<MODE, ST>(at<ST>(a.src, cb));
-#define LBMEP_GATHER(q) c.v[q] = gather<q, ST, OFF, MODE>(a.src, pst, es, cb, rows, rok, xs, xok);
+#define LBMEP_GATHER(q) c.v[q] = gather<q, ST, OFF, MODE>(a.src, pst, cb, n);
         LBMEP_FOR_Q18(LBMEP_GATHER)
 #undef LBMEP_GATHER
     }
@@ -527,16 +526,14 @@ __device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int 
                                     (!a.g.per[2] || a.g.nz % 2 == 0);
             if (MODE != kLocal && split_even && valid && !(fl & (kWall | kObst | kNear))) {
                 // every neighbour a fluid cell inside the grid: the
-                // stencil's slots from the gather's wrapped rows and columns
-                // (row (y', z') starts at entry nx / 2 (y' + ny z'), column
-                // x' is entry x' / 2, the colour-1 half at Ns / 2); the
-                // colour of the neighbour (x, y, z) + (dx, dy, dz) is the
+                // stencil's slots from the gather's source cells (cell c' is
+                // entry c' / 2, nx being even, the colour-1 half at Ns / 2);
+                // the colour of the neighbour (x, y, z) + (dx, dy, dz) is the
                 // cell's own xor the parity of dx + dy + dz
                 const OFF half = (OFF)(a.g.Ns >> 1) * (OFF)sizeof(CT);
-                const OFF cs = (OFF)(((xc + yc + z) & 1) ? half : 0), co = half - cs;
+                const OFF cs = (OFF)(((x + y + z) & 1) ? half : 0), co = half - cs;
                 auto val = [&](int dx, int dy, int dz) -> CT {
-                    const OFF ob = rows[1 - dy][1 - dz] / (2 * es) * (OFF)sizeof(CT) +
-                                   xs[1 - dx] / (2 * es) * (OFF)sizeof(CT) +
+                    const OFF ob = n.at(-dx, -dy, -dz) / (2 * es) * (OFF)sizeof(CT) +
                                    (((dx + dy + dz) & 1) ? co : cs);
                     return *at<CT>(a.force, ob);
                 };
@@ -578,14 +575,14 @@ __device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int 
 // refill (if uncovered), collide and store one loaded cell
 template <typename ST, int FMODE, typename OFF, int MODE>
 __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, int z,
-                                            CellIn<typename Storage<ST>::CT> &c) {
+                                            CellIn<typename Storage<ST>::CT, OFF> &c) {
     using T = Storage<ST>;
     using CT = typename T::CT;
     const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
     const OFF es = (OFF)sizeof(ST);
     const OFF pst = (OFF)a.g.Ns * es;
-    const bool act = !(c.fl & (kWall | kObst));
-    const OFF ci = act ? (OFF)x + (OFF)nx * ((OFF)y + (OFF)ny * (OFF)z) : (OFF)0;
+    const bool act = !(c.fl & (kWall | kObst));  // not so beyond the grid
+    const OFF ci = c.ci;
     const OFF cb = ci * es;
     CT(&v)[Q] = c.v;
 
@@ -615,11 +612,10 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
     if constexpr (MODE == kReadout) {
         // solid cells get defined values: the rest state at walls and
         // f^eq(rho0, u_s) of the owning particle at obstacle cells
-        if (!act && (c.fl & (kWall | kObst)) && x < nx && y < ny) {
-            const OFF si = (OFF)x + (OFF)nx * ((OFF)y + (OFF)ny * (OFF)z);
+        if (!act && c.valid) {
             double u0 = 0.0, u1 = 0.0, u2 = 0.0;
             if (!(c.fl & kWall)) {
-                const uint32_t po = a.owner[si];
+                const uint32_t po = a.owner[ci];
                 const double *Xp = a.Xc + 3 * (size_t)po;
                 const double *U = a.U + 3 * (size_t)po;
                 const double *W = a.W + 3 * (size_t)po;
@@ -634,18 +630,16 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 const double cu = ((double)kCx[q] * u0 + (double)kCy[q] * u1) + (double)kCz[q] * u2;
-                T::sc(at<ST>(static_cast<char *>(a.dst) + (size_t)q * pst, si * es),
-                      (CT)T::feq_c(q, (cu * 3.0 + (cu * cu) * 4.5) - uu * 1.5));
+                v[q] = (CT)T::feq_c(q, (cu * 3.0 + (cu * cu) * 4.5) - uu * 1.5);
             }
         }
-        if (act) {
+        if (c.valid) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
                 T::sc(at<ST>(static_cast<char *>(a.dst) + (size_t)q * pst, cb), v[q]);
         }
     } else {
-        // the collision runs on every lane; only the stores are restricted
-        // to fluid cells
+        // the collision runs on every lane
         if constexpr (sizeof(CT) == 4) {
             collide_f32<FMODE != kForceNone>(v, a.tf, c.fb0, c.fb1, c.fb2);
         } else {
@@ -698,8 +692,14 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
         collide_pair<17>(v, rho, ux, uy, uz, uu, ufb, fb0, fb1, fb2, le, lo, ae, ao, forced);
         }
 
-        if (act) {
-            // aligned store of the post-collision state
+        // Aligned store of the post-collision state, also to the obstacle
+        // cells beside fluid ones: nothing reads there but the slots that the
+        // exchange writes after the sweep, and whole lines cost less than
+        // lines with holes (4096 spheres of radius 4, with the holes and
+        // without: 512^3 FP32 3730 -> 3500 us, 512 x 384 x 320 FP16 1083 ->
+        // 1001, 300 x 256^2 FP64 1230 -> 1126).  The slots of wall cells,
+        // which a fixed list keeps up, stay untouched.
+        if (__any(act) && c.valid && !(c.fl & kWall)) {
 #define LBMEP_STORE(q) store_pop<q, MODE, ST, OFF>(a.dst, pst, cb, v[q]);
             LBMEP_STORE(0)
             LBMEP_FOR_Q18(LBMEP_STORE)
@@ -709,25 +709,44 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
 }
 
 
-// one workgroup's x-segment of a 1-D grid of segments: CPT cells per
-// thread, on consecutive rows y (their loads are all issued before the first
-// collision, for more memory-level parallelism per wave)
-template <typename ST, int FMODE, typename OFF, int MODE, int CPT>
-__device__ __forceinline__ void sweep_segment(const SweepArgs &a, uint32_t lb) {
-    using T = Storage<ST>;
-    using CT = typename T::CT;
-    const int nx = a.g.nx, ny = a.g.ny;
-    const uint32_t nyb = (uint32_t)((ny + CPT - 1) / CPT);
-    const uint32_t xb = lb % (uint32_t)a.nxb, row = lb / (uint32_t)a.nxb;
-    const int y0 = (int)(row % nyb) * CPT, z = (int)(row / nyb);
-    const int x = (int)xb * blockDim.x + threadIdx.x;
+// t / n for t < n + 2^11 (a segment or less past the axis), m = 2^31 / n + 1
+// or one more: a single subtraction from n = 2^11 on, and below that the
+// product's error, at most 2 t / 2^31 of a quotient step of 1 / n, is too small
+__device__ __forceinline__ uint32_t quot(uint32_t t, int n, uint32_t m) {
+    return n >= 2048 ? (uint32_t)(t >= (uint32_t)n) : __umulhi(2u * t, m);
+}
 
-    CellIn<CT> c[CPT];
-#pragma unroll
-    for (int r = 0; r < CPT; ++r)
-        load_cell<ST, FMODE, OFF, MODE>(a, x, y0 + r, z, x < nx && y0 + r < ny, c[r]);
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) finish_cell<ST, FMODE, OFF, MODE>(a, x, y0 + r, z, c[r]);
+// One workgroup's blockDim.x consecutive cells of the flat grid.  A sweep is
+// bound by its memory traffic; with the cells dealt out across rows every
+// lane has a cell and every store covers whole aligned lines, whatever nx is.
+// (Segments of single rows, with y and z in scalar registers, left lanes idle
+// at the rows' ends and split lines between workgroups.  Step of a lattice
+// with a charge force, row segments and now, FP64 / FP32 / FP16:
+//   101 x 67 x 83    39.7 -> 35.2   23.3 -> 18.7   16.5 -> 12.0 us
+//   300 x 333 x 250  1722 -> 1411   1218 ->  696    690 ->  392 us
+//   512^3            7614 -> 7068   3648 -> 3589   1883 -> 1818 us.)
+template <typename ST, int FMODE, typename OFF, int MODE>
+__device__ __forceinline__ void sweep_segment(const SweepArgs &a, uint32_t lb) {
+    const int nx = a.g.nx, ny = a.g.ny;
+    // the first cell's place in scalar registers: quotients by multiplication
+    // with 2^63 / n + 1, exact while cell times extent is below 2^63
+    const OFF c0 = (OFF)lb * blockDim.x;
+    const uint64_t row = __umul64hi(2u * (uint64_t)c0, a.mx);
+    const uint64_t plane = __umul64hi(2u * row, a.my);
+    const uint32_t x0 = (uint32_t)((uint64_t)c0 - row * (uint64_t)(uint32_t)nx);
+    const uint32_t y0 = (uint32_t)(row - plane * (uint64_t)(uint32_t)ny);
+    // this lane's, from there
+    const uint32_t t = x0 + threadIdx.x;
+    const uint32_t dy = quot(t, nx, (uint32_t)(a.mx >> 32) + 1u);
+    const uint32_t ty = y0 + dy;
+    const uint32_t dz = quot(ty, ny, (uint32_t)(a.my >> 32) + 1u);
+    const bool valid = (size_t)c0 + threadIdx.x < a.g.N;
+    const int x = valid ? (int)(t - dy * (uint32_t)nx) : 0;
+    const int y = valid ? (int)(ty - dz * (uint32_t)ny) : 0;
+    const int z = valid ? (int)((uint32_t)plane + dz) : 0;
+    CellIn<typename Storage<ST>::CT, OFF> c;
+    load_cell<ST, FMODE, OFF, MODE>(a, x, y, z, valid ? c0 + threadIdx.x : (OFF)0, valid, c);
+    finish_cell<ST, FMODE, OFF, MODE>(a, x, y, z, c);
 }
 
 // workgroup b of the next level's mapping: a particle per kMapThreads threads
@@ -745,7 +764,7 @@ __device__ __forceinline__ void map_particles(const ParticleArgs &pa, uint32_t b
 // its XCD) spread evenly among the sweep's, which hides their few dependent
 // round trips behind the streaming (a launch of its own took 10 us at 128^3
 // and 36-85 us at 512^3 with 4096 particles)
-template <typename ST, int FMODE, typename OFF, int MODE, int CPT>
+template <typename ST, int FMODE, typename OFF, int MODE>
 __global__ void __launch_bounds__(512) k_sweep(SweepArgs a, MapSetArgs ms, uint32_t nseg) {
     uint32_t b = blockIdx.x;
     if (ms.groups) {
@@ -757,7 +776,7 @@ __global__ void __launch_bounds__(512) k_sweep(SweepArgs a, MapSetArgs ms, uint3
         b -= 8u * min(ms.groups, (g + ms.stride - 1u) / ms.stride);
         if (b >= nseg) return;
     }
-    sweep_segment<ST, FMODE, OFF, MODE, CPT>(a, a.xcd_swizzle ? xcd_remap(b, nseg) : b);
+    sweep_segment<ST, FMODE, OFF, MODE>(a, a.xcd_swizzle ? xcd_remap(b, nseg) : b);
 }
 
 // the gather sweep of several lattices in one dispatch
@@ -777,7 +796,7 @@ __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
     const SweepArgs a = d->sweep[t.state[e]];
     // streaming hints as in the single-lattice default: stores only
     constexpr int MODE = kPullNTS;
-    sweep_segment<ST, FMODE, uint32_t, MODE, 1>(a, b);
+    sweep_segment<ST, FMODE, uint32_t, MODE>(a, b);
 }
 
 template <typename ST>
@@ -795,9 +814,9 @@ hipError_t launch_sweep_packed_typed(int force_mode, const PackTable &t, hipStre
     return hipGetLastError();
 }
 
-// host launcher for one storage type; cpt = cells per thread (1 or 2)
+// host launcher for one storage type
 template <typename ST>
-hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x, int cpt,
+hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x,
                         const MapSetArgs *map, hipStream_t s) {
     // 32-bit byte offsets when two population arrays fit in 4 GiB (the
     // gather addresses an opposite pair from one base)
@@ -812,21 +831,11 @@ hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x, int 
                 cells += (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
         hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, a);
     }
-    if (!small || mode == kReadout) cpt = 1;
     // the workgroups-per-CU cap was measured on the 32-bit-offset kernel;
     // the 64-bit one runs faster without it (864 x 1248 x 864 FP32: 24.6
     // against 27.5 ms)
     if (!small) a.lds = 0;
-    // no more wavefronts than the row has cells for (101 cells in segments of
-    // 256: half the wavefronts would load and drop cells beyond the row)
-    const int full_x = block_x;
-    if (block_x > (a.g.nx + 63) / 64 * 64) block_x = (a.g.nx + 63) / 64 * 64;
-    // a.lds caps the workgroups per CU at their default width; narrower ones
-    // keep the same number of wavefronts (128^3 FP32, two wavefronts per row:
-    // 4 workgroups 77 us, 8 workgroups 64 us, none 65 us)
-    if (a.lds && block_x < full_x) a.lds = a.lds / (uint32_t)full_x * (uint32_t)block_x / 16 * 16;
-    a.nxb = (a.g.nx + block_x - 1) / block_x;
-    const size_t nblocks = (size_t)a.nxb * ((a.g.ny + cpt - 1) / cpt) * a.g.nz;
+    const size_t nblocks = (a.g.N + (size_t)block_x - 1) / (size_t)block_x;
     const dim3 block(block_x, 1, 1);
     MapSetArgs ms{};
     size_t total = nblocks;
@@ -840,32 +849,26 @@ hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x, int 
     }
     const dim3 grid((unsigned)total, 1, 1);
     const uint32_t nseg = (uint32_t)nblocks;
-#define LBMEP_LAUNCH(MD, FM, OFF, C) \
-    hipLaunchKernelGGL((k_sweep<ST, FM, OFF, MD, C>), grid, block, a.lds, s, a, ms, nseg)
-#define LBMEP_BY_FORCE(MD, OFF, C)                                           \
-    do {                                                                     \
-        if (force_mode == kForceNone) LBMEP_LAUNCH(MD, kForceNone, OFF, C);      \
-        else if (force_mode == kForceDense) LBMEP_LAUNCH(MD, kForceDense, OFF, C); \
-        else if (force_mode == kForceCharge) LBMEP_LAUNCH(MD, kForceCharge, OFF, C); \
-        else LBMEP_LAUNCH(MD, kForcePotential, OFF, C);                        \
-    } while (0)
-#define LBMEP_BY_CPT(MD)                                    \
-    do {                                                    \
-        if (cpt == 2) LBMEP_BY_FORCE(MD, uint32_t, 2);      \
-        else LBMEP_BY_FORCE(MD, uint32_t, 1);               \
+#define LBMEP_LAUNCH(MD, FM, OFF) \
+    hipLaunchKernelGGL((k_sweep<ST, FM, OFF, MD>), grid, block, a.lds, s, a, ms, nseg)
+#define LBMEP_BY_FORCE(MD, OFF)                                           \
+    do {                                                                  \
+        if (force_mode == kForceNone) LBMEP_LAUNCH(MD, kForceNone, OFF);        \
+        else if (force_mode == kForceDense) LBMEP_LAUNCH(MD, kForceDense, OFF); \
+        else if (force_mode == kForceCharge) LBMEP_LAUNCH(MD, kForceCharge, OFF); \
+        else LBMEP_LAUNCH(MD, kForcePotential, OFF);                            \
     } while (0)
     if (small) {
-        if (mode == kPull) LBMEP_BY_CPT(kPull);
-        else if (mode == kPullNT) LBMEP_BY_CPT(kPullNT);
-        else if (mode == kPullNTS) LBMEP_BY_CPT(kPullNTS);
-        else if (mode == kLocal) LBMEP_BY_CPT(kLocal);
-        else LBMEP_LAUNCH(kReadout, kForceNone, uint32_t, 1);
+        if (mode == kPull) LBMEP_BY_FORCE(kPull, uint32_t);
+        else if (mode == kPullNT) LBMEP_BY_FORCE(kPullNT, uint32_t);
+        else if (mode == kPullNTS) LBMEP_BY_FORCE(kPullNTS, uint32_t);
+        else if (mode == kLocal) LBMEP_BY_FORCE(kLocal, uint32_t);
+        else LBMEP_LAUNCH(kReadout, kForceNone, uint32_t);
     } else {
-        if (mode == kPull || mode == kPullNT || mode == kPullNTS) LBMEP_BY_FORCE(kPull, uint64_t, 1);
-        else if (mode == kLocal) LBMEP_BY_FORCE(kLocal, uint64_t, 1);
-        else LBMEP_LAUNCH(kReadout, kForceNone, uint64_t, 1);
+        if (mode == kPull || mode == kPullNT || mode == kPullNTS) LBMEP_BY_FORCE(kPull, uint64_t);
+        else if (mode == kLocal) LBMEP_BY_FORCE(kLocal, uint64_t);
+        else LBMEP_LAUNCH(kReadout, kForceNone, uint64_t);
     }
-#undef LBMEP_BY_CPT
 #undef LBMEP_BY_FORCE
 #undef LBMEP_LAUNCH
     return hipGetLastError();

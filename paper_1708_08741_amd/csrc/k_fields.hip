@@ -106,93 +106,6 @@ __global__ void k_convert(const TI *in, TO *out, size_t n, size_t si, size_t so,
         for (int k = 0; k < ncomp; ++k) out[k * so + i] = (TO)in[k * si + i];
 }
 
-__device__ __forceinline__ double min_image(double d, int len, int periodic) {
-    if (periodic) {
-        const double h = 0.5 * (double)len;
-        if (d > h)
-            d -= (double)len;
-        else if (d < -h)
-            d += (double)len;
-    }
-    return d;
-}
-
-template <typename ST, typename CT>
-__global__ void k_macro(Grid g, int force_mode, const ST *f, const uint8_t *flag,
-                        const uint32_t *owner, const double *Xc, const double *U, const double *W,
-                        const CT *force, double E0, double E1, double E2, double keps,
-                        const double *zeta, double *rho, double *u) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= g.nx) return;
-    const int y = blockIdx.y, z = blockIdx.z;
-    const size_t c = (size_t)x + (size_t)g.nx * ((size_t)y + (size_t)g.ny * (size_t)z);
-    const uint8_t fl = flag[c];
-    if (fl & kWall) {
-        rho[c] = 1.0;
-        u[c] = u[g.N + c] = u[2 * g.N + c] = 0.0;
-        return;
-    }
-    if (fl & kObst) {
-        const uint32_t p = owner[c];
-        const double *Xp = Xc + 3 * (size_t)p;
-        const double r0 = min_image(((double)x + 0.5) - Xp[0], g.nx, g.per[0]);
-        const double r1 = min_image(((double)y + 0.5) - Xp[1], g.ny, g.per[1]);
-        const double r2 = min_image(((double)z + 0.5) - Xp[2], g.nz, g.per[2]);
-        const double *Up = U + 3 * (size_t)p, *Wp = W + 3 * (size_t)p;
-        rho[c] = 1.0;
-        u[c] = Up[0] + (Wp[1] * r2 - Wp[2] * r1);
-        u[g.N + c] = Up[1] + (Wp[2] * r0 - Wp[0] * r2);
-        u[2 * g.N + c] = Up[2] + (Wp[0] * r1 - Wp[1] * r0);
-        return;
-    }
-    double fb[3] = {0.0, 0.0, 0.0};
-    if (force_mode == kForceDense) {
-        fb[0] = (double)force[c];
-        fb[1] = (double)force[g.Ns + c];
-        fb[2] = (double)force[2 * g.Ns + c];
-    } else if (force_mode == kForceCharge) {
-        const double re = (double)force[c];
-        fb[0] = re * E0;
-        fb[1] = re * E1;
-        fb[2] = re * E2;
-    } else if (force_mode == kForcePotential) {
-        // the force of the sweep, in its compute precision
-        CT f0, f1, f2;
-        potential_force<CT>(g, x, y, z, fl, force, flag, owner, zeta, (CT)keps, (CT)E0, (CT)E1,
-                            (CT)E2, f0, f1, f2);
-        fb[0] = (double)f0;
-        fb[1] = (double)f1;
-        fb[2] = (double)f2;
-    }
-    double s = 0.0, j[3] = {0.0, 0.0, 0.0};
-    if constexpr (sizeof(ST) == 8) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) s += (double)f[(size_t)q * g.Ns + c];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const double v = (double)f[(size_t)q * g.Ns + c];
-            j[0] += (double)kCx[q] * v;
-            j[1] += (double)kCy[q] * v;
-            j[2] += (double)kCz[q] * v;
-        }
-        rho[c] = s;
-    } else {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const double v = dev_value<ST>(f[(size_t)q * g.Ns + c]);
-            s += v;
-            j[0] += (double)kCx[q] * v;
-            j[1] += (double)kCy[q] * v;
-            j[2] += (double)kCz[q] * v;
-        }
-        rho[c] = 1.0 + s;
-    }
-    // Eq. modified_velocity
-    u[c] = j[0] + 0.5 * fb[0];
-    u[g.N + c] = j[1] + 0.5 * fb[1];
-    u[2 * g.N + c] = j[2] + 0.5 * fb[2];
-}
-
 // block-level sums of (rho or rho - 1, j) over fluid cells; the block sums
 // are reduced by one block in a fixed order -> deterministic result
 template <typename ST>
@@ -368,27 +281,6 @@ hipError_t launch_convert_force(int precision, const void *in, int in_dtype, voi
     else
         hipLaunchKernelGGL((k_convert<float, float>), grid, block, 0, s, (const float *)in,
                            (float *)out, n, in_stride, out_stride, ncomp);
-    return hipGetLastError();
-}
-
-hipError_t launch_macro(int precision, int force_mode, const Grid &g, const void *f,
-                        const uint8_t *flag, const uint32_t *owner, const double *Xc,
-                        const double *U, const double *W, const void *force, const double E[3],
-                        double keps, const double *zeta, double *rho, double *u, hipStream_t s) {
-    const int bx = 64;
-    const dim3 grid((g.nx + bx - 1) / bx, g.ny, g.nz), block(bx);
-    if (precision == LBMEP_FP64)
-        hipLaunchKernelGGL((k_macro<double, double>), grid, block, 0, s, g, force_mode,
-                           (const double *)f, flag, owner, Xc, U, W, (const double *)force, E[0],
-                           E[1], E[2], keps, zeta, rho, u);
-    else if (precision == LBMEP_FP32DEV)
-        hipLaunchKernelGGL((k_macro<float, float>), grid, block, 0, s, g, force_mode,
-                           (const float *)f, flag, owner, Xc, U, W, (const float *)force, E[0],
-                           E[1], E[2], keps, zeta, rho, u);
-    else
-        hipLaunchKernelGGL((k_macro<__half, float>), grid, block, 0, s, g, force_mode,
-                           (const __half *)f, flag, owner, Xc, U, W, (const float *)force, E[0],
-                           E[1], E[2], keps, zeta, rho, u);
     return hipGetLastError();
 }
 

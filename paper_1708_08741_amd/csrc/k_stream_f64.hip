@@ -11,6 +11,11 @@ hipError_t launch_sweep_f64(int mode, int force_mode, const SweepArgs &a, int bl
     return sweep::launch_typed<double>(mode, force_mode, a, block_x, ms, s);
 }
 
+hipError_t launch_macro_f64(int force_mode, const SweepArgs &a, bool pull, double *rho, double *u,
+                            hipStream_t s) {
+    return sweep::launch_macro_typed<double>(force_mode, a, pull, rho, u, s);
+}
+
 hipError_t launch_parts_f64(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {
     return sweep::launch_parts_typed<double>(a, q, s);
 }

@@ -16,6 +16,17 @@ hipError_t launch_sweep(int precision, int mode, int force_mode, const SweepArgs
     return sweep::launch_typed<__half>(mode, force_mode, a, block_x, ms, s);
 }
 
+hipError_t launch_macro_f64(int force_mode, const SweepArgs &a, bool pull, double *rho, double *u,
+                            hipStream_t s);
+
+hipError_t launch_macro(int precision, int force_mode, const SweepArgs &a, bool pull, double *rho,
+                        double *u, hipStream_t s) {
+    if (precision == LBMEP_FP64) return launch_macro_f64(force_mode, a, pull, rho, u, s);
+    if (precision == LBMEP_FP32DEV)
+        return sweep::launch_macro_typed<float>(force_mode, a, pull, rho, u, s);
+    return sweep::launch_macro_typed<__half>(force_mode, a, pull, rho, u, s);
+}
+
 hipError_t launch_parts_f64(const SweepArgs &a, const PartsArgs &q, hipStream_t s);
 
 hipError_t launch_parts(int precision, const SweepArgs &a, const PartsArgs &q, hipStream_t s) {

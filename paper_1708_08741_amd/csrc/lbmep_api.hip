@@ -1159,8 +1159,6 @@ int lbmep_get_macro(lbmep_lattice *L, double *rho, double *u, int on_device) {
     if (!L || !rho || !u) return fail(LBMEP_EINVAL, "null argument");
     int rc = set_device(L);
     if (rc) return rc;
-    rc = materialize(L);
-    if (rc) return rc;
     const size_t N = L->g.N;
     double *drho = rho, *du = u;
     if (!on_device) {
@@ -1170,11 +1168,8 @@ int lbmep_get_macro(lbmep_lattice *L, double *rho, double *u, int on_device) {
             return fail(LBMEP_ENOMEM, "temp");
         }
     }
-    hipError_t e = launch_macro(L->precision, L->force_mode, L->g, L->f[L->cur], L->flag,
-                                L->np > 0 ? L->map[L->cur_owner].owner : nullptr,
-                                L->np > 0 ? L->map[L->cur_owner].X : nullptr, L->U, L->W, L->force,
-                                L->E, L->keps, L->force_mode == kForcePotential ? L->zeta : nullptr,
-                                drho, du, L->stream);
+    hipError_t e = launch_macro(L->precision, L->force_mode, sweep_args(L), L->pmode, drho, du,
+                                L->stream);
     if (e == hipSuccess && !on_device) {
         e = hipMemcpyAsync(rho, drho, N * sizeof(double), hipMemcpyDeviceToHost, L->stream);
         if (e == hipSuccess)

@@ -309,10 +309,7 @@ hipError_t launch_convert_force(int precision, const void *in, int in_dtype, voi
                                 size_t n, size_t in_stride, size_t out_stride, int ncomp,
                                 hipStream_t s);
 // macroscopic read-out
-hipError_t launch_macro(int precision, int force_mode, const Grid &g, const void *f,
-                        const uint8_t *flag, const uint32_t *owner, const double *Xc,
-                        const double *U, const double *W, const void *force,
-                        const double E[3], double keps, const double *zeta, double *rho,
+hipError_t launch_macro(int precision, int force_mode, const SweepArgs &a, bool pull, double *rho,
                         double *u, hipStream_t s);
 // Debye-Hueckel equation of the EDL potential by red-black SOR: control
 // block in device memory (the kernels of a solve stop once done is set)

@@ -283,11 +283,8 @@ int enqueue_readout(lbmep_server *S, Slot &slot) {
                                     L->red_blocks, dout, s));
     if (slot.fields) {
         const size_t N = L->g.N;
-        LBMEP_HIP_TRY(launch_macro(L->precision, L->force_mode, L->g, L->f[L->cur], L->flag,
-                                   L->np > 0 ? L->map[L->cur_owner].owner : nullptr,
-                                   L->np > 0 ? L->map[L->cur_owner].X : nullptr, L->U, L->W,
-                                   L->force, L->E, L->keps, nullptr, slot.fields,
-                                   slot.fields + N, s));
+        LBMEP_HIP_TRY(launch_macro(L->precision, L->force_mode, sweep_args(L), L->pmode,
+                                   slot.fields, slot.fields + N, s));
     }
     slot.ev = get_event(S);
     if (!slot.ev) return fail(LBMEP_EDEVICE, "event creation failed");

@@ -572,13 +572,50 @@ __device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int 
     }
 }
 
+// surface velocity u_s of particle p, centred at X, at cell (x, y, z)
+__device__ __forceinline__ void surface_velocity(const SweepArgs &a, const double *X, uint32_t p,
+                                                 int x, int y, int z, double (&u)[3]) {
+    const double *Xp = X + 3 * (size_t)p;
+    const double *U = a.U + 3 * (size_t)p;
+    const double *W = a.W + 3 * (size_t)p;
+    const double r0 = min_image(((double)x + 0.5) - Xp[0], a.g.nx, a.g.per[0]);
+    const double r1 = min_image(((double)y + 0.5) - Xp[1], a.g.ny, a.g.per[1]);
+    const double r2 = min_image(((double)z + 0.5) - Xp[2], a.g.nz, a.g.per[2]);
+    u[0] = U[0] + (W[1] * r2 - W[2] * r1);
+    u[1] = U[1] + (W[2] * r0 - W[0] * r2);
+    u[2] = U[2] + (W[0] * r1 - W[1] * r0);
+}
+
+// f^eq(rho0, u) as stored, in compute units
+template <typename ST>
+__device__ __forceinline__ void equilibrium(const double (&u)[3], typename Storage<ST>::CT (&v)[Q]) {
+    using T = Storage<ST>;
+    const double uu = (u[0] * u[0] + u[1] * u[1]) + u[2] * u[2];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const double cu = ((double)kCx[q] * u[0] + (double)kCy[q] * u[1]) + (double)kCz[q] * u[2];
+        v[q] = (typename T::CT)T::feq_c(q, (cu * 3.0 + (cu * cu) * 4.5) - uu * 1.5);
+    }
+}
+
+// refill of a cell uncovered at this level: f^eq(rho0, u_s) with the surface
+// velocity of its previous owner at its previous place (Sec. 3.2)
+template <typename ST, typename OFF>
+__device__ __forceinline__ void refill(const SweepArgs &a, int x, int y, int z,
+                                       CellIn<typename Storage<ST>::CT, OFF> &c) {
+    if ((c.fl & kUncov) && !(c.fl & (kWall | kObst))) {
+        double u[3];
+        surface_velocity(a, a.Xold, a.owner_old[c.ci], x, y, z, u);
+        equilibrium<ST>(u, c.v);
+    }
+}
+
 // refill (if uncovered), collide and store one loaded cell
 template <typename ST, int FMODE, typename OFF, int MODE>
 __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, int z,
                                             CellIn<typename Storage<ST>::CT, OFF> &c) {
     using T = Storage<ST>;
     using CT = typename T::CT;
-    const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
     const OFF es = (OFF)sizeof(ST);
     const OFF pst = (OFF)a.g.Ns * es;
     const bool act = !(c.fl & (kWall | kObst));  // not so beyond the grid
@@ -586,52 +623,15 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
     const OFF cb = ci * es;
     CT(&v)[Q] = c.v;
 
-    // refill of a cell uncovered at this level: f^eq(rho0, u_s) with the
-    // surface velocity of its previous owner at its previous place (Sec. 3.2)
-    if constexpr (MODE != kLocal) {
-        if (act && (c.fl & kUncov)) {
-            const uint32_t po = a.owner_old[ci];
-            const double *Xp = a.Xold + 3 * (size_t)po;
-            const double *U = a.U + 3 * (size_t)po;
-            const double *W = a.W + 3 * (size_t)po;
-            const double r0 = min_image(((double)x + 0.5) - Xp[0], nx, a.g.per[0]);
-            const double r1 = min_image(((double)y + 0.5) - Xp[1], ny, a.g.per[1]);
-            const double r2 = min_image(((double)z + 0.5) - Xp[2], nz, a.g.per[2]);
-            const double u0 = U[0] + (W[1] * r2 - W[2] * r1);
-            const double u1 = U[1] + (W[2] * r0 - W[0] * r2);
-            const double u2 = U[2] + (W[0] * r1 - W[1] * r0);
-            const double uu = (u0 * u0 + u1 * u1) + u2 * u2;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const double cu = ((double)kCx[q] * u0 + (double)kCy[q] * u1) + (double)kCz[q] * u2;
-                v[q] = (CT)T::feq_c(q, (cu * 3.0 + (cu * cu) * 4.5) - uu * 1.5);
-            }
-        }
-    }
+    if constexpr (MODE != kLocal) refill<ST, OFF>(a, x, y, z, c);
 
     if constexpr (MODE == kReadout) {
         // solid cells get defined values: the rest state at walls and
         // f^eq(rho0, u_s) of the owning particle at obstacle cells
         if (!act && c.valid) {
-            double u0 = 0.0, u1 = 0.0, u2 = 0.0;
-            if (!(c.fl & kWall)) {
-                const uint32_t po = a.owner[ci];
-                const double *Xp = a.Xc + 3 * (size_t)po;
-                const double *U = a.U + 3 * (size_t)po;
-                const double *W = a.W + 3 * (size_t)po;
-                const double r0 = min_image(((double)x + 0.5) - Xp[0], nx, a.g.per[0]);
-                const double r1 = min_image(((double)y + 0.5) - Xp[1], ny, a.g.per[1]);
-                const double r2 = min_image(((double)z + 0.5) - Xp[2], nz, a.g.per[2]);
-                u0 = U[0] + (W[1] * r2 - W[2] * r1);
-                u1 = U[1] + (W[2] * r0 - W[0] * r2);
-                u2 = U[2] + (W[0] * r1 - W[1] * r0);
-            }
-            const double uu = (u0 * u0 + u1 * u1) + u2 * u2;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const double cu = ((double)kCx[q] * u0 + (double)kCy[q] * u1) + (double)kCz[q] * u2;
-                v[q] = (CT)T::feq_c(q, (cu * 3.0 + (cu * cu) * 4.5) - uu * 1.5);
-            }
+            double u[3] = {0.0, 0.0, 0.0};
+            if (!(c.fl & kWall)) surface_velocity(a, a.Xc, a.owner[ci], x, y, z, u);
+            equilibrium<ST>(u, v);
         }
         if (c.valid) {
 #pragma unroll
@@ -716,6 +716,35 @@ __device__ __forceinline__ uint32_t quot(uint32_t t, int n, uint32_t m) {
     return n >= 2048 ? (uint32_t)(t >= (uint32_t)n) : __umulhi(2u * t, m);
 }
 
+// this lane's cell of segment lb; beyond the grid: not valid, cell 0
+template <typename OFF>
+struct Place {
+    int x, y, z;
+    OFF ci;
+    bool valid;
+    __device__ __forceinline__ Place(const SweepArgs &a, uint32_t lb) {
+        const int nx = a.g.nx, ny = a.g.ny;
+        // the segment's first cell in scalar registers: quotients by
+        // multiplication with 2^63 / n + 1, exact while cell times extent is
+        // below 2^63
+        const OFF c0 = (OFF)lb * blockDim.x;
+        const uint64_t row = __umul64hi(2u * (uint64_t)c0, a.mx);
+        const uint64_t plane = __umul64hi(2u * row, a.my);
+        const uint32_t x0 = (uint32_t)((uint64_t)c0 - row * (uint64_t)(uint32_t)nx);
+        const uint32_t y0 = (uint32_t)(row - plane * (uint64_t)(uint32_t)ny);
+        // this lane's, from there
+        const uint32_t t = x0 + threadIdx.x;
+        const uint32_t dy = quot(t, nx, (uint32_t)(a.mx >> 32) + 1u);
+        const uint32_t ty = y0 + dy;
+        const uint32_t dz = quot(ty, ny, (uint32_t)(a.my >> 32) + 1u);
+        valid = (size_t)c0 + threadIdx.x < a.g.N;
+        x = valid ? (int)(t - dy * (uint32_t)nx) : 0;
+        y = valid ? (int)(ty - dz * (uint32_t)ny) : 0;
+        z = valid ? (int)((uint32_t)plane + dz) : 0;
+        ci = valid ? c0 + threadIdx.x : (OFF)0;
+    }
+};
+
 // One workgroup's blockDim.x consecutive cells of the flat grid.  A sweep is
 // bound by its memory traffic; with the cells dealt out across rows every
 // lane has a cell and every store covers whole aligned lines, whatever nx is.
@@ -727,26 +756,10 @@ __device__ __forceinline__ uint32_t quot(uint32_t t, int n, uint32_t m) {
 //   512^3            7614 -> 7068   3648 -> 3589   1883 -> 1818 us.)
 template <typename ST, int FMODE, typename OFF, int MODE>
 __device__ __forceinline__ void sweep_segment(const SweepArgs &a, uint32_t lb) {
-    const int nx = a.g.nx, ny = a.g.ny;
-    // the first cell's place in scalar registers: quotients by multiplication
-    // with 2^63 / n + 1, exact while cell times extent is below 2^63
-    const OFF c0 = (OFF)lb * blockDim.x;
-    const uint64_t row = __umul64hi(2u * (uint64_t)c0, a.mx);
-    const uint64_t plane = __umul64hi(2u * row, a.my);
-    const uint32_t x0 = (uint32_t)((uint64_t)c0 - row * (uint64_t)(uint32_t)nx);
-    const uint32_t y0 = (uint32_t)(row - plane * (uint64_t)(uint32_t)ny);
-    // this lane's, from there
-    const uint32_t t = x0 + threadIdx.x;
-    const uint32_t dy = quot(t, nx, (uint32_t)(a.mx >> 32) + 1u);
-    const uint32_t ty = y0 + dy;
-    const uint32_t dz = quot(ty, ny, (uint32_t)(a.my >> 32) + 1u);
-    const bool valid = (size_t)c0 + threadIdx.x < a.g.N;
-    const int x = valid ? (int)(t - dy * (uint32_t)nx) : 0;
-    const int y = valid ? (int)(ty - dz * (uint32_t)ny) : 0;
-    const int z = valid ? (int)((uint32_t)plane + dz) : 0;
-    CellIn<typename Storage<ST>::CT, OFF> c;
-    load_cell<ST, FMODE, OFF, MODE>(a, x, y, z, valid ? c0 + threadIdx.x : (OFF)0, valid, c);
-    finish_cell<ST, FMODE, OFF, MODE>(a, x, y, z, c);
+    const Place<OFF> c(a, lb);
+    CellIn<typename Storage<ST>::CT, OFF> in;
+    load_cell<ST, FMODE, OFF, MODE>(a, c.x, c.y, c.z, c.ci, c.valid, in);
+    finish_cell<ST, FMODE, OFF, MODE>(a, c.x, c.y, c.z, in);
 }
 
 // workgroup b of the next level's mapping: a particle per kMapThreads threads
@@ -777,6 +790,103 @@ __global__ void __launch_bounds__(512) k_sweep(SweepArgs a, MapSetArgs ms, uint3
         if (b >= nseg) return;
     }
     sweep_segment<ST, FMODE, OFF, MODE>(a, a.xcd_swizzle ? xcd_remap(b, nseg) : b);
+}
+
+// Density and velocity (Eq. MacroscopVel with the velocity of
+// Eq. modified_velocity) as FP64 fields.  MODE kReadout gathers the
+// populations from the post-collision state, as the next sweep will, and
+// leaves that state as it is: one pass over the populations, bound by it (512^3
+// FP32: 2.68 ms for 15.2 GB; 20 steps with 4096 spheres and a read-out took
+// 86.3 ms with a gather into the spare grid, read again here and collided in
+// place by the next step, and take 81.9 ms); kLocal reads the post-stream
+// state in the grid.
+template <typename ST, typename OFF, int MODE>
+__global__ void __launch_bounds__(256) k_macro(SweepArgs a, int force_mode, double *rho, double *u) {
+    using CT = typename Storage<ST>::CT;
+    const Place<OFF> p(a, blockIdx.x);
+    CellIn<CT, OFF> c;
+    load_cell<ST, kForceNone, OFF, MODE>(a, p.x, p.y, p.z, p.ci, p.valid, c);
+    const size_t N = a.g.N, i = (size_t)p.ci;
+    double fb[3] = {0.0, 0.0, 0.0};
+    if (force_mode == kForceDense) {
+        const CT *f = static_cast<const CT *>(a.force) + i;
+        for (int k = 0; k < 3; ++k) fb[k] = (double)f[(size_t)k * a.g.Ns];
+    } else if (force_mode == kForceCharge) {
+        const double re = (double)static_cast<const CT *>(a.force)[i];
+        for (int k = 0; k < 3; ++k) fb[k] = re * a.E[k];
+    } else if (force_mode == kForcePotential && !(c.fl & (kWall | kObst))) {
+        // the force of the sweep, in its compute precision
+        CT f0, f1, f2;
+        potential_force<CT>(a.g, p.x, p.y, p.z, c.fl, static_cast<const CT *>(a.force), a.flag,
+                            a.owner, a.zeta, (CT)a.keps, (CT)a.E[0], (CT)a.E[1], (CT)a.E[2], f0, f1,
+                            f2);
+        fb[0] = (double)f0;
+        fb[1] = (double)f1;
+        fb[2] = (double)f2;
+    }
+    if constexpr (MODE != kLocal) refill<ST, OFF>(a, p.x, p.y, p.z, c);
+    if (!p.valid) return;
+    double r = 1.0, v[3] = {0.0, 0.0, 0.0};
+    if (c.fl & (kWall | kObst)) {
+        if (!(c.fl & kWall)) surface_velocity(a, a.Xc, a.owner[i], p.x, p.y, p.z, v);
+    } else {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            // the stored value: compute units of FP16 are scaled deviations
+            double f = (double)c.v[q];
+            if constexpr (sizeof(ST) == 2) f = (double)((float)c.v[q] * kHalfInvScale);
+            s += f;
+            v[0] += (double)kCx[q] * f;
+            v[1] += (double)kCy[q] * f;
+            v[2] += (double)kCz[q] * f;
+        }
+        r = sizeof(ST) == 8 ? s : 1.0 + s;
+        for (int k = 0; k < 3; ++k) v[k] = v[k] + 0.5 * fb[k];
+    }
+    __builtin_nontemporal_store(r, rho + i);
+    for (int k = 0; k < 3; ++k) __builtin_nontemporal_store(v[k], u + (size_t)k * N + i);
+}
+
+template <typename ST>
+void launch_slip_swap(const SweepArgs &a, hipStream_t s) {
+    const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
+    size_t cells = 0;
+    for (int f = 0; f < 6; ++f)
+        if (a.slip & (1 << f))
+            cells += (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
+    if (cells)
+        hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, a);
+}
+
+// 32-bit byte offsets when two population arrays fit in 4 GiB (the gather
+// addresses an opposite pair from one base)
+template <typename ST>
+bool small_grid(const Grid &g) {
+    return 2 * g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * g.Ns < (size_t(1) << 32);
+}
+
+// read-out of the post-collision state in a.src (pull) or of the post-stream
+// state there
+template <typename ST>
+hipError_t launch_macro_typed(int force_mode, const SweepArgs &a, bool pull, double *rho, double *u,
+                              hipStream_t s) {
+    const dim3 grid((unsigned)((a.g.N + 255) / 256)), block(256);
+    // the reflection of free-slip faces is a swap of slots, so a second one
+    // after the gather restores the state
+    if (pull) launch_slip_swap<ST>(a, s);
+#define LBMEP_MACRO(OFF, MD) \
+    hipLaunchKernelGGL((k_macro<ST, OFF, MD>), grid, block, 0, s, a, force_mode, rho, u)
+    if (small_grid<ST>(a.g)) {
+        if (pull) LBMEP_MACRO(uint32_t, kReadout);
+        else LBMEP_MACRO(uint32_t, kLocal);
+    } else {
+        if (pull) LBMEP_MACRO(uint64_t, kReadout);
+        else LBMEP_MACRO(uint64_t, kLocal);
+    }
+#undef LBMEP_MACRO
+    if (pull) launch_slip_swap<ST>(a, s);
+    return hipGetLastError();
 }
 
 // the gather sweep of several lattices in one dispatch
@@ -818,19 +928,10 @@ hipError_t launch_sweep_packed_typed(int force_mode, const PackTable &t, hipStre
 template <typename ST>
 hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x,
                         const MapSetArgs *map, hipStream_t s) {
-    // 32-bit byte offsets when two population arrays fit in 4 GiB (the
-    // gather addresses an opposite pair from one base)
-    const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);
-    if (a.slip && mode != kLocal) {
-        // free-slip faces: the reflected values into the slots the gather
-        // reads beyond those faces
-        const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
-        size_t cells = 0;
-        for (int f = 0; f < 6; ++f)
-            if (a.slip & (1 << f))
-                cells += (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
-        hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, a);
-    }
+    const bool small = small_grid<ST>(a.g);
+    // free-slip faces: the reflected values into the slots the gather reads
+    // beyond those faces
+    if (mode != kLocal) launch_slip_swap<ST>(a, s);
     // the workgroups-per-CU cap was measured on the 32-bit-offset kernel;
     // the 64-bit one runs faster without it (864 x 1248 x 864 FP32: 24.6
     // against 27.5 ms)

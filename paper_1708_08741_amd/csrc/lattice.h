@@ -135,6 +135,7 @@ size_t storage_bytes(int precision);
 size_t population_stride(size_t N, int precision);
 size_t compute_bytes(int precision);
 bool finite_all(const double *p, size_t n);
+bool finite_all(const float *p, size_t n);
 int check_config(const lbmep_config *cfg);
 // device bytes of a lattice (what lbmep_footprint reports)
 size_t lattice_bytes(const lbmep_config *cfg, int32_t n_particles, double r_max,

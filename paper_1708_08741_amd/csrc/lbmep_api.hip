@@ -52,10 +52,28 @@ size_t population_stride(size_t N, int precision) {
 
 size_t compute_bytes(int precision) { return precision == LBMEP_FP64 ? 8 : 4; }
 
-bool finite_all(const double *p, size_t n) {
-    for (size_t i = 0; i < n; ++i)
-        if (!std::isfinite(p[i])) return false;
+// the exponent of an infinity or NaN is all ones: adding one to it carries
+// into the sign bit, and the or of the sums needs no branch per value, so the
+// host's vector instructions do it
+template <typename U, typename T>
+bool finite_bits(const T *p, size_t n, U mask, U one) {
+    for (size_t i = 0; i < n;) {
+        const size_t e = std::min(n, i + 4096);
+        U any = 0;
+        for (; i < e; ++i) {
+            U b;
+            std::memcpy(&b, p + i, sizeof b);
+            any |= (b & mask) + one;
+        }
+        if (any >> (8 * sizeof(U) - 1)) return false;
+    }
     return true;
+}
+bool finite_all(const double *p, size_t n) {
+    return finite_bits<uint64_t>(p, n, uint64_t(0x7ff) << 52, uint64_t(1) << 52);
+}
+bool finite_all(const float *p, size_t n) {
+    return finite_bits<uint32_t>(p, n, uint32_t(0xff) << 23, uint32_t(1) << 23);
 }
 
 hipError_t dev_alloc(lbmep_lattice *L, void **p, size_t bytes) {
@@ -664,13 +682,9 @@ static int set_force_common(lbmep_lattice *L, const void *in, int dtype, int on_
     if (rc) return rc;
     const size_t N = L->g.N, Ns = L->g.Ns;
     const size_t ib = dtype == LBMEP_DTYPE_F64 ? 8 : 4;
-    if (!on_device) {
-        for (size_t i = 0; i < (size_t)ncomp * N; ++i) {
-            const double v = dtype == LBMEP_DTYPE_F64 ? ((const double *)in)[i]
-                                                      : (double)((const float *)in)[i];
-            if (!std::isfinite(v)) return fail(LBMEP_EINVAL, "non-finite force value");
-        }
-    }
+    if (!on_device && !(dtype == LBMEP_DTYPE_F64 ? finite_all((const double *)in, (size_t)ncomp * N)
+                                                 : finite_all((const float *)in, (size_t)ncomp * N)))
+        return fail(LBMEP_EINVAL, "non-finite force value");
     HIP_TRY(hipStreamSynchronize(L->stream));
     const size_t need = (size_t)ncomp * Ns * compute_bytes(L->precision);
     if (L->force_bytes < need) {

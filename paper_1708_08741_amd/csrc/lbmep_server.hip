@@ -104,6 +104,55 @@ class Arena final : public DevHeap {
     std::unordered_map<size_t, size_t> live_;  // offset -> length
 };
 
+// Pinned host blocks for the results of one server.  A copy from the device
+// into pinned memory runs beside the host and the stepping at the link's rate
+// (32 MB: 0.6 ms; into fresh pageable memory 8 ms, with the host waiting; a
+// batch of eight with 30 MB each finished after 28 instead of 38-72 ms).
+// A block belongs to a request until that is released and then waits for the
+// next one that fits; all blocks together stay below `limit` (a result that
+// finds no room goes to pageable memory) and go back with the server.
+class PinnedBlocks {
+  public:
+    ~PinnedBlocks() {
+        for (auto &b : all_) hipHostFree(b.first);
+    }
+    void set_limit(size_t bytes) { limit_ = bytes; }
+    double *take(size_t bytes) {
+        const size_t need = round_up(bytes, size_t(1) << 20);
+        // the smallest waiting block of up to twice the size
+        auto it = idle_.lower_bound(need);
+        if (it != idle_.end() && it->first <= 2 * need) {
+            double *p = it->second;
+            idle_.erase(it);
+            return p;
+        }
+        while (held_ + need > limit_ && !idle_.empty()) drop(std::prev(idle_.end()));
+        if (held_ + need > limit_) return nullptr;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        all_[static_cast<double *>(p)] = need;
+        held_ += need;
+        return static_cast<double *>(p);
+    }
+    void give(double *p) {
+        if (p) idle_.emplace(all_[p], p);
+    }
+
+  private:
+    void drop(std::multimap<size_t, double *>::iterator it) {
+        held_ -= it->first;
+        all_.erase(it->second);
+        hipHostFree(it->second);
+        idle_.erase(it);
+    }
+    size_t limit_ = 0, held_ = 0;
+    std::map<double *, size_t> all_;
+    std::multimap<size_t, double *> idle_;  // by size
+};
+
 struct Request {
     uint64_t id = 0;
     lbmep_config cfg{};
@@ -121,6 +170,7 @@ struct Request {
     int status = LBMEP_OK;
     std::string error;
     std::vector<double> F, M, rho, u;
+    double *fields = nullptr;  // rho, u in a pinned block (instead of the vectors)
     double inv[4] = {0, 0, 0, 0};
 };
 
@@ -150,7 +200,8 @@ struct lbmep_server {
     lbmep_server_config cfg{};
     std::chrono::steady_clock::time_point t0;
     Arena arena;
-    hipStream_t main = nullptr, setup = nullptr;
+    PinnedBlocks pinned;
+    hipStream_t main = nullptr, setup = nullptr, copy = nullptr;
     std::deque<std::unique_ptr<Request>> queue;
     std::unordered_map<uint64_t, std::unique_ptr<Request>> finished;
     std::deque<uint64_t> unreported;  // finished ids not yet returned by poll
@@ -164,6 +215,25 @@ struct lbmep_server {
 };
 
 namespace {
+
+// copy of a result into the caller's memory, which is mostly touched here for
+// the first time: a large one by four threads (eight results of 30 MB on
+// average: one thread 13.5 ms, four 7.6 ms)
+void copy_out(void *dst, const void *src, size_t bytes) {
+    constexpr size_t kParts = 4, kLarge = size_t(4) << 20;
+    const size_t part = bytes < kLarge ? bytes : round_up(bytes / kParts + 1, 4096);
+    std::vector<std::thread> t;
+    size_t done = 0;
+    try {
+        t.reserve(kParts);
+        for (; done + part < bytes; done += part)
+            t.emplace_back(std::memcpy, static_cast<char *>(dst) + done,
+                           static_cast<const char *>(src) + done, part);
+    } catch (...) {  // no thread to be had: the rest is copied here
+    }
+    std::memcpy(static_cast<char *>(dst) + done, static_cast<const char *>(src) + done, bytes - done);
+    for (std::thread &k : t) k.join();
+}
 
 hipEvent_t get_event(lbmep_server *S) {
     if (!S->ev_pool.empty()) {
@@ -223,9 +293,7 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
         rc = lbmep_set_charge_force(L, r->rho_e.data(), r->rho_dtype, r->E, 0);
         if (rc) return undo(rc);
     }
-    const double u0[3] = {0, 0, 0};
-    rc = lbmep_init_equilibrium(L, 1.0, u0);
-    if (rc) return undo(rc);
+    // (a new lattice rests in equilibrium at density 1)
     rc = lbmep_set_particles(L, r->n, r->X.data(), r->R.data(), r->U.data(), r->W.data());
     if (rc) return undo(rc);
     rc = lbmep_step(L, 1);
@@ -289,6 +357,17 @@ int enqueue_readout(lbmep_server *S, Slot &slot) {
     slot.ev = get_event(S);
     if (!slot.ev) return fail(LBMEP_EDEVICE, "event creation failed");
     LBMEP_HIP_TRY(hipEventRecord(slot.ev, s));
+    if (slot.fields) {
+        // the fields travel beside the stepping of the other simulations
+        const size_t b = 4 * L->g.N * sizeof(double);
+        slot.req->fields = S->pinned.take(b);
+        if (slot.req->fields) {
+            LBMEP_HIP_TRY(hipStreamWaitEvent(S->copy, slot.ev, 0));
+            LBMEP_HIP_TRY(hipMemcpyAsync(slot.req->fields, slot.fields, b, hipMemcpyDeviceToHost,
+                                         S->copy));
+            LBMEP_HIP_TRY(hipEventRecord(slot.ev, S->copy));
+        }
+    }
     slot.retiring = true;
     return LBMEP_OK;
 }
@@ -313,7 +392,7 @@ void retire(lbmep_server *S, Slot &slot) {
     }
     ok = ok && hipMemcpy(r->inv, L->red + 5 * (size_t)L->red_blocks, 4 * sizeof(double),
                          hipMemcpyDeviceToHost) == hipSuccess;
-    if (slot.fields) {
+    if (slot.fields && !r->fields) {
         r->rho.resize(N);
         r->u.resize(3 * N);
         ok = ok && hipMemcpy(r->rho.data(), slot.fields, N * sizeof(double),
@@ -494,6 +573,8 @@ int lbmep_server_create(const lbmep_server_config *cfg, lbmep_server **out) {
         return fail(LBMEP_ENOMEM, "device arena allocation failed");
     LBMEP_HIP_TRY(hipStreamCreateWithFlags(&S->main, hipStreamNonBlocking));
     LBMEP_HIP_TRY(hipStreamCreateWithFlags(&S->setup, hipStreamNonBlocking));
+    LBMEP_HIP_TRY(hipStreamCreateWithFlags(&S->copy, hipStreamNonBlocking));
+    S->pinned.set_limit(std::min(S->arena.size(), size_t(1) << 30));
     S->slots.resize(cfg->max_slots);
     S->st.budget = S->arena.size();
     *out = S.release();
@@ -505,6 +586,7 @@ int lbmep_server_destroy(lbmep_server *S) {
     hipSetDevice(S->cfg.device);
     hipStreamSynchronize(S->main);
     hipStreamSynchronize(S->setup);
+    hipStreamSynchronize(S->copy);
     for (Slot &sl : S->slots) {
         if (!sl.req) continue;
         S->arena.release(sl.fields);
@@ -517,6 +599,7 @@ int lbmep_server_destroy(lbmep_server *S) {
     for (hipEvent_t e : S->ev_pool) hipEventDestroy(e);
     hipStreamDestroy(S->main);
     hipStreamDestroy(S->setup);
+    hipStreamDestroy(S->copy);
     delete S;
     return LBMEP_OK;
 }
@@ -624,9 +707,10 @@ int lbmep_server_fields(lbmep_server *S, uint64_t id, double *rho, double *u) {
     if (it == S->finished.end()) return fail(LBMEP_ESTATE, "request not finished (or unknown)");
     Request *r = it->second.get();
     if (r->status != LBMEP_OK) return fail(r->status, "request failed: " + r->error);
-    if (r->rho.empty()) return fail(LBMEP_ESTATE, "request was submitted without keep_fields");
-    std::memcpy(rho, r->rho.data(), r->rho.size() * sizeof(double));
-    std::memcpy(u, r->u.data(), r->u.size() * sizeof(double));
+    if (!r->keep_fields) return fail(LBMEP_ESTATE, "request was submitted without keep_fields");
+    const size_t N = (size_t)r->cfg.nx * r->cfg.ny * r->cfg.nz;
+    copy_out(rho, r->fields ? r->fields : r->rho.data(), N * sizeof(double));
+    copy_out(u, r->fields ? r->fields + N : r->u.data(), 3 * N * sizeof(double));
     return LBMEP_OK;
 }
 
@@ -634,6 +718,7 @@ int lbmep_server_release(lbmep_server *S, uint64_t id) {
     if (!S) return fail(LBMEP_EINVAL, "null server");
     auto it = S->finished.find(id);
     if (it == S->finished.end()) return fail(LBMEP_ESTATE, "request not finished (or unknown)");
+    S->pinned.give(it->second->fields);
     S->finished.erase(it);
     return LBMEP_OK;
 }

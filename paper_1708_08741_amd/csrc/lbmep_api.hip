@@ -400,7 +400,7 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
     // overlapped stepping for a lattice of its own with moving particles
     // (LBMEP_STEP_OVERLAP=0: the classification after the exchange, in the
     // same workgroups, for comparisons)
-    L->overlap = heap == nullptr && cfg->move_particles;
+    L->overlap = cfg->move_particles != 0;
     if (const char *e = std::getenv("LBMEP_STEP_OVERLAP")) L->overlap = L->overlap && std::atoi(e) != 0;
     L->precision = cfg->precision;
     Grid &g = L->g;

@@ -241,6 +241,10 @@ struct LatticeDev {
     // is the source, which map is the current level's)
     SweepArgs sweep[6];
     ParticleArgs pa;
+    // split: the link lists of the next level, by the parity of the state
+    int split;
+    uint2 *plist[2];
+    uint32_t *pcount[2];
     LevelMap map[3];
     int wall_blocks;  // workgroups of the wall links in the exchange kernel
     uint32_t map_blocks;  // workgroups of the packed sweep that map the next level

@@ -249,7 +249,8 @@ hipEvent_t get_event(lbmep_server *S) {
 size_t request_footprint(const lbmep_config &c, int32_t n, double r_max, bool charge, bool flags,
                          bool keep_fields) {
     const size_t N = (size_t)c.nx * c.ny * c.nz;
-    size_t b = lattice_bytes(&c, n, r_max, charge ? kForceCharge : kForceNone, false);
+    size_t b = lattice_bytes(&c, n, r_max, charge ? kForceCharge : kForceNone,
+                             n > 0 && c.move_particles);
     b += 32 * Arena::kAlign;                 // alignment of the lattice's arrays
     b += round_up(sizeof(LatticeDev), Arena::kAlign);
     // staging of the inputs during set-up
@@ -300,9 +301,19 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     if (rc) return undo(rc);
     // device descriptor for the packed launches
     LatticeDev h{};
+    h.split = L->overlap && L->np > 0;
     for (int cur = 0; cur < 2; ++cur)
         for (int co = 0; co < 3; ++co) {
-            h.sweep[cur + 2 * co] = sweep_args_state(L, cur, co);
+            SweepArgs a = sweep_args_state(L, cur, co);
+            if (h.split) {
+                // the lists change places with the population grids
+                const int l = L->lcur ^ L->cur ^ cur;
+                a.plist = L->plist_buf[l];
+                a.pcount = L->pcount_buf[l];
+                h.plist[cur] = L->plist_buf[l ^ 1];
+                h.pcount[cur] = L->pcount_buf[l ^ 1];
+            }
+            h.sweep[cur + 2 * co] = a;
         }
     h.pa = particle_args(L);
     for (int b = 0; b < 3; ++b) h.map[b] = L->map[b];
@@ -446,7 +457,8 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                     ts.level[ts.n] = tn.level[tn.n] = L->level + 1;
                     ts.start[ts.n + 1] = ts.start[ts.n] + sb;
                     tn.start[tn.n + 1] =
-                        tn.start[tn.n] + (uint32_t)near_blocks(L->np, L->g, L->has_walls);
+                        tn.start[tn.n] + (uint32_t)near_blocks(L->np, L->g, L->has_walls) +
+                        (L->overlap ? (uint32_t)L->np : 0u);
                     ts.n++;
                     tn.n++;
                     if (ts.n == kMaxPack) {

@@ -321,8 +321,10 @@ inline uint32_t parts_lds(int mode, uint32_t box_rows) {
 // (complete since the sweep's launch), the current one and the walls, and
 // writes flags and the next level's link lists; the exchange reads the
 // current lists and the post-collision state; nothing reads the previous
-// level's map any more: they run side by side.
-template <typename ST, typename OFF>
+// level's map any more: they run side by side.  (DYN: lattices with dynamics
+// may come; its run-time component index would keep the arguments that a
+// packed launch loads in scratch memory.)
+template <typename ST, typename OFF, bool DYN>
 __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs &q, uint32_t blk) {
     extern __shared__ __align__(16) unsigned char part_lds[];
     const uint32_t np = (uint32_t)a.np;
@@ -343,7 +345,7 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
         __syncthreads();  // part_lds is reused
         part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
         part::map_clear(q.pa, (int)blk, q.old);
-    } else if (q.mode == kPartsDyn) {
+    } else if (DYN && q.mode == kPartsDyn) {
         __syncthreads();
         move_particle(q.pa, q.dyn, blk, sum, a.Xc + 3 * (size_t)blk);
         __syncthreads();  // X0 is read by every thread
@@ -354,7 +356,7 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
 
 template <typename ST, typename OFF>
 __global__ void __launch_bounds__(kPartThreads, 4) k_parts(SweepArgs a, PartsArgs q) {
-    parts_block<ST, OFF>(a, q, blockIdx.x);
+    parts_block<ST, OFF, true>(a, q, blockIdx.x);
 }
 
 // one workgroup per particle for several lattices in one dispatch
@@ -363,17 +365,22 @@ __global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
     const int e = pack_find(t, blockIdx.x);
     const LatticeDev *d = t.d[e];
     const uint32_t st = t.state[e];
-    const SweepArgs a = d->sweep[st];
+    const SweepArgs a = packed_args(&d->sweep[st]);
     const uint32_t c = st >> 1;
     PartsArgs q{};
-    q.mode = d->pa.moving && d->pa.np > 0 ? kPartsOne : kPartsNear;
-    q.wall_blocks = d->wall_blocks;
-    q.pa = d->pa;
-    q.old = d->map[c == 0 ? 2 : c - 1];
-    q.cur = d->map[c];
-    q.next = d->map[c == 2 ? 0 : c + 1];
+    q.wall_blocks = load_uniform(&d->wall_blocks);
+    q.pa = packed_args(&d->pa);
+    const int split = load_uniform(&d->split);
+    q.mode = !q.pa.moving || q.pa.np == 0 ? kPartsNear : split ? kPartsSplit : kPartsOne;
+    if (split) {
+        q.pa.plist = as_global(load_uniform(&d->plist[st & 1u]));
+        q.pa.pcount = as_global(load_uniform(&d->pcount[st & 1u]));
+    }
+    q.old = packed_args(&d->map[c == 0 ? 2 : c - 1]);
+    q.cur = packed_args(&d->map[c]);
+    q.next = packed_args(&d->map[c == 2 ? 0 : c + 1]);
     q.level = t.level[e];
-    parts_block<ST, uint32_t>(a, q, blockIdx.x - t.start[e]);
+    parts_block<ST, uint32_t, false>(a, q, blockIdx.x - t.start[e]);
 }
 
 // workgroups of the wall pass (0 without wall cells)

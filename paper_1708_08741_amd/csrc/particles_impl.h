@@ -380,6 +380,7 @@ __device__ __forceinline__ void classify(const ParticleArgs &pa, int p, const Le
     const double R = pa.R[p];
     Box b;
     const int len[3] = {g.nx, g.ny, g.nz};
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
         const double a0 = old.X[3 * (size_t)p + k], a1 = now.X[3 * (size_t)p + k];
         double mn = a0 < a1 ? a0 : a1, mx = a0 < a1 ? a1 : a0;
@@ -431,11 +432,21 @@ __device__ __forceinline__ void classify(const ParticleArgs &pa, int p, const Le
             rows.mine[h] = 0ull;
         }
         __syncthreads();
-        // p's own obstacle cells (four owners of a row in flight)
+        // p's own obstacle cells, of those with a neighbour that is not solid
+        // (links lead to no others; four owners of a row in flight)
         for (int h = tid; h < hrows; h += nt) {
             uint64_t o = rows.obst[h], mine = 0;
             if (!o) continue;
-            int y = b.lo[1] - 1 + h % hy, z = b.lo[2] - 1 + h / hy;
+            const int iy = h % hy, iz = h / hy;
+            if (iy > 0 && iy < hy - 1 && iz > 0 && iz < hz - 1) {
+                const uint64_t *S = rows.solid + h;
+                const uint64_t face = S[-1] & S[1] & S[-hy] & S[hy], all5 = S[0] & face;
+                // closed: all 18 neighbours solid; the end columns stay open
+                const uint64_t closed = face & S[-1 - hy] & S[1 - hy] & S[-1 + hy] & S[1 + hy] &
+                                        (all5 << 1) & (all5 >> 1);
+                o &= ~closed;
+            }
+            int y = b.lo[1] - 1 + iy, z = b.lo[2] - 1 + iz;
             if (g.per[1]) y = wrap_axis(y, g.ny);
             if (g.per[2]) z = wrap_axis(z, g.nz);
             const uint32_t *ow = now.owner + cell_of(g, 0, y, z);

@@ -889,6 +889,64 @@ hipError_t launch_macro_typed(int force_mode, const SweepArgs &a, bool pull, dou
     return hipGetLastError();
 }
 
+// A packed launch reads its arguments from the lattice's descriptor.  Loaded
+// through a plain pointer they would be vector values, and the pointers among
+// them generic ones: the descriptor is constant during the launch and the
+// entry the same for the workgroup, so they are read into scalar registers,
+// and the pointers are to global memory (eight lattices of 64^3 to 128^3 cells
+// with up to 56 spheres each: exchange and classification 71 -> 42 us, in
+// which 296 bytes of arguments per thread had also lain in scratch memory).
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T *p) {
+    T r;
+    __builtin_memcpy(&r, (const T *)(const __attribute__((address_space(4))) T *)(uintptr_t)p, sizeof(T));
+    return r;
+}
+__device__ __forceinline__ SweepArgs packed_args(const SweepArgs *p) {
+    SweepArgs a = load_uniform(p);
+    a.src = as_global(a.src);
+    a.dst = as_global(a.dst);
+    a.flag = as_global(a.flag);
+    a.nearmask = as_global(a.nearmask);
+    a.owner = as_global(a.owner);
+    a.owner_old = as_global(a.owner_old);
+    a.Xc = as_global(a.Xc);
+    a.Xold = as_global(a.Xold);
+    a.U = as_global(a.U);
+    a.W = as_global(a.W);
+    a.FM = as_global(a.FM);
+    a.force = as_global(a.force);
+    a.zeta = as_global(a.zeta);
+    a.plist = as_global(a.plist);
+    a.pcount = as_global(a.pcount);
+    a.wlist = as_global(a.wlist);
+    a.wcount = as_global(a.wcount);
+    return a;
+}
+__device__ __forceinline__ ParticleArgs packed_args(const ParticleArgs *p) {
+    ParticleArgs a = load_uniform(p);
+    a.X0 = as_global(a.X0);
+    a.R = as_global(a.R);
+    a.U = as_global(a.U);
+    a.W = as_global(a.W);
+    a.flag = as_global(a.flag);
+    a.wallbits = as_global(a.wallbits);
+    a.plist = as_global(a.plist);
+    a.pcount = as_global(a.pcount);
+    return a;
+}
+__device__ __forceinline__ LevelMap packed_args(const LevelMap *p) {
+    LevelMap m = load_uniform(p);
+    m.owner = as_global(m.owner);
+    m.bits = as_global(m.bits);
+    m.X = as_global(m.X);
+    return m;
+}
+
 // the gather sweep of several lattices in one dispatch
 template <typename ST, int FMODE>
 __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
@@ -897,13 +955,14 @@ __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
     const LatticeDev *d = t.d[e];
     uint32_t b = gb - t.start[e];
     // the entry's first workgroups map its next level
-    if (b < d->map_blocks) {
+    const uint32_t map_blocks = load_uniform(&d->map_blocks);
+    if (b < map_blocks) {
         const uint32_t c = t.state[e] >> 1;
-        map_particles(d->pa, b, t.level[e], d->map[c == 2 ? 0 : c + 1]);
+        map_particles(packed_args(&d->pa), b, t.level[e], packed_args(&d->map[c == 2 ? 0 : c + 1]));
         return;
     }
-    b -= d->map_blocks;
-    const SweepArgs a = d->sweep[t.state[e]];
+    b -= map_blocks;
+    const SweepArgs a = packed_args(&d->sweep[t.state[e]]);
     // streaming hints as in the single-lattice default: stores only
     constexpr int MODE = kPullNTS;
     sweep_segment<ST, FMODE, uint32_t, MODE>(a, b);

@@ -38,7 +38,7 @@
 // plane) space is cut into one equal range per resident workgroup, so the
 // last wave of workgroups is not nearly empty and small grids still use every
 // CU.  Measured, 29 iterations with boundaries: 512^3 FP32 with 4096 spheres
-// 8.91 -> 6.34 ms, 64^3 FP32 1.47 -> 0.28 ms, 144^3 FP64 3.03 -> 0.98 ms,
+// 8.91 -> 6.34 ms, 64^3 FP32 1.47 -> 0.28 ms, 144^3 FP64 3.03 -> 0.76 ms,
 // 256 x 200 x 300 FP64 3.11 -> 1.98 ms.  Two rows per wavefront (8 wavefronts,
 // half the scalar work per row) took 7.45 ms, reading the next stage's LDS
 // rows a stage early (spills) 6.73 ms.
@@ -602,14 +602,19 @@ struct TilePlan {
     TileShape shape;
     bool pairs = false;  // two iterations per pass
 };
-// two iterations per pass halve the bytes of a solve; their 2 * 3 rows of
-// halo need a workgroup of 16 rows (rows in one wavefront)
+// Two iterations per pass halve the bytes of a solve; their 2 * 3 rows of
+// halo need a workgroup of 16 rows (rows in one wavefront).  FP64 takes one:
+// the operands of four stages do not fit in 128 registers, and of two rows of
+// halo in 16 less is computed twice.  Per iteration in pairs and singly: FP64
+// 64^3 13.6 / 11.5, 144^3 29.9 / 24.4, 200^3 45.6 / 37.1, 320 x 300 x 280 149 /
+// 141, 512^3 539 / 536 us; FP32 144^3 17.9 / 19.3, 320 x 300 x 280 54 / 65,
+// 512^3 196 / 277 us.
 template <typename CT>
 TilePlan tile_plan(const SorArgs &a, bool fused) {
     TilePlan t;
     if (!fused || !a.psi2 || !a.save || !a.codes) return t;
     t.shape = tile_shape<CT>(a.g);
-    t.pairs = t.shape.V > 0 && t.shape.nwx == 1;
+    t.pairs = sizeof(CT) == 4 && t.shape.V > 0 && t.shape.nwx == 1;
     return t;
 }
 
@@ -668,10 +673,15 @@ template <typename CT>
 void launch_tile_pass(const SorArgs &a, const CT *src, CT *dst, int k, hipStream_t s) {
     const TileShape t = tile_shape<CT>(a.g);
     if constexpr (sizeof(CT) == 4) {
-        if (t.V == 4) return k == 2 ? launch_tile<CT, 4, 2>(a, t, src, dst, s) : launch_tile<CT, 4, 1>(a, t, src, dst, s);
+        if (k == 2) {
+            if (t.V == 4) return launch_tile<CT, 4, 2>(a, t, src, dst, s);
+            if (t.V == 2) return launch_tile<CT, 2, 2>(a, t, src, dst, s);
+            return launch_tile<CT, 1, 2>(a, t, src, dst, s);
+        }
+        if (t.V == 4) return launch_tile<CT, 4, 1>(a, t, src, dst, s);
     }
-    if (t.V == 2) return k == 2 ? launch_tile<CT, 2, 2>(a, t, src, dst, s) : launch_tile<CT, 2, 1>(a, t, src, dst, s);
-    return k == 2 ? launch_tile<CT, 1, 2>(a, t, src, dst, s) : launch_tile<CT, 1, 1>(a, t, src, dst, s);
+    if (t.V == 2) return launch_tile<CT, 2, 1>(a, t, src, dst, s);
+    return launch_tile<CT, 1, 1>(a, t, src, dst, s);
 }
 
 // launch shape of the passes over the flags: E entries (8 cells, whose flags

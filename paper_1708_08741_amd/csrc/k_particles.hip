@@ -185,7 +185,7 @@ uint32_t box_row_capacity(double r_max) {
     const double e = 2.0 * std::ceil(r_max) + 9.0;
     return e * e <= 1024.0 ? (uint32_t)(e * e) : 1024u;
 }
-uint32_t classify_lds(uint32_t box_rows) { return box_rows * 8u * kRowArrays + 64u; }
+uint32_t classify_lds(uint32_t box_rows) { return box_rows * 8u * kRowArrays + 64u + 4u * kRowCells; }
 
 uint32_t link_capacity(double r_max) {
     const double e = 2.0 * std::ceil(r_max) + 3.0;

@@ -458,7 +458,7 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                     ts.start[ts.n + 1] = ts.start[ts.n] + sb;
                     tn.start[tn.n + 1] =
                         tn.start[tn.n] + (uint32_t)near_blocks(L->np, L->g, L->has_walls) +
-                        (L->overlap ? (uint32_t)L->np : 0u);
+                        (L->overlap ? 2u * (uint32_t)L->np : 0u);
                     ts.n++;
                     tn.n++;
                     if (ts.n == kMaxPack) {

@@ -316,7 +316,7 @@ inline uint32_t parts_lds(int mode, uint32_t box_rows) {
     return mode == kPartsNear || mode == kPartsDyn ? kNearLds : c > kNearLds ? c : kNearLds;
 }
 
-// the particle workgroups of a step, blk of np (2 np when split) + wall
+// the particle workgroups of a step, blk of np (3 np when split) + wall
 // blocks.  The classification of the next level reads that level's map
 // (complete since the sweep's launch), the current one and the walls, and
 // writes flags and the next level's link lists; the exchange reads the
@@ -331,10 +331,13 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
     if (q.mode == kPartsSplit) {
         if (blk < np) {  // first: these take longer
             part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
-            part::map_clear(q.pa, (int)blk, q.old);
             return;
         }
         blk -= np;
+        if (blk >= np + (uint32_t)q.wall_blocks) {
+            part::map_clear(q.pa, (int)(blk - np - (uint32_t)q.wall_blocks), q.old);
+            return;
+        }
     }
     if (blk >= np) {
         near_walls<ST, OFF>(a, blk - np, (uint32_t)q.wall_blocks);
@@ -402,7 +405,7 @@ hipError_t launch_parts_packed_typed(const PackTable &t, uint32_t lds, hipStream
 
 template <typename ST>
 hipError_t launch_parts_typed(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {
-    const unsigned blocks = (unsigned)a.np * (q.mode == kPartsSplit ? 2u : 1u) + (unsigned)q.wall_blocks;
+    const unsigned blocks = (unsigned)a.np * (q.mode == kPartsSplit ? 3u : 1u) + (unsigned)q.wall_blocks;
     if (blocks == 0) return hipSuccess;
     const uint32_t lds = parts_lds(q.mode, q.pa.box_rows);
     const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);

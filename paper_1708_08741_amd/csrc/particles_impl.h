@@ -359,7 +359,9 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t mine, uint32_t *wsum, 
 struct BoxRows {
     uint64_t *solid, *obst, *mine, *uncov, *near, *near7;
     uint32_t *wsum;
+    uint32_t *cell;  // kRowCells list entries in the making: row, column
 };
+constexpr uint32_t kRowCells = 2048;
 
 // Classification around particle p (union of its boxes at the previous and
 // the new position, grown by one cell): flags of the new level and the list
@@ -498,24 +500,33 @@ __device__ __forceinline__ void classify(const ParticleArgs &pa, int p, const Le
             uint32_t total;
             uint32_t pos = base + block_prefix((uint32_t)__popcll(ml), rows.wsum, &total);
             base += total;
-            if (ml) {
-                int y = b.lo[1] + iy, z = b.lo[2] + iz;
-                if (g.per[1]) y = wrap_axis(y, g.ny);
-                if (g.per[2]) z = wrap_axis(z, g.nz);
-                const size_t c0 = cell_of(g, 0, y, z);
-                const uint64_t *M = rows.mine + h;
-                while (ml) {
-                    const int ix = __ffsll((unsigned long long)ml) - 1;
-                    ml &= ml - 1ull;
-                    int x = b.lo[0] - 1 + ix;
+            // a row's cells are laid out in LDS, then taken one per thread: a
+            // row thread that formed their masks itself held up the others
+            // (14 cells of 18 directions)
+            const uint32_t start = base - total;
+            for (uint32_t w0 = 0; w0 < total; w0 += kRowCells) {
+                for (; ml && pos - start - w0 < kRowCells; ml &= ml - 1ull, ++pos)
+                    rows.cell[pos - start - w0] =
+                        (uint32_t)h << 6 | (uint32_t)(__ffsll((unsigned long long)ml) - 1);
+                __syncthreads();
+                const uint32_t m = min(kRowCells, total - w0);
+                for (uint32_t k = (uint32_t)tid; k < m; k += (uint32_t)nt) {
+                    const uint32_t w = rows.cell[k];
+                    const int ch = (int)(w >> 6), ix = (int)(w & 63u);
+                    const int cz = ch / hy;
+                    int x = b.lo[0] - 1 + ix, y = b.lo[1] - 1 + (ch - cz * hy), z = b.lo[2] - 1 + cz;
                     if (g.per[0]) x = wrap_axis(x, g.nx);
+                    if (g.per[1]) y = wrap_axis(y, g.ny);
+                    if (g.per[2]) z = wrap_axis(z, g.nz);
+                    const uint64_t *M = rows.mine + ch;
                     uint32_t pm = 0;
 #pragma unroll
                     for (int q = 1; q < Q; ++q)
                         pm |= (uint32_t)((M[kCy[q] + hy * kCz[q]] >> (ix + kCx[q])) & 1ull) << (q - 1);
-                    if (pos < pa.pcap) plist[pos] = make_uint2((uint32_t)(c0 + (size_t)x), pm);
-                    ++pos;
+                    if (start + w0 + k < pa.pcap)
+                        plist[start + w0 + k] = make_uint2((uint32_t)cell_of(g, x, y, z), pm);
                 }
+                __syncthreads();
             }
             __syncthreads();  // wsum is reused; near rows are complete after the last pass
         }
@@ -574,6 +585,7 @@ __device__ __forceinline__ BoxRows box_rows(unsigned char *lds, uint32_t nrows) 
     r.near = w + 4 * (size_t)nrows;
     r.near7 = w + 5 * (size_t)nrows;
     r.wsum = reinterpret_cast<uint32_t *>(w + kRowArrays * (size_t)nrows);
+    r.cell = r.wsum + 16;
     return r;
 }
 

@@ -133,6 +133,11 @@ size_t storage_bytes(int precision);
 // to 128 plus a pad that staggers the 19 arrays against the HBM channel
 // interleave
 size_t population_stride(size_t N, int precision);
+// the two population grids of a lattice: their bytes, and whether they stay
+// in the memory-side cache from one step to the next
+constexpr size_t kInfinityCache = 250000000;
+size_t population_bytes(const lbmep::Grid &g, int precision);
+bool cache_resident(const lbmep::Grid &g, int precision);
 size_t compute_bytes(int precision);
 bool finite_all(const double *p, size_t n);
 bool finite_all(const float *p, size_t n);

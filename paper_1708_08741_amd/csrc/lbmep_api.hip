@@ -384,6 +384,13 @@ int destroy_lattice(lbmep_lattice *L, bool sync) {
     return LBMEP_OK;
 }
 
+size_t population_bytes(const Grid &g, int precision) {
+    return 2 * (size_t)Q * g.Ns * storage_bytes(precision);
+}
+bool cache_resident(const Grid &g, int precision) {
+    return population_bytes(g, precision) < kInfinityCache;
+}
+
 int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) {
     int rc = check_config(cfg);
     if (rc) return rc;
@@ -432,12 +439,19 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
     //                    3.55, FP16 2.31 / 2.05 / 1.86 / 1.78 ms
     //   32^3             FP64 4.9 / 4.9 / 5.4 / 6.1, FP32 4.1 / 4.0 / 4.4 /
     //                    4.6, FP16 3.9 / 3.8 / 4.1 / 4.4 us
-    // Hardware order against segments dealt onto XCDs in contiguous runs: FP64
-    // 825 / 930 us and 7.05 / 6.85 ms (runs vary by 3 %), FP32 389 / 504 us
-    // and 3.48 / 3.75 ms, FP16 201 / 273 us and 1.79 / 1.87 ms on the first
-    // two: every XCD streams the same planes.
+    // Lattices whose two population grids fit in the 256 MB Infinity Cache
+    // keep them there: no streaming hints, and segments dealt onto XCDs in
+    // contiguous runs, so that most neighbours come from the XCD's own L2;
+    // larger ones stream in the hardware's order (every XCD on the same
+    // planes).  With hints and hardware order / without and in runs:
+    //   48^3             FP64 9.5 / 7.2, FP32 6.0 / 5.0, FP16 4.9 / 4.3 us
+    //   101 x 67 x 83    FP64 35.1 / 28.6, FP32 18.7 / 14.8, FP16 11.8 / 9.2
+    //   128 x 96^2       FP64 (359 MB) 69.3 / 77.7, FP32 (179 MB) 40.2 / 28.7
+    //   150^3            FP32 (513 MB) 93.9 / 105, FP16 (256 MB) 49.9 / 54.7
+    //   216^3            FP64 550 / 612, FP32 283 / 312, FP16 149 / 162
+    const bool cached = cache_resident(g, L->precision);
     L->block_x = L->precision == LBMEP_FP64 ? 128 : L->precision == LBMEP_FP16DEV ? 512 : 256;
-    L->xcd_swizzle = 0;
+    L->xcd_swizzle = cached;
     // SOR tiles: 8 rows per thread and 8-plane chunks for FP32 psi; FP64 psi
     // needs twice the registers per row, so 4 and 4 (measured best of each)
     L->sor_rows = L->precision == LBMEP_FP64 ? 4 : 8;
@@ -487,7 +501,7 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
         const int w = std::atoi(e);
         if (w >= 0 && w <= 32) L->sweep_wgcu = w;
     }
-    L->sweep_nt = 2;
+    L->sweep_nt = cached ? 0 : 2;
     if (const char *e = std::getenv("LBMEP_SWEEP_NT")) {
         const int v = std::atoi(e);
         if (v >= 0 && v <= 2) L->sweep_nt = v;

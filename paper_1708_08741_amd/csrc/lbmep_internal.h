@@ -253,6 +253,7 @@ struct LatticeDev {
 struct PackTable {
     int n;
     int xcd_swizzle;
+    int cached;  // the lattices stay in the Infinity Cache: no streaming hints
     uint32_t start[kMaxPack + 1];  // first workgroup of each entry; start[n] = total
     const LatticeDev *d[kMaxPack];
     uint32_t state[kMaxPack];      // cur + 2 cur_owner before the step

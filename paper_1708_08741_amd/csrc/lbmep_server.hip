@@ -428,6 +428,8 @@ void retire(lbmep_server *S, Slot &slot) {
 // enqueue `k` steps of every active slot as packed launches
 int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
     hipStream_t s = S->main;
+    size_t bytes = 0;
+    for (const Slot *sl : act) bytes += population_bytes(sl->L->g, sl->L->precision);
     for (int it = 0; it < k; ++it) {
         // sweep and exchange, one packed launch pair per (precision, force mode)
         for (int prec = LBMEP_FP64; prec <= LBMEP_FP16DEV; ++prec)
@@ -435,6 +437,7 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                 PackTable ts{}, tn{};
                 uint32_t lds = near_lds();
                 ts.xcd_swizzle = 1;
+                ts.cached = bytes < kInfinityCache;
                 auto flush = [&]() -> int {
                     if (ts.n == 0) return LBMEP_OK;
                     LBMEP_HIP_TRY(launch_sweep_packed(prec, fm, ts, s));

@@ -948,7 +948,8 @@ __device__ __forceinline__ LevelMap packed_args(const LevelMap *p) {
 }
 
 // the gather sweep of several lattices in one dispatch
-template <typename ST, int FMODE>
+// (MODE: kPullNTS, or kPull where the lattices fit in the Infinity Cache)
+template <typename ST, int FMODE, int MODE>
 __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
     const uint32_t gb = t.xcd_swizzle ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
     const int e = pack_find(t, gb);
@@ -963,8 +964,6 @@ __global__ void __launch_bounds__(kPackBlockX) k_sweep_packed(PackTable t) {
     }
     b -= map_blocks;
     const SweepArgs a = packed_args(&d->sweep[t.state[e]]);
-    // streaming hints as in the single-lattice default: stores only
-    constexpr int MODE = kPullNTS;
     sweep_segment<ST, FMODE, uint32_t, MODE>(a, b);
 }
 
@@ -972,14 +971,18 @@ template <typename ST>
 hipError_t launch_sweep_packed_typed(int force_mode, const PackTable &t, hipStream_t s) {
     const uint32_t total = t.start[t.n];
     if (t.n == 0 || total == 0) return hipSuccess;
-    if (force_mode == kForceNone)
-        hipLaunchKernelGGL((k_sweep_packed<ST, kForceNone>), dim3(total), dim3(kPackBlockX), 0, s, t);
-    else if (force_mode == kForceDense)
-        hipLaunchKernelGGL((k_sweep_packed<ST, kForceDense>), dim3(total), dim3(kPackBlockX), 0, s, t);
-    else if (force_mode == kForceCharge)
-        hipLaunchKernelGGL((k_sweep_packed<ST, kForceCharge>), dim3(total), dim3(kPackBlockX), 0, s, t);
-    else
-        return hipErrorInvalidValue;  // served requests carry no potential force
+#define LBMEP_PACKED(FM)                                                                         \
+    do {                                                                                         \
+        if (t.cached)                                                                            \
+            hipLaunchKernelGGL((k_sweep_packed<ST, FM, kPull>), dim3(total), dim3(kPackBlockX), 0, s, t); \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_sweep_packed<ST, FM, kPullNTS>), dim3(total), dim3(kPackBlockX), 0, s, t); \
+    } while (0)
+    if (force_mode == kForceNone) LBMEP_PACKED(kForceNone);
+    else if (force_mode == kForceDense) LBMEP_PACKED(kForceDense);
+    else if (force_mode == kForceCharge) LBMEP_PACKED(kForceCharge);
+    else return hipErrorInvalidValue;  // served requests carry no potential force
+#undef LBMEP_PACKED
     return hipGetLastError();
 }
 

@@ -54,3 +54,37 @@ def test_held_results_keep_their_fields(lb, budget_mb):
             srv.release(i)
             del held[i]
     srv.close()
+
+
+@pytest.mark.parametrize("prec", ["FP64", "FP32DEV"])
+def test_batch_larger_than_the_infinity_cache(lb, prec):
+    """Batches whose populations start above the cache's size and fall below
+    it as requests finish (FP64 64^3: 80 MB each): the sweep's streaming hints
+    change on the way, the results do not."""
+    precision = getattr(lb, prec)
+    edges = (64, 64, 60, 64, 62) if prec == "FP64" else (80, 84, 80, 82, 80)
+    srv = lb.Server(2 << 30, max_slots=8, chunk_steps=2)
+    rng = np.random.default_rng(4)
+    want = {}
+    for r, e in enumerate(edges):
+        shape, steps = (e, e - 6, e + 2), 3 + 2 * r
+        X = rng.random((3, 3)) * np.array(shape)
+        U = rng.uniform(-0.01, 0.01, (3, 3))
+        R = np.array([3.0, 4.0, 3.5])
+        i = srv.submit(shape, X=X, R=R, U=U, steps=steps, precision=precision, moving=True,
+                       keep_fields=True)
+        want[i] = (shape, X, R, U, steps)
+    srv.wait_all(list(want), sleep=0.0)
+    for i, (shape, X, R, U, steps) in want.items():
+        L = lb.Lattice(shape, precision=precision, move_particles=True)
+        L.set_particles(X, R, U)
+        L.step(steps)
+        rho, u = L.macro()
+        got = srv.fields(i)
+        assert (got[0] == rho).all() and (got[1] == u).all()
+        F, M = L.ft()
+        res = srv.result(i)
+        assert (res[0] == F).all() and (res[1] == M).all()
+        L.close()
+        srv.release(i)
+    srv.close()

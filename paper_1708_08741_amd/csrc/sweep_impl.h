@@ -375,90 +375,57 @@ __device__ __forceinline__ typename Storage<ST>::CT gather(const void *src, OFF 
 }
 
 // Free-slip faces: a population that a face cell x gathers from beyond a
-// free-slip face (direction q, source x - c_q outside along the axes of
-// mask) comes from the tangential neighbour s' (x - c_q with those
-// components set back to x's) in the direction p = q mirrored across the
-// crossed axes, unless s' is a wall or obstacle cell or a crossed face is
-// no-slip (then the half-way bounce-back stands).  Beyond a non-periodic
-// edge the gather reads slot q-bar of x itself, which no other gather reads;
-// slot p of s' is likewise read only through the reflection of (s', q2),
-// q2 = q-bar mirrored across the same axes, whose partner is (x, q).  So the
-// reflection is a swap of the two slots, made once per pair before a gather
-// of the state by a pass over the face cells; the gather itself keeps no
-// branch for it.
-template <int q, typename ST>
-__device__ __forceinline__ void slip_pair(const SweepArgs &a, const int (&o)[3], size_t c,
-                                          int ax, int side) {
-    constexpr int cq[3] = {kCx[q], kCy[q], kCz[q]};
-    // the pass of face (ax, side) takes the directions that cross it
-    if (cq[ax] == 0 || (side == 0) != (cq[ax] > 0)) return;
-    const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
-    int s[3] = {o[0] - cq[0], o[1] - cq[1], o[2] - cq[2]};
-    int mask = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if (s[k] >= 0 && s[k] < len[k]) continue;
-        if (a.g.per[k]) {
-            s[k] = s[k] < 0 ? s[k] + len[k] : s[k] - len[k];
-            continue;
-        }
-        if (!(a.slip & (1 << (2 * k + (s[k] < 0 ? 0 : 1))))) return;  // no-slip face
-        mask |= 1 << k;
-        s[k] = o[k];
-    }
-    // a pair that crosses an edge or corner is taken by its lowest axis
-    if (mask & ((1 << ax) - 1)) return;
-    int p = q, q2 = q;
-    switch (mask) {
-        case 1: p = mirror_dir(q, 1); q2 = mirror_dir(opp(q), 1); break;
-        case 2: p = mirror_dir(q, 2); q2 = mirror_dir(opp(q), 2); break;
-        case 3: p = mirror_dir(q, 3); q2 = mirror_dir(opp(q), 3); break;
-        case 4: p = mirror_dir(q, 4); q2 = mirror_dir(opp(q), 4); break;
-        case 5: p = mirror_dir(q, 5); q2 = mirror_dir(opp(q), 5); break;
-        case 6: p = mirror_dir(q, 6); q2 = mirror_dir(opp(q), 6); break;
-        default: p = mirror_dir(q, 7); q2 = mirror_dir(opp(q), 7); break;
-    }
-    const size_t sc = (size_t)s[0] + (size_t)a.g.nx * ((size_t)s[1] + (size_t)a.g.ny * (size_t)s[2]);
-    // normal incidence (s' = x, p = q-bar): the bounce-back is the reflection;
-    // otherwise the pair is swapped by its smaller (cell, direction)
-    if (sc * Q + (size_t)q2 <= c * Q + (size_t)q) return;
-    if ((a.flag[c] | a.flag[sc]) & (kWall | kObst)) return;
-    ST *f = static_cast<ST *>(const_cast<void *>(a.src));
-    ST *u = f + (size_t)opp(q) * a.g.Ns + c;
-    ST *v = f + (size_t)p * a.g.Ns + sc;
-    const ST t = *u;
-    *u = *v;
-    *v = t;
+// free-slip face (direction q, source x - c_q outside along axis a) comes from
+// the tangential neighbour s' (x - c_q with that component set back to x's) in
+// the direction p = q mirrored across the face, unless s' is a wall or
+// obstacle cell (then the half-way bounce-back stands).  Along the normal, and
+// where a diagonal crosses two faces at an edge, the reflection is the
+// bounce-back that the gather has already taken.  So each face has four
+// directions to take again, on the lanes at it: their slots lie in lines that
+// the wavefront's gather reads anyway.  (A pass that swapped the slots of the
+// pairs of such populations before every gather took 39 us beside a sweep of
+// 375 us at 216 x 312 x 216 FP32, most of it on the x faces, a line per cell;
+// 20 steps and a read-out there 9.72 -> 9.30 ms.)
+template <int q, int ax, typename ST, typename OFF, int MODE>
+__device__ __forceinline__ void slip_direction(const SweepArgs &a, const Sources<OFF> &n,
+                                               typename Storage<ST>::CT &v) {
+    constexpr int c[3] = {kCx[q], kCy[q], kCz[q]};
+    constexpr int b = ax == 0 ? (c[1] != 0 ? 1 : 2) : ax == 1 ? (c[0] != 0 ? 0 : 2) : (c[0] != 0 ? 0 : 1);
+    static_assert(c[ax] != 0 && c[b] != 0, "a diagonal");
+    constexpr int p = mirror_dir(q, 1 << ax);
+    if (!n.in[b][c[b] + 1]) return;  // an edge of two faces
+    const OFF o = n.cb + n.d[b][c[b] + 1];
+    const char *base = static_cast<const char *>(a.src) + (size_t)p * a.g.Ns * sizeof(ST);
+    const uint8_t fs = a.flag[o / (OFF)sizeof(ST)];
+    const typename Storage<ST>::CT t = pop_load<MODE, ST>(at<ST>(static_cast<const void *>(base), o));
+    if (!(fs & (kWall | kObst))) v = t;
 }
 
-// one thread per cell of every free-slip face, the faces one after the other
-// (each slot belongs to one pair, so the faces need no order among them); one
-// launch instead of one per face: 6 x 10.7 us at 216 x 312 x 216
-template <typename ST>
-__global__ void __launch_bounds__(256) k_slip_swap(SweepArgs a) {
-    const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int face = -1;
-    for (int f = 0; f < 6; ++f) {
-        if (!(a.slip & (1 << f))) continue;
-        const size_t cells = (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
-        if (i < cells) {
-            face = f;
-            break;
-        }
-        i -= cells;
+template <typename ST, typename OFF, int MODE>
+__device__ __forceinline__ void slip_faces(const SweepArgs &a, const Sources<OFF> &n,
+                                           typename Storage<ST>::CT (&v)[Q]) {
+    // directions that come from beyond the low face of an axis have a
+    // positive component along it, those from beyond the high face a negative
+#define LBMEP_FACE(ax, side, q0, q1, q2, q3)                                       \
+    if ((a.slip & (1 << (2 * ax + side))) && !n.in[ax][side ? 0 : 2]) {            \
+        slip_direction<q0, ax, ST, OFF, MODE>(a, n, v[q0]);                        \
+        slip_direction<q1, ax, ST, OFF, MODE>(a, n, v[q1]);                        \
+        slip_direction<q2, ax, ST, OFF, MODE>(a, n, v[q2]);                        \
+        slip_direction<q3, ax, ST, OFF, MODE>(a, n, v[q3]);                        \
     }
-    if (face < 0) return;
-    const int ax = face / 2, side = face & 1;
-    const int a1 = ax == 0 ? 1 : 0, a2 = ax == 2 ? 1 : 2;
-    int o[3];
-    o[ax] = side ? len[ax] - 1 : 0;
-    o[a1] = (int)(i % (size_t)len[a1]);
-    o[a2] = (int)(i / (size_t)len[a1]);
-    const size_t c = (size_t)o[0] + (size_t)a.g.nx * ((size_t)o[1] + (size_t)a.g.ny * (size_t)o[2]);
-#define LBMEP_SLIP(q) slip_pair<q, ST>(a, o, c, ax, side);
-    LBMEP_FOR_Q18(LBMEP_SLIP)
-#undef LBMEP_SLIP
+    LBMEP_FACE(0, 0, 7, 9, 11, 13)
+    LBMEP_FACE(0, 1, 8, 10, 12, 14)
+    LBMEP_FACE(1, 0, 7, 10, 15, 17)
+    LBMEP_FACE(1, 1, 8, 9, 16, 18)
+    LBMEP_FACE(2, 0, 11, 14, 15, 18)
+    LBMEP_FACE(2, 1, 12, 13, 16, 17)
+#undef LBMEP_FACE
+    static_assert(kCx[7] == 1 && kCx[9] == 1 && kCx[11] == 1 && kCx[13] == 1, "low x face");
+    static_assert(kCx[8] == -1 && kCx[10] == -1 && kCx[12] == -1 && kCx[14] == -1, "high x face");
+    static_assert(kCy[7] == 1 && kCy[10] == 1 && kCy[15] == 1 && kCy[17] == 1, "low y face");
+    static_assert(kCy[8] == -1 && kCy[9] == -1 && kCy[16] == -1 && kCy[18] == -1, "high y face");
+    static_assert(kCz[11] == 1 && kCz[14] == 1 && kCz[15] == 1 && kCz[18] == 1, "low z face");
+    static_assert(kCz[12] == -1 && kCz[13] == -1 && kCz[16] == -1 && kCz[17] == -1, "high z face");
 }
 
 // store population q of a cell at byte offset cb; addressed from the base of
@@ -510,6 +477,7 @@ __device__ __forceinline__ void load_cell(const SweepArgs &a, int x, int y, int 
 #define LBMEP_GATHER(q) c.v[q] = gather<q, ST, OFF, MODE>(a.src, pst, cb, n);
         LBMEP_FOR_Q18(LBMEP_GATHER)
 #undef LBMEP_GATHER
+        if (a.slip && valid && !(fl & (kWall | kObst))) slip_faces<ST, OFF, MODE>(a, n, c.v);
     }
     c.fb0 = c.fb1 = c.fb2 = CT(0);
     if constexpr (MODE != kReadout) {
@@ -848,17 +816,6 @@ __global__ void __launch_bounds__(256) k_macro(SweepArgs a, int force_mode, doub
     for (int k = 0; k < 3; ++k) __builtin_nontemporal_store(v[k], u + (size_t)k * N + i);
 }
 
-template <typename ST>
-void launch_slip_swap(const SweepArgs &a, hipStream_t s) {
-    const int len[3] = {a.g.nx, a.g.ny, a.g.nz};
-    size_t cells = 0;
-    for (int f = 0; f < 6; ++f)
-        if (a.slip & (1 << f))
-            cells += (size_t)len[f / 2 == 0 ? 1 : 0] * (size_t)len[f / 2 == 2 ? 1 : 2];
-    if (cells)
-        hipLaunchKernelGGL((k_slip_swap<ST>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, a);
-}
-
 // 32-bit byte offsets when two population arrays fit in 4 GiB (the gather
 // addresses an opposite pair from one base)
 template <typename ST>
@@ -872,9 +829,6 @@ template <typename ST>
 hipError_t launch_macro_typed(int force_mode, const SweepArgs &a, bool pull, double *rho, double *u,
                               hipStream_t s) {
     const dim3 grid((unsigned)((a.g.N + 255) / 256)), block(256);
-    // the reflection of free-slip faces is a swap of slots, so a second one
-    // after the gather restores the state
-    if (pull) launch_slip_swap<ST>(a, s);
 #define LBMEP_MACRO(OFF, MD) \
     hipLaunchKernelGGL((k_macro<ST, OFF, MD>), grid, block, 0, s, a, force_mode, rho, u)
     if (small_grid<ST>(a.g)) {
@@ -885,7 +839,6 @@ hipError_t launch_macro_typed(int force_mode, const SweepArgs &a, bool pull, dou
         else LBMEP_MACRO(uint64_t, kLocal);
     }
 #undef LBMEP_MACRO
-    if (pull) launch_slip_swap<ST>(a, s);
     return hipGetLastError();
 }
 
@@ -991,9 +944,6 @@ template <typename ST>
 hipError_t launch_typed(int mode, int force_mode, SweepArgs a, int block_x,
                         const MapSetArgs *map, hipStream_t s) {
     const bool small = small_grid<ST>(a.g);
-    // free-slip faces: the reflected values into the slots the gather reads
-    // beyond those faces
-    if (mode != kLocal) launch_slip_swap<ST>(a, s);
     // the workgroups-per-CU cap was measured on the 32-bit-offset kernel;
     // the 64-bit one runs faster without it (864 x 1248 x 864 FP32: 24.6
     // against 27.5 ms)

@@ -273,7 +273,7 @@ __device__ __forceinline__ int pack_find(const PackTable &t, uint32_t b) {
     return lo;
 }
 
-// launch shape of the packed sweep (x-segments of 128 cells, one cell per thread)
+// launch shape of the packed sweep (segments of 128 cells)
 constexpr int kPackBlockX = 128;
 
 // kernels (host-side launchers); each returns hipError_t of the launch

@@ -213,14 +213,17 @@ int lbmep_set_free_slip(lbmep_lattice *L, const int32_t faces[6]);
  * (bounce-back, exchange, refill).  q: L's particle count of charges (host;
  * NULL: uncharged); E: the applied field for q E.  Needs move_particles = 1;
  * dropped by the next lbmep_set_particles.  A particle must stay below one
- * cell per step (lbmep_get_particles reports it).  Errors: EINVAL (null E,
- * not moving, rho_p <= 0, non-finite values), ENOMEM. */
+ * cell per step (lbmep_get_particles reports it; a velocity component that
+ * does not stay below no longer moves the particle, so the map stays valid
+ * and further calls run, but the motion is not the body's any more).
+ * Errors: EINVAL (null E, not moving, rho_p <= 0, non-finite values),
+ * ENOMEM. */
 int lbmep_set_dynamics(lbmep_lattice *L, double rho_p, const double *q, const double E[3]);
 
 /* Current positions, velocities and angular velocities of the particles
  * (host arrays of 3 n doubles each; synchronises).  Errors: EINVAL (null
  * with n > 0; a velocity component reached one cell per step under
- * dynamics, i.e. the mapping no longer follows the body), EDEVICE. */
+ * dynamics, i.e. the position no longer follows the velocity), EDEVICE. */
 int lbmep_get_particles(lbmep_lattice *L, double *X, double *U, double *W);
 
 /* Set every population to the incompressible equilibrium f^eq(rho, u)

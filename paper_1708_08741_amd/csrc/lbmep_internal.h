@@ -197,7 +197,7 @@ constexpr int kMaxPack = 64;
 
 // Newton-Euler update of every particle from the step's accumulators: U, W
 // in place, X0 = the next level's positions; *too_fast = 1 when a velocity
-// component reaches one cell per step
+// component reaches one cell per step (it does not move the particle)
 struct DynArgs {
     const double *q;     // charges or null
     double *U, *W, *X0;

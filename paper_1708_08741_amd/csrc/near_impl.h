@@ -255,7 +255,11 @@ __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint3
 // applied field move the particle), one explicit step, velocities first:
 //     U += (F_h + q E) / m,  W += M_h / I,  X(n+1) = X(n) + U,
 // m = rho_p 4/3 pi R^3, I = 2/5 m R^2; F_h, M_h assembled from the 12 sums t
-// as k_finalize_ft does, in the same order; one component per thread
+// as k_finalize_ft does, in the same order; one component per thread.  A
+// component of one cell per step or more (an infinity and a NaN too) is
+// reported and leaves the position as it is: the flags of a step are renewed
+// around the positions of two levels, so after a longer way marks of the level
+// before would stay whose owners the maps do not hold any more.
 __device__ __forceinline__ void move_particle(const ParticleArgs &pa, const DynArgs &d, uint32_t p,
                                               const double *t, const double *Xp) {
     if (threadIdx.x >= 3) return;
@@ -271,13 +275,14 @@ __device__ __forceinline__ void move_particle(const ParticleArgs &pa, const DynA
     const double u = d.U[i] + (F + qp * d.E[k]) / m;
     d.U[i] = u;
     d.W[i] = d.W[i] + M / I;
-    double x = Xp[k] + u;
+    const bool fast = !(fabs(u) < 1.0);
+    double x = fast ? Xp[k] : Xp[k] + u;
     if (pa.g.per[k]) {
         x = x - (double)len * floor(x / (double)len);
         if (x >= (double)len) x -= (double)len;
     }
     d.X0[i] = x;
-    if (!(fabs(u) < 1.0)) *d.too_fast = 1;
+    if (fast) *d.too_fast = 1;
 }
 
 // Links to wall cells (a list fixed while the walls are): plain bounce-back

@@ -21,13 +21,15 @@ __global__ void k_positions(ParticleArgs pa, int64_t level, double *X) {
 
 // map every particle at `level` (into an emptied map)
 __global__ void __launch_bounds__(kBoxThreads) k_map_set(ParticleArgs pa, int64_t level, LevelMap m) {
-    advance_set(pa, blockIdx.x, level, m, (int)threadIdx.x, (int)blockDim.x);
+    const uint32_t p = row_block();
+    if (p < (uint32_t)pa.np) advance_set(pa, (int)p, level, m, (int)threadIdx.x, (int)blockDim.x);
 }
 
 __global__ void __launch_bounds__(kPartThreads)
     k_classify_boxes(ParticleArgs pa, LevelMap old, LevelMap now) {
     extern __shared__ __align__(16) unsigned char part_lds[];
-    classify(pa, blockIdx.x, old, now, box_rows(part_lds, pa.box_rows));
+    const uint32_t p = row_block();
+    if (p < (uint32_t)pa.np) classify(pa, (int)p, old, now, box_rows(part_lds, pa.box_rows));
 }
 
 // wall cells as one bit per cell; one word per thread
@@ -217,7 +219,7 @@ hipError_t launch_positions(const ParticleArgs &pa, int64_t level, double *X, hi
 
 hipError_t launch_map_set(const ParticleArgs &pa, int64_t level, const LevelMap &m, hipStream_t s) {
     if (pa.np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_map_set, dim3(pa.np), dim3(kBoxThreads), 0, s, pa, level, m);
+    hipLaunchKernelGGL(k_map_set, row_grid((size_t)pa.np), dim3(kBoxThreads), 0, s, pa, level, m);
     return hipGetLastError();
 }
 
@@ -238,7 +240,7 @@ hipError_t launch_classify_all(const Grid &g, uint8_t *flag, uint32_t *wallmask,
 hipError_t launch_classify_boxes(const ParticleArgs &pa, const LevelMap &old, const LevelMap &now,
                                  hipStream_t s) {
     if (pa.np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_classify_boxes, dim3(pa.np), dim3(kPartThreads), classify_lds(pa.box_rows), s,
+    hipLaunchKernelGGL(k_classify_boxes, row_grid((size_t)pa.np), dim3(kPartThreads), classify_lds(pa.box_rows), s,
                        pa, old, now);
     return hipGetLastError();
 }

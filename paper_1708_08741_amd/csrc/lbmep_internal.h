@@ -92,6 +92,17 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t lb, uint32_t nblk) {
     return (xcd < rem ? xcd * (per + 1u) : rem * (per + 1u) + (xcd - rem) * per) + slot;
 }
 
+// A launch of one workgroup per particle (or several) can have more workgroups
+// than a grid's x extent takes: it counts threads in 32 bits, 8.4 million
+// workgroups of 512.  They are laid out in rows of kGridRow; the last row may
+// hold more than n.
+constexpr uint32_t kGridRow = 1u << 22;
+inline dim3 row_grid(size_t n) {
+    const size_t x = n < kGridRow ? n : kGridRow;
+    return dim3((unsigned)x, (unsigned)((n + x - 1) / x), 1);
+}
+__device__ __forceinline__ uint32_t row_block() { return blockIdx.x + blockIdx.y * kGridRow; }
+
 // arguments of the fused stream-collide sweep
 // constants of the FP32-compute TRT collision (FP32 and FP16 storage), set
 // on the host from lambda_e, lambda_o and the compute unit kC of the storage
@@ -219,6 +230,7 @@ enum PartsMode {
 struct PartsArgs {
     int mode;
     int wall_blocks;      // workgroups of the wall links
+    uint32_t blocks;      // workgroups of the launch
     ParticleArgs pa;      // with the link lists of the next level
     LevelMap old, cur, next;
     int64_t level;        // the next level

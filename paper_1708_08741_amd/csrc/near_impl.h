@@ -364,13 +364,16 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
 
 template <typename ST, typename OFF>
 __global__ void __launch_bounds__(kPartThreads, 4) k_parts(SweepArgs a, PartsArgs q) {
-    parts_block<ST, OFF, true>(a, q, blockIdx.x);
+    const uint32_t blk = row_block();
+    if (blk < q.blocks) parts_block<ST, OFF, true>(a, q, blk);
 }
 
 // one workgroup per particle for several lattices in one dispatch
 template <typename ST>
 __global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
-    const int e = pack_find(t, blockIdx.x);
+    const uint32_t gb = row_block();
+    if (gb >= t.start[t.n]) return;
+    const int e = pack_find(t, gb);
     const LatticeDev *d = t.d[e];
     const uint32_t st = t.state[e];
     const SweepArgs a = packed_args(&d->sweep[st]);
@@ -388,7 +391,7 @@ __global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
     q.cur = packed_args(&d->map[c]);
     q.next = packed_args(&d->map[c == 2 ? 0 : c + 1]);
     q.level = t.level[e];
-    parts_block<ST, uint32_t, false>(a, q, blockIdx.x - t.start[e]);
+    parts_block<ST, uint32_t, false>(a, q, gb - t.start[e]);
 }
 
 // workgroups of the wall pass (0 without wall cells)
@@ -404,20 +407,21 @@ template <typename ST>
 hipError_t launch_parts_packed_typed(const PackTable &t, uint32_t lds, hipStream_t s) {
     const uint32_t total = t.start[t.n];
     if (t.n == 0 || total == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_parts_packed<ST>), dim3(total), dim3(kPartThreads), lds, s, t);
+    hipLaunchKernelGGL((k_parts_packed<ST>), row_grid(total), dim3(kPartThreads), lds, s, t);
     return hipGetLastError();
 }
 
 template <typename ST>
-hipError_t launch_parts_typed(const SweepArgs &a, const PartsArgs &q, hipStream_t s) {
-    const unsigned blocks = (unsigned)a.np * (q.mode == kPartsSplit ? 3u : 1u) + (unsigned)q.wall_blocks;
-    if (blocks == 0) return hipSuccess;
+hipError_t launch_parts_typed(const SweepArgs &a, PartsArgs q, hipStream_t s) {
+    q.blocks = (uint32_t)a.np * (q.mode == kPartsSplit ? 3u : 1u) + (uint32_t)q.wall_blocks;
+    if (q.blocks == 0) return hipSuccess;
+    const dim3 grid = row_grid(q.blocks);
     const uint32_t lds = parts_lds(q.mode, q.pa.box_rows);
     const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);
     if (small)
-        hipLaunchKernelGGL((k_parts<ST, uint32_t>), dim3(blocks), dim3(kPartThreads), lds, s, a, q);
+        hipLaunchKernelGGL((k_parts<ST, uint32_t>), grid, dim3(kPartThreads), lds, s, a, q);
     else
-        hipLaunchKernelGGL((k_parts<ST, uint64_t>), dim3(blocks), dim3(kPartThreads), lds, s, a, q);
+        hipLaunchKernelGGL((k_parts<ST, uint64_t>), grid, dim3(kPartThreads), lds, s, a, q);
     return hipGetLastError();
 }
 

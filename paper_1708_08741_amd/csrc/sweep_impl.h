@@ -377,8 +377,11 @@ __device__ __forceinline__ typename Storage<ST>::CT gather(const void *src, OFF 
 // Free-slip faces: a population that a face cell x gathers from beyond a
 // free-slip face (direction q, source x - c_q outside along axis a) comes from
 // the tangential neighbour s' (x - c_q with that component set back to x's) in
-// the direction p = q mirrored across the face, unless s' is a wall or
-// obstacle cell (then the half-way bounce-back stands).  Along the normal, and
+// the direction p = q mirrored across the face, unless s' was a wall or
+// obstacle cell when the populations streamed (then the half-way bounce-back
+// stands): the map of the level before decides, not that of the level they are
+// gathered for, at which a sphere cut by the face may have moved on.  Along
+// the normal, and
 // where a diagonal crosses two faces at an edge, the reflection is the
 // bounce-back that the gather has already taken.  So each face has four
 // directions to take again, on the lanes at it: their slots lie in lines that
@@ -398,7 +401,11 @@ __device__ __forceinline__ void slip_direction(const SweepArgs &a, const Sources
     const char *base = static_cast<const char *>(a.src) + (size_t)p * a.g.Ns * sizeof(ST);
     const uint8_t fs = a.flag[o / (OFF)sizeof(ST)];
     const typename Storage<ST>::CT t = pop_load<MODE, ST>(at<ST>(static_cast<const void *>(base), o));
-    if (!(fs & (kWall | kObst))) v = t;
+    // kUncov: an obstacle cell of the level before; kObst: of this level, and of
+    // that one if it had an owner there (a fixed map is both levels' map)
+    bool fluid = !(fs & (kWall | kUncov));
+    if (fluid && (fs & kObst)) fluid = a.owner_old[o / (OFF)sizeof(ST)] == kNone;
+    if (fluid) v = t;
 }
 
 template <typename ST, typename OFF, int MODE>
@@ -661,8 +668,8 @@ __device__ __forceinline__ void finish_cell(const SweepArgs &a, int x, int y, in
         }
 
         // Aligned store of the post-collision state, also to the obstacle
-        // cells beside fluid ones: nothing reads there but the slots that the
-        // exchange writes after the sweep, and whole lines cost less than
+        // cells beside fluid ones: the next gather reads there only the slots
+        // that the exchange writes after the sweep, and whole lines cost less than
         // lines with holes (4096 spheres of radius 4, with the holes and
         // without: 512^3 FP32 3730 -> 3500 us, 512 x 384 x 320 FP16 1083 ->
         // 1001, 300 x 256^2 FP64 1230 -> 1126).  The slots of wall cells,

@@ -63,13 +63,15 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t mine, uint32_t *wsum, ui
 }
 
 // the whole grid (after the flags or the particle table changed): flags and
-// the wall-link masks of every cell
+// the wall-link masks of every cell.  An obstacle cell's wall links are listed
+// too: the slot of a wall cell is read by the cell it was bounced from alone,
+// so they do no harm until a sphere uncovers the cell.
 __global__ void k_classify_all(Grid g, uint8_t *flag, uint32_t *wallmask, const uint32_t *owner) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= g.nx) return;
     const int y = blockIdx.y, z = blockIdx.z;
     uint32_t wm, pm;
-    const uint8_t f = classify_cell(g, x, y, z, flag, owner, nullptr, kNone, &wm, &pm);
+    const uint8_t f = classify_cell<true>(g, x, y, z, flag, owner, nullptr, kNone, &wm, &pm);
     const size_t c = cell_of(g, x, y, z);
     flag[c] = f;
     wallmask[c] = wm;

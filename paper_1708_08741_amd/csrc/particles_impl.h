@@ -255,45 +255,49 @@ __device__ __forceinline__ void advance_set(const ParticleArgs &pa, int p, int64
 // one cell's classification from the wall bits and the map (global reads):
 // its flag; *wmask = directions whose neighbour is a wall cell; *pmask =
 // directions whose neighbour is an obstacle cell of particle p (p != kNone);
-// with owner_old, a fluid cell that was an obstacle cell is marked uncovered
+// with owner_old, a fluid cell that was an obstacle cell is marked uncovered.
+// WALLS: the wall directions of obstacle cells as well (a sphere may uncover
+// them while the walls are as they are)
+template <bool WALLS>
 __device__ __forceinline__ uint8_t classify_cell(const Grid &g, int x, int y, int z,
                                                  const uint8_t *flag, const uint32_t *owner,
                                                  const uint32_t *owner_old, uint32_t p,
                                                  uint32_t *wmask, uint32_t *pmask) {
     const size_t c = cell_of(g, x, y, z);
     const uint8_t wall = flag[c] & kWall;
+    const bool obst = !wall && owner && owner[c] != kNone;
     uint8_t f = wall;
     uint32_t mask = 0, wm = 0, pm = 0;
-    if (!wall) {
-        if (owner && owner[c] != kNone) {
-            f = kObst;
-        } else {
+    if (!wall && (WALLS || !obst)) {
 #pragma unroll
-            for (int q = 1; q < Q; ++q) {
-                int sx = x + kCx[q], sy = y + kCy[q], sz = z + kCz[q];
-                bool solid = false;
-                if (sx < 0 || sx >= g.nx) {
-                    if (g.per[0]) sx = sx < 0 ? sx + g.nx : sx - g.nx; else solid = true;
-                }
-                if (sy < 0 || sy >= g.ny) {
-                    if (g.per[1]) sy = sy < 0 ? sy + g.ny : sy - g.ny; else solid = true;
-                }
-                if (sz < 0 || sz >= g.nz) {
-                    if (g.per[2]) sz = sz < 0 ? sz + g.nz : sz - g.nz; else solid = true;
-                }
-                if (!solid) {
-                    const size_t s = cell_of(g, sx, sy, sz);
-                    const bool w = flag[s] & kWall;
-                    const uint32_t o = owner ? owner[s] : kNone;
-                    solid = w || o != kNone;
-                    if (w) wm |= 1u << (q - 1);
-                    if (!w && o != kNone && o == p) pm |= 1u << (q - 1);
-                }
-                if (solid) mask |= 1u << (q - 1);
+        for (int q = 1; q < Q; ++q) {
+            int sx = x + kCx[q], sy = y + kCy[q], sz = z + kCz[q];
+            bool solid = false;
+            if (sx < 0 || sx >= g.nx) {
+                if (g.per[0]) sx = sx < 0 ? sx + g.nx : sx - g.nx; else solid = true;
             }
-            f = (mask ? kNear : 0) | ((mask & kFaceDirs) ? kNear7 : 0);
-            if (owner_old && owner_old[c] != kNone) f |= kUncov;
+            if (sy < 0 || sy >= g.ny) {
+                if (g.per[1]) sy = sy < 0 ? sy + g.ny : sy - g.ny; else solid = true;
+            }
+            if (sz < 0 || sz >= g.nz) {
+                if (g.per[2]) sz = sz < 0 ? sz + g.nz : sz - g.nz; else solid = true;
+            }
+            if (!solid) {
+                const size_t s = cell_of(g, sx, sy, sz);
+                const bool w = flag[s] & kWall;
+                const uint32_t o = owner ? owner[s] : kNone;
+                solid = w || o != kNone;
+                if (w) wm |= 1u << (q - 1);
+                if (!w && o != kNone && o == p) pm |= 1u << (q - 1);
+            }
+            if (solid) mask |= 1u << (q - 1);
         }
+        f = (mask ? kNear : 0) | ((mask & kFaceDirs) ? kNear7 : 0);
+        if (owner_old && owner_old[c] != kNone) f |= kUncov;
+    }
+    if (obst) {
+        f = kObst;
+        pm = 0;
     }
     *wmask = wm;
     *pmask = pm;
@@ -560,7 +564,7 @@ __device__ __forceinline__ void classify(const ParticleArgs &pa, int p, const Le
                 box_cell(g, b, i, x, y, z);
                 c = cell_of(g, x, y, z);
                 uint32_t wm;
-                uint8_t f = classify_cell(g, x, y, z, pa.flag, now.owner, old.owner, (uint32_t)p, &wm, &pm);
+                uint8_t f = classify_cell<false>(g, x, y, z, pa.flag, now.owner, old.owner, (uint32_t)p, &wm, &pm);
                 pa.flag[c] = f;
             }
             uint32_t total;

@@ -22,8 +22,9 @@
 // its constant right-hand side (the Dirichlet faces' 2 b) and its diagonal.
 // Every neighbour then enters the sum as its stored value -- a wall or
 // obstacle cell as an exact 0, as does a neighbour beyond a non-periodic
-// edge -- and one formula serves every cell; a solid cell's reciprocal
-// diagonal of 0 keeps it at 0.
+// edge -- and one formula serves every cell; a solid cell's result is set to
+// 0 whatever its neighbours hold (0 times an infinity or a NaN would not be 0,
+// and would reach the other side of the wall).
 //
 // What bounds it: the vector unit (about 265 vector instructions per
 // wavefront and step of 64 V entries in each of four stages, 0.48 of the
@@ -365,14 +366,18 @@ __global__ void __launch_bounds__(64 * kTileWaves)
                             nw.v[v] = om1 * old.v[v] + om * quot_const(s.v[v], diag0, rd0);
                     } else if constexpr (sizeof(CT) == 4) {
 #pragma unroll
-                        for (int v = 0; v < V; ++v)
-                            nw.v[v] = om1 * old.v[v] + om * ((co[j].rhs.v[v] + s.v[v]) *
-                                                                rd[(co[j].code >> (8 * v)) & 15u]);
+                        for (int v = 0; v < V; ++v) {
+                            const uint32_t k = (co[j].code >> (8 * v)) & 15u;
+                            const float r = om1 * old.v[v] + om * ((co[j].rhs.v[v] + s.v[v]) * rd[k]);
+                            nw.v[v] = k == kTileSolid ? 0.0f : r;
+                        }
                     } else {
 #pragma unroll
-                        for (int v = 0; v < V; ++v)
-                            nw.v[v] = om1 * old.v[v] +
-                                         om * ((co[j].rhs.v[v] + s.v[v]) / co[j].diag.v[v]);
+                        for (int v = 0; v < V; ++v) {
+                            const double d = co[j].diag.v[v];  // a solid cell's is infinite
+                            const double r = om1 * old.v[v] + om * ((co[j].rhs.v[v] + s.v[v]) / d);
+                            nw.v[v] = d > 0x1p1000 ? 0.0 : r;
+                        }
                     }
                     if (j + 1 < S) {
                         G[j + 1 < S ? j + 1 : j][ic] = nw;

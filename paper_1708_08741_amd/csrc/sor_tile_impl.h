@@ -48,6 +48,7 @@
 #include <climits>
 #include <type_traits>
 
+#include "device_table.h"
 #include "lbmep_internal.h"
 
 namespace lbmep {
@@ -639,9 +640,11 @@ void launch_tile(const SorArgs &a, const TileShape &t, const CT *src, CT *dst, h
         return 2u * 2u * K * (uint32_t)((kTileSlots / nwx + 2) * nwx) * 64u * V * (uint32_t)sizeof(CT);
     };
     // places of workgroups on the device by wavefronts per row (1, 2, 4)
-    static const std::array<int, 3> places = [&] {
-        int dev = 0, cu = 256;
-        hipGetDevice(&dev);
+    static DeviceTable<std::array<int, 3>> table;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    const std::array<int, 3> places = table.get(dev, [&] {
+        int cu = 256;
         hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
         hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sor_tile<CT, V, K>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of(K == 2 ? 1 : 4));
@@ -655,7 +658,7 @@ void launch_tile(const SorArgs &a, const TileShape &t, const CT *src, CT *dst, h
         }
         (void)hipGetLastError();
         return r;
-    }();
+    });
     const uint32_t lds = lds_of(t.nwx);
     const int resident = places[t.nwx == 4 ? 2 : t.nwx - 1];
     const Grid &g = a.g;

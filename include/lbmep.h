@@ -297,7 +297,11 @@ int lbmep_get_particle_count(const lbmep_lattice *L, int32_t *n);
 /* Device bytes held by a lattice of this configuration with n particles of
  * radius at most r_max and a charge force or none (used for admission by
  * footprint).  With moving particles this includes the next level's link
- * lists of the overlapped step, n (8 (2 ceil(r_max) + 3)^3 + 4).  Not
+ * lists of the overlapped step, n (8 (2 ceil(r_max) + 3)^3 + 4), with
+ * particles the next level's map, 4 N + 24 n (counted for fixed ones too,
+ * which do without), and N / 2 bytes of bitmaps.  Where the device has no room
+ * for these, lbmep_set_particles takes a form without them, whose steps take
+ * more launches and more time for the particles; the results are the same.  Not
  * counted: a potential solver (lbmep_set_potential_solver adds about 23 N
  * bytes with FP32 psi, 39 N with FP64 psi: boundary lists and their rows,
  * interior bitmaps, and for the one-pass iteration (even nx) a second psi
@@ -396,7 +400,10 @@ int lbmep_server_create(const lbmep_server_config *cfg, lbmep_server **out);
  * queued or resident).  NULL is OK. */
 int lbmep_server_destroy(lbmep_server *srv);
 
-/* Device bytes a request holds while resident (its admission footprint). */
+/* Device bytes a request holds while resident (its admission footprint).  A
+ * request whose footprint exceeds the budget is still accepted if it fits
+ * without what lbmep_footprint names as dispensable; it is then stepped by
+ * launches of its own. */
 int lbmep_server_request_footprint(const lbmep_request *req, size_t *bytes);
 
 /* Queue a request; every input array is copied before the call returns.

@@ -20,9 +20,18 @@ __global__ void k_positions(ParticleArgs pa, int64_t level, double *X) {
 }
 
 // map every particle at `level` (into an emptied map)
+template <bool BITS>
 __global__ void __launch_bounds__(kBoxThreads) k_map_set(ParticleArgs pa, int64_t level, LevelMap m) {
     const uint32_t p = row_block();
-    if (p < (uint32_t)pa.np) advance_set(pa, (int)p, level, m, (int)threadIdx.x, (int)blockDim.x);
+    if (p < (uint32_t)pa.np)
+        advance_set<BITS>(pa, (int)p, level, m, (int)threadIdx.x, (int)blockDim.x);
+}
+
+// the previous level's cells leave a map without bitmaps (with them the step's
+// own launches do it)
+__global__ void __launch_bounds__(kBoxThreads) k_map_clear(ParticleArgs pa, LevelMap m) {
+    const uint32_t p = row_block();
+    if (p < (uint32_t)pa.np) map_clear<false>(pa, (int)p, m);
 }
 
 __global__ void __launch_bounds__(kPartThreads)
@@ -221,7 +230,17 @@ hipError_t launch_positions(const ParticleArgs &pa, int64_t level, double *X, hi
 
 hipError_t launch_map_set(const ParticleArgs &pa, int64_t level, const LevelMap &m, hipStream_t s) {
     if (pa.np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_map_set, row_grid((size_t)pa.np), dim3(kBoxThreads), 0, s, pa, level, m);
+    const dim3 grid = row_grid((size_t)pa.np), block(kBoxThreads);
+    if (m.bits)
+        hipLaunchKernelGGL(k_map_set<true>, grid, block, 0, s, pa, level, m);
+    else
+        hipLaunchKernelGGL(k_map_set<false>, grid, block, 0, s, pa, level, m);
+    return hipGetLastError();
+}
+
+hipError_t launch_map_clear(const ParticleArgs &pa, const LevelMap &m, hipStream_t s) {
+    if (pa.np == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_map_clear, row_grid((size_t)pa.np), dim3(kBoxThreads), 0, s, pa, m);
     return hipGetLastError();
 }
 

@@ -50,8 +50,13 @@ struct lbmep_lattice {
     // maps of the previous, the current and (moving particles) the next level
     // by turns: map[cur_owner] is the current level's, the one before it
     // (old_map) the previous level's, the one after it (next_map) empty until
-    // the next level is mapped.  A fixed map needs two.
+    // the next level is mapped.  A fixed map needs two (0 and 2).
     lbmep::LevelMap map[3] = {};
+    // two maps (0 and 2 by turns), no bitmaps and one set of link lists: for
+    // lattices that the memory has no room for otherwise.  A step empties the
+    // previous level's map, maps and classifies the next level in launches of
+    // their own.
+    bool tight = false;
     uint32_t *wallbits = nullptr;     // wall cells, one bit per cell
     int cur_owner = 0;
     int ft_buf = 0;  // map of the last streamed time level
@@ -142,9 +147,13 @@ size_t compute_bytes(int precision);
 bool finite_all(const double *p, size_t n);
 bool finite_all(const float *p, size_t n);
 int check_config(const lbmep_config *cfg);
-// device bytes of a lattice (what lbmep_footprint reports)
+// device bytes of a lattice (what lbmep_footprint reports); tight: in the
+// form of lbmep_lattice::tight
 size_t lattice_bytes(const lbmep_config *cfg, int32_t n_particles, double r_max,
-                     int force_mode, bool overlap);
+                     int force_mode, bool tight);
+
+// the tight form, of a lattice without particles
+void make_tight(lbmep_lattice *L);
 
 hipError_t dev_alloc(lbmep_lattice *L, void **p, size_t bytes);
 void dev_free(lbmep_lattice *L, void *p);
@@ -160,8 +169,8 @@ SweepArgs sweep_args_state(const lbmep_lattice *L, int cur, int cur_owner);
 SweepArgs sweep_args(const lbmep_lattice *L);
 // gather the post-stream state into the spare grid (after a step)
 int materialize(lbmep_lattice *L);
-inline int old_map(int c) { return c == 0 ? 2 : c - 1; }
-inline int next_map(int c) { return c == 2 ? 0 : c + 1; }
+inline int old_map(const lbmep_lattice *L, int c) { return L->tight ? 2 - c : c == 0 ? 2 : c - 1; }
+inline int next_map(const lbmep_lattice *L, int c) { return L->tight ? 2 - c : c == 2 ? 0 : c + 1; }
 // host bookkeeping of one completed step (the grid / map buffers flip)
 void advance_state(lbmep_lattice *L);
 

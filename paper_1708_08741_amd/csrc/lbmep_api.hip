@@ -77,7 +77,14 @@ bool finite_all(const float *p, size_t n) {
 }
 
 hipError_t dev_alloc(lbmep_lattice *L, void **p, size_t bytes) {
-    if (!L->heap) return hipMalloc(p, bytes);
+    if (!L->heap) {
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess) {
+            *p = nullptr;
+            (void)hipGetLastError();  // the next launch's check is not to find it
+        }
+        return e;
+    }
     *p = L->heap->alloc(bytes);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -131,10 +138,10 @@ int remap_all(lbmep_lattice *L) {
         for (int b = 0; b < 3; ++b) {
             if (!L->map[b].owner) continue;
             HIP_TRY(launch_fill_u32(L->map[b].owner, kNone, L->g.N, s));
-            HIP_TRY(launch_fill_u32(L->map[b].bits, 0u, map_words(L->g.N), s));
+            if (L->map[b].bits) HIP_TRY(launch_fill_u32(L->map[b].bits, 0u, map_words(L->g.N), s));
         }
         // the current and the previous level; the next one's stays empty
-        if (L->has_walls) HIP_TRY(launch_wall_bits(L->g, L->flag, L->wallbits, s));
+        if (L->has_walls && L->wallbits) HIP_TRY(launch_wall_bits(L->g, L->flag, L->wallbits, s));
         HIP_TRY(launch_map_set(pa, L->level, L->map[0], s));
         HIP_TRY(launch_map_set(pa, L->level, L->map[2], s));
         L->cur_owner = 0;
@@ -181,9 +188,9 @@ SweepArgs sweep_args_state(const lbmep_lattice *L, int cur, int co) {
     a.nearmask = L->wallmask;
     const bool parts = L->np > 0;
     a.owner = parts ? L->map[co].owner : nullptr;
-    a.owner_old = parts ? L->map[old_map(co)].owner : nullptr;
+    a.owner_old = parts ? L->map[old_map(L, co)].owner : nullptr;
     a.Xc = parts ? L->map[co].X : nullptr;
-    a.Xold = parts ? L->map[old_map(co)].X : nullptr;
+    a.Xold = parts ? L->map[old_map(L, co)].X : nullptr;
     a.U = L->U;
     a.W = L->W;
     a.FM = parts ? L->FM : nullptr;
@@ -226,7 +233,7 @@ void advance_state(lbmep_lattice *L) {
     L->cur = 1 - L->cur;
     L->pmode = true;
     if (L->np > 0 && L->cfg.move_particles) {
-        L->cur_owner = next_map(L->cur_owner);
+        L->cur_owner = next_map(L, L->cur_owner);
         // with dynamics the classification follows the exchange and may
         // rewrite the lists in place
         if (L->overlap && !L->dynamic) L->lcur ^= 1;
@@ -264,18 +271,84 @@ void free_particles(lbmep_lattice *L) {
     L->np_cap = 0;
 }
 
+// maps of the current (0) and the previous level (2), with moving particles
+// of the next (1), their bitmaps and the walls'
+bool alloc_maps(lbmep_lattice *L) {
+    const size_t words = 4 * map_words(L->g.N);
+    for (int b = 0; b < 3; ++b) {
+        if (b == 1 && (L->tight || !L->cfg.move_particles)) continue;
+        LevelMap &m = L->map[b];
+        if (!m.owner && dev_alloc(L, (void **)&m.owner, 4 * L->g.N) != hipSuccess) return false;
+        if (!L->tight && !m.bits && dev_alloc(L, (void **)&m.bits, words) != hipSuccess) return false;
+    }
+    return L->tight || L->wallbits || dev_alloc(L, (void **)&L->wallbits, words) == hipSuccess;
+}
+
+// the particle table for n particles
+bool alloc_tables(lbmep_lattice *L, size_t n) {
+    if (n <= L->np_cap) return true;
+    free_particles(L);
+    const size_t b = 3 * n * sizeof(double);
+    bool ok = dev_alloc(L, (void **)&L->X0, b) == hipSuccess && dev_alloc(L, (void **)&L->U, b) == hipSuccess &&
+              dev_alloc(L, (void **)&L->W, b) == hipSuccess && dev_alloc(L, (void **)&L->R, b / 3) == hipSuccess &&
+              dev_alloc(L, (void **)&L->FM, 6 * b) == hipSuccess;
+    for (int r = 0; r < 3 && ok; ++r)
+        if (L->map[r].owner) ok = dev_alloc(L, (void **)&L->map[r].X, b) == hipSuccess;
+    for (int r = 0; r < (L->overlap ? 2 : 1) && ok; ++r)
+        ok = dev_alloc(L, (void **)&L->pcount_buf[r], 4 * n) == hipSuccess;
+    if (ok) L->np_cap = n;
+    return ok;
+}
+
+// the link lists of `entries` entries altogether
+bool alloc_lists(lbmep_lattice *L, size_t entries) {
+    if (entries <= L->plist_entries) return true;
+    L->plist_entries = 0;
+    for (int r = 0; r < 2; ++r) {
+        dev_free(L, L->plist_buf[r]);
+        L->plist_buf[r] = nullptr;
+    }
+    for (int r = 0; r < (L->overlap ? 2 : 1); ++r)
+        if (dev_alloc(L, (void **)&L->plist_buf[r], entries * sizeof(uint2)) != hipSuccess) return false;
+    L->plist_entries = entries;
+    return true;
+}
+
+// the form with two maps, one set of link lists and no bitmaps, from a new
+// lattice's or before the particles are set anew (their tables go too)
+void make_tight(lbmep_lattice *L) {
+    free_particles(L);
+    for (int b = 0; b < 3; ++b) {
+        dev_free(L, L->map[b].bits);
+        L->map[b].bits = nullptr;
+    }
+    dev_free(L, L->map[1].owner);
+    L->map[1].owner = nullptr;
+    dev_free(L, L->wallbits);
+    L->wallbits = nullptr;
+    for (int r = 0; r < 2; ++r) {
+        dev_free(L, L->plist_buf[r]);
+        L->plist_buf[r] = nullptr;
+    }
+    L->plist_entries = 0;
+    L->tight = true;
+    L->overlap = false;
+}
+
 size_t lattice_bytes(const lbmep_config *cfg, int32_t n_particles, double r_max,
-                     int force_mode, bool overlap) {
+                     int force_mode, bool tight) {
     const size_t N = (size_t)cfg->nx * cfg->ny * cfg->nz;
     const size_t Ns = population_stride(N, cfg->precision);
     size_t b = 2 * (size_t)Q * Ns * storage_bytes(cfg->precision);  // two population grids
     b += round_up(N, 4096) + 4 * round_up(N, 4096) + 4 * N;      // flags, wall masks, wall list
     if (n_particles > 0) {
-        // maps of three levels (owners and bits), wall bits, particle table
-        b += 3 * (4 * N + 4 * map_words(N)) + 4 * map_words(N) + (size_t)n_particles * (16 + 7 * 3) * 8;
-        b += (size_t)n_particles * (8 * (size_t)link_capacity(r_max) + 4);  // link lists
-        if (overlap)  // overlapped stepping: the next level's link lists
-            b += (size_t)n_particles * (8 * (size_t)link_capacity(r_max) + 4);
+        const bool third = cfg->move_particles && !tight;
+        const size_t maps = third ? 3 : 2, lists = third ? 2 : 1;
+        b += maps * 4 * N;                                   // owners by level
+        if (!tight) b += (maps + 1) * 4 * map_words(N);      // bits by level, wall bits
+        b += (size_t)n_particles * (16 + (4 + maps) * 3) * 8;  // particle table
+        // link lists; with overlapped stepping the next level's too
+        b += lists * (size_t)n_particles * (8 * (size_t)link_capacity(r_max) + 4);
     }
     if (force_mode == kForceDense) b += 3 * Ns * compute_bytes(cfg->precision);
     if (force_mode == kForceCharge || force_mode == kForcePotential)
@@ -322,8 +395,12 @@ int lbmep_footprint(const lbmep_config *cfg, int32_t n_particles, double r_max, 
     if (rc) return rc;
     if (!bytes || n_particles < 0 || !(r_max >= 0.0) || !std::isfinite(r_max))
         return fail(LBMEP_EINVAL, "bad footprint arguments");
-    *bytes = lattice_bytes(cfg, n_particles, r_max, with_charge ? kForceCharge : kForceNone,
-                           n_particles > 0 && cfg->move_particles);
+    *bytes = lattice_bytes(cfg, n_particles, r_max, with_charge ? kForceCharge : kForceNone, false);
+    // (fixed particles, which do without the next level's map, are given as
+    // much, so that a configuration differs from its moving one by the lists)
+    if (n_particles > 0 && !cfg->move_particles)
+        *bytes += 4 * ((size_t)cfg->nx * cfg->ny * cfg->nz + map_words((size_t)cfg->nx * cfg->ny * cfg->nz)) +
+                  24 * (size_t)n_particles;
     return LBMEP_OK;
 }
 
@@ -409,6 +486,10 @@ int create_lattice(const lbmep_config *cfg, DevHeap *heap, lbmep_lattice **out) 
     // same workgroups, for comparisons)
     L->overlap = cfg->move_particles != 0;
     if (const char *e = std::getenv("LBMEP_STEP_OVERLAP")) L->overlap = L->overlap && std::atoi(e) != 0;
+    // (LBMEP_STEP_TIGHT=1: the form for lattices that the memory has no room
+    // for otherwise, for comparisons)
+    if (const char *e = std::getenv("LBMEP_STEP_TIGHT"))
+        if (std::atoi(e) != 0) make_tight(L);
     L->precision = cfg->precision;
     Grid &g = L->g;
     g.nx = cfg->nx;
@@ -606,56 +687,27 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
     rc = materialize(L);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(L->stream));
-    // maps of the current (0) and the previous level (2), with moving
-    // particles of the next (1)
-    for (int b = 0; n > 0 && b < 3; ++b) {
-        if (L->map[b].owner || (b == 1 && !L->cfg.move_particles)) continue;
-        if (dev_alloc(L, (void **)&L->map[b].owner, 4 * L->g.N) != hipSuccess ||
-            dev_alloc(L, (void **)&L->map[b].bits, 4 * map_words(L->g.N)) != hipSuccess) {
-            dev_free(L, L->map[b].owner);
-            L->map[b].owner = nullptr;
-            return fail(LBMEP_ENOMEM, "owner field allocation failed");
-        }
-    }
-    if (n > 0 && !L->wallbits && dev_alloc(L, (void **)&L->wallbits, 4 * map_words(L->g.N)) != hipSuccess)
-        return fail(LBMEP_ENOMEM, "wall bitmap allocation failed");
-    const int nlists = L->overlap ? 2 : 1;
-    if ((size_t)n > L->np_cap) {
-        free_particles(L);
-        const size_t b = 3 * (size_t)n * sizeof(double);
-        bool ok = dev_alloc(L, (void **)&L->X0, b) == hipSuccess && dev_alloc(L, (void **)&L->U, b) == hipSuccess &&
-                  dev_alloc(L, (void **)&L->W, b) == hipSuccess && dev_alloc(L, (void **)&L->R, b / 3) == hipSuccess &&
-                  dev_alloc(L, (void **)&L->FM, 6 * b) == hipSuccess;
-        for (int r = 0; r < 3; ++r)
-            ok = ok && dev_alloc(L, (void **)&L->map[r].X, b) == hipSuccess;
-        for (int r = 0; r < nlists; ++r)
-            ok = ok && dev_alloc(L, (void **)&L->pcount_buf[r], 4 * (size_t)n) == hipSuccess;
-        if (!ok) {
-            free_particles(L);
-            L->np = 0;
-            return fail(LBMEP_ENOMEM, "particle table allocation failed");
-        }
-        L->np_cap = n;
-    }
-    // link lists: capacity per particle from the largest radius
+    // capacity of the link lists per particle, from the largest radius
     double rmax = 0.0;
     for (int i = 0; i < n; ++i) rmax = R[i] > rmax ? R[i] : rmax;
     const uint32_t pcap = n > 0 ? link_capacity(rmax) : 0;
-    if ((size_t)n * pcap > L->plist_entries) {
-        L->plist_entries = 0;
-        for (int r = 0; r < 2; ++r) {
-            dev_free(L, L->plist_buf[r]);
-            L->plist_buf[r] = nullptr;
-        }
-        for (int r = 0; r < nlists; ++r)
-            if (dev_alloc(L, (void **)&L->plist_buf[r], (size_t)n * pcap * sizeof(uint2)) != hipSuccess) {
-                L->np = 0;
-                return fail(LBMEP_ENOMEM, "link list allocation failed");
-            }
-        L->plist_entries = (size_t)n * pcap;
+    // the maps, the tables and the lists, in the tight form where the memory
+    // has no room for the other (a lattice of a server keeps the form that it
+    // was admitted in)
+    bool ok = n == 0 || (alloc_maps(L) && alloc_tables(L, n) && alloc_lists(L, (size_t)n * pcap));
+    if (!ok && !L->heap && !L->tight) {
+        make_tight(L);
+        ok = alloc_maps(L) && alloc_tables(L, n) && alloc_lists(L, (size_t)n * pcap);
+    }
+    if (!ok) {  // the lattice is left without particles, their flags with them
+        free_particles(L);
+        L->np = 0;
+        rc = remap_all(L);
+        return rc ? rc : fail(LBMEP_ENOMEM, "particle map, table or link list allocation failed");
     }
     L->pcap = pcap;
-    L->box_rows = n > 0 ? box_row_capacity(rmax) : 0;
+    // (without bitmaps every box is classified cell by cell)
+    L->box_rows = n > 0 && !L->tight ? box_row_capacity(rmax) : 0;
     // boundary values of the potential and the dynamics belong to the
     // particle table they were given with
     dev_free(L, L->zeta);
@@ -1140,13 +1192,16 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
         MapSetArgs ms{};
         if (moving) {
             const bool split = L->overlap && !dyn;
-            q.mode = dyn ? kPartsDyn : split ? kPartsSplit : kPartsOne;
+            q.mode = L->tight ? (dyn ? kPartsMove : kPartsNear)
+                     : dyn    ? kPartsDyn
+                     : split  ? kPartsSplit
+                              : kPartsOne;
             // the next level's link lists
             q.pa.plist = L->plist_buf[split ? L->lcur ^ 1 : L->lcur];
             q.pa.pcount = L->pcount_buf[split ? L->lcur ^ 1 : L->lcur];
-            q.old = L->map[old_map(c)];
+            q.old = L->map[old_map(L, c)];
             q.cur = L->map[c];
-            q.next = L->map[next_map(c)];
+            q.next = L->map[next_map(L, c)];
             q.level = L->level + 1;
             if (dyn) {
                 // the particles move under this step's force and torque
@@ -1164,12 +1219,17 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
             }
         }
         HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x,
-                             moving && !dyn ? &ms : nullptr, s));
+                             moving && !dyn && !L->tight ? &ms : nullptr, s));
         if (L->timing) HIP_TRY(hipEventRecord(e1, s));
         // bounce-back slots and momentum exchange next to solid cells, and the
         // next level's flags and link lists
         HIP_TRY(launch_parts(L->precision, a, q, s));
-        if (dyn) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
+        if (moving && L->tight) {
+            // (the next level takes the previous one's map)
+            HIP_TRY(launch_map_clear(q.pa, q.next, s));
+            HIP_TRY(launch_map_set(q.pa, q.level, q.next, s));
+        }
+        if (dyn || (moving && L->tight)) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
         advance_state(L);
     }
     return LBMEP_OK;

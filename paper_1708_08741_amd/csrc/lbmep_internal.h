@@ -176,8 +176,8 @@ struct ParticleArgs {
 };
 
 // the map of one time level: owner of every obstacle cell (kNone elsewhere),
-// the obstacle cells as one bit per cell (map_words words), and the particle
-// centres (3n)
+// the obstacle cells as one bit per cell (map_words words; null in a lattice
+// of the tight form), and the particle centres (3n)
 struct LevelMap {
     uint32_t *owner;
     uint32_t *bits;
@@ -224,8 +224,9 @@ enum PartsMode {
                       // of the next level and the emptying of the previous
                       // level's map (two sets of link lists)
     kPartsOne = 2,    // the same, one workgroup per particle (one set of lists)
-    kPartsDyn = 3     // the exchange, the particle's dynamics, its cells of the
+    kPartsDyn = 3,    // the exchange, the particle's dynamics, its cells of the
                       // next level's map, the emptying of the previous level's
+    kPartsMove = 4    // the exchange and the particle's dynamics
 };
 struct PartsArgs {
     int mode;
@@ -405,6 +406,8 @@ int invariants_blocks(const Grid &g);
 hipError_t launch_positions(const ParticleArgs &pa, int64_t level, double *X, hipStream_t s);
 // positions at `level` into m.X and the particles' cells into the emptied map m
 hipError_t launch_map_set(const ParticleArgs &pa, int64_t level, const LevelMap &m, hipStream_t s);
+// the particles' cells leave the map m
+hipError_t launch_map_clear(const ParticleArgs &pa, const LevelMap &m, hipStream_t s);
 hipError_t launch_wall_bits(const Grid &g, const uint8_t *flag, uint32_t *bits, hipStream_t s);
 // classify cells (flags + wall-link masks) over the whole grid
 hipError_t launch_classify_all(const Grid &g, uint8_t *flag, uint32_t *wallmask,

@@ -164,6 +164,7 @@ struct Request {
     bool charge = false, keep_fields = false;
     double E[3] = {0, 0, 0};
     size_t footprint = 0;
+    bool tight = false;  // admitted in the tight form
     double t_submit = 0, t_admit = 0, t_done = 0;
     // results
     bool done = false;
@@ -247,12 +248,11 @@ hipEvent_t get_event(lbmep_server *S) {
 }
 
 size_t request_footprint(const lbmep_config &c, int32_t n, double r_max, bool charge, bool flags,
-                         bool keep_fields) {
+                         bool keep_fields, bool tight) {
     const size_t N = (size_t)c.nx * c.ny * c.nz;
-    size_t b = lattice_bytes(&c, n, r_max, charge ? kForceCharge : kForceNone,
-                             n > 0 && c.move_particles);
+    size_t b = lattice_bytes(&c, n, r_max, charge ? kForceCharge : kForceNone, tight);
     b += 32 * Arena::kAlign;                 // alignment of the lattice's arrays
-    b += round_up(sizeof(LatticeDev), Arena::kAlign);
+    if (!tight) b += round_up(sizeof(LatticeDev), Arena::kAlign);
     // staging of the inputs during set-up
     size_t stage = 0;
     if (flags) stage = std::max(stage, N);
@@ -282,6 +282,7 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     lbmep_lattice *L = nullptr;
     int rc = create_lattice(&c, &S->arena, &L);
     if (rc) return rc;
+    if (r->tight) make_tight(L);
     auto undo = [&](int code) {
         destroy_lattice(L, true);
         return code;
@@ -299,7 +300,8 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     if (rc) return undo(rc);
     rc = lbmep_step(L, 1);
     if (rc) return undo(rc);
-    // device descriptor for the packed launches
+    // device descriptor for the packed launches (a lattice in the tight form
+    // is stepped by launches of its own)
     LatticeDev h{};
     h.split = L->overlap && L->np > 0;
     for (int cur = 0; cur < 2; ++cur)
@@ -319,8 +321,11 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     for (int b = 0; b < 3; ++b) h.map[b] = L->map[b];
     h.map_blocks = map_blocks(L);
     h.wall_blocks = near_wall_blocks(L->g, L->has_walls);
-    LatticeDev *d = static_cast<LatticeDev *>(S->arena.alloc(sizeof(LatticeDev)));
-    if (!d) return undo(fail(LBMEP_ENOMEM, "arena exhausted (descriptor)"));
+    LatticeDev *d = nullptr;
+    if (!L->tight) {
+        d = static_cast<LatticeDev *>(S->arena.alloc(sizeof(LatticeDev)));
+        if (!d) return undo(fail(LBMEP_ENOMEM, "arena exhausted (descriptor)"));
+    }
     double *fields = nullptr;
     if (r->keep_fields) {
         fields = static_cast<double *>(S->arena.alloc(4 * L->g.N * sizeof(double)));
@@ -329,7 +334,8 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
             return undo(fail(LBMEP_ENOMEM, "arena exhausted (fields)"));
         }
     }
-    hipError_t e = hipMemcpyAsync(d, &h, sizeof h, hipMemcpyHostToDevice, S->setup);
+    hipError_t e = hipSuccess;
+    if (d) e = hipMemcpyAsync(d, &h, sizeof h, hipMemcpyHostToDevice, S->setup);
     if (e == hipSuccess) e = hipStreamSynchronize(S->setup);
     if (e != hipSuccess) {
         S->arena.release(d);
@@ -425,7 +431,8 @@ void retire(lbmep_server *S, Slot &slot) {
     slot = Slot{};
 }
 
-// enqueue `k` steps of every active slot as packed launches
+// enqueue `k` steps of every active slot as packed launches (those in the
+// tight form, which only a budget without room for the other sees, one by one)
 int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
     hipStream_t s = S->main;
     size_t bytes = 0;
@@ -450,7 +457,7 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                 };
                 for (Slot *sl : act) {
                     lbmep_lattice *L = sl->L;
-                    if (L->precision != prec || L->force_mode != fm) continue;
+                    if (L->tight || L->precision != prec || L->force_mode != fm) continue;
                     const uint32_t state = (uint32_t)(L->cur + 2 * L->cur_owner);
                     const uint32_t sb =
                         map_blocks(L) + (uint32_t)((L->g.N + kPackBlockX - 1) / kPackBlockX);
@@ -473,7 +480,12 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
                 if (rc) return rc;
             }
         for (Slot *sl : act) {
-            advance_state(sl->L);
+            if (sl->L->tight) {
+                const int rc = lbmep_step(sl->L, 1);
+                if (rc) return rc;
+            } else {
+                advance_state(sl->L);
+            }
             sl->to_enqueue -= 1;
             S->st.cell_updates += (double)sl->L->g.N;
         }
@@ -626,7 +638,7 @@ int lbmep_server_request_footprint(const lbmep_request *q, size_t *bytes) {
     double rmax = 0.0;
     for (int i = 0; q->R && i < q->n; ++i) rmax = std::max(rmax, q->R[i]);
     *bytes = request_footprint(q->cfg, q->n, rmax, q->rho_e != nullptr, q->flags != nullptr,
-                               q->keep_fields != 0);
+                               q->keep_fields != 0, false);
     return LBMEP_OK;
 }
 
@@ -650,8 +662,13 @@ int lbmep_server_submit(lbmep_server *S, const lbmep_request *q, uint64_t *id) {
     double rmax = 0.0;
     for (int i = 0; i < q->n; ++i)
         if (std::isfinite(q->R[i])) rmax = std::max(rmax, q->R[i]);
-    const size_t fp = request_footprint(c, q->n, rmax, q->rho_e != nullptr, q->flags != nullptr,
-                                        q->keep_fields != 0);
+    auto footprint = [&](bool tight) {
+        return request_footprint(c, q->n, rmax, q->rho_e != nullptr, q->flags != nullptr,
+                                 q->keep_fields != 0, tight);
+    };
+    size_t fp = footprint(false);
+    const bool tight = fp > S->arena.size();
+    if (tight) fp = footprint(true);
     if (fp > S->arena.size()) return fail(LBMEP_EINVAL, "request footprint exceeds the budget");
     if ((int32_t)S->queue.size() >= S->cfg.max_queue) return fail(LBMEP_EBUSY, "queue full");
     auto r = std::make_unique<Request>();
@@ -677,6 +694,7 @@ int lbmep_server_submit(lbmep_server *S, const lbmep_request *q, uint64_t *id) {
     }
     r->keep_fields = q->keep_fields != 0;
     r->footprint = fp;
+    r->tight = tight;
     r->id = S->next_id++;
     r->t_submit = now_s(S->t0);
     *id = r->id;

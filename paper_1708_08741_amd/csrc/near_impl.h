@@ -318,7 +318,7 @@ __device__ __forceinline__ void near_walls(const SweepArgs &a, uint32_t blk, uin
 // LDS of a particle workgroup: the exchange or the classification
 inline uint32_t parts_lds(int mode, uint32_t box_rows) {
     const uint32_t c = classify_lds(box_rows);
-    return mode == kPartsNear || mode == kPartsDyn ? kNearLds : c > kNearLds ? c : kNearLds;
+    return mode != kPartsSplit && mode != kPartsOne ? kNearLds : c > kNearLds ? c : kNearLds;
 }
 
 // the particle workgroups of a step, blk of np (3 np when split) + wall
@@ -353,9 +353,10 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
         __syncthreads();  // part_lds is reused
         part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
         part::map_clear(q.pa, (int)blk, q.old);
-    } else if (DYN && q.mode == kPartsDyn) {
+    } else if (DYN && (q.mode == kPartsDyn || q.mode == kPartsMove)) {
         __syncthreads();
         move_particle(q.pa, q.dyn, blk, sum, a.Xc + 3 * (size_t)blk);
+        if (q.mode == kPartsMove) return;
         __syncthreads();  // X0 is read by every thread
         part::advance_set(q.pa, (int)blk, q.level, q.next, (int)threadIdx.x, (int)blockDim.x);
         part::map_clear(q.pa, (int)blk, q.old);

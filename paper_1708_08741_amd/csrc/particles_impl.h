@@ -217,21 +217,29 @@ __device__ __forceinline__ void run_words(size_t c, int n, F &&fn) {
 }
 
 // the cells particle p covers at m.X leave the map: every cell of a level's
-// map lies in the ball of some particle, so this empties it
+// map lies in the ball of some particle, so this empties it (BITS: the map has
+// bitmaps)
+template <bool BITS = true>
 __device__ __forceinline__ void map_clear(const ParticleArgs &pa, int p, const LevelMap &m) {
     ball_rows(pa.g, m.X + 3 * (size_t)p, pa.R[p], (int)threadIdx.x, (int)blockDim.x,
               [&](size_t c0, int x, int n) {
         const size_t c = c0 + (size_t)x;
         for (int k = 0; k < n; ++k) m.owner[c + (size_t)k] = kNone;
         // the other cells of the words leave the map as well
-        run_words(c, n, [&](size_t w, uint32_t) { m.bits[w] = 0u; });
+        if constexpr (BITS) run_words(c, n, [&](size_t w, uint32_t) { m.bits[w] = 0u; });
     });
 }
 
 // the cells particle p covers at Xp enter the (emptied) map
+template <bool BITS>
 __device__ __forceinline__ void map_set(const ParticleArgs &pa, int p, const double *Xp,
                                         const LevelMap &m, int tid, int nt) {
     ball_rows(pa.g, Xp, pa.R[p], tid, nt, [&](size_t c0, int x, int n) {
+        if constexpr (!BITS) {
+            for (size_t c = c0 + (size_t)x; c < c0 + (size_t)(x + n); ++c)
+                if (!(pa.flag[c] & kWall)) atomicMin(&m.owner[c], (uint32_t)p);
+            return;
+        }
         run_words(c0 + (size_t)x, n, [&](size_t w, uint32_t mask) {
             if (pa.wallbits) mask &= ~pa.wallbits[w];
             if (!mask) return;
@@ -244,12 +252,13 @@ __device__ __forceinline__ void map_set(const ParticleArgs &pa, int p, const dou
 
 // particle p at `level`: its position into the level's map and its cells, by
 // nt threads (tid: this one's number among them)
+template <bool BITS = true>
 __device__ __forceinline__ void advance_set(const ParticleArgs &pa, int p, int64_t level,
                                             const LevelMap &m, int tid, int nt) {
     const double Xp[3] = {position(pa, p, 0, level), position(pa, p, 1, level),
                           position(pa, p, 2, level)};
     if (tid < 3) m.X[3 * (size_t)p + (size_t)tid] = tid == 0 ? Xp[0] : tid == 1 ? Xp[1] : Xp[2];
-    map_set(pa, p, Xp, m, tid, nt);
+    map_set<BITS>(pa, p, Xp, m, tid, nt);
 }
 
 // one cell's classification from the wall bits and the map (global reads):

@@ -355,6 +355,12 @@ int lbmep_copy_reference(void *dst, const void *src, size_t bytes, void *stream)
  * Progress (completion, admission, enqueueing) happens inside
  * lbmep_server_poll, which never waits for the GPU except for the set-up of a
  * newly admitted request (which overlaps the resident requests' steps).
+ *
+ * Host memory: the fields of finished requests (keep_fields, 32 N bytes each)
+ * lie in pinned memory until lbmep_server_release, in slabs of 32 MiB or one
+ * result's size that the first results make the server pin and that it keeps
+ * for later ones until it is destroyed, at most the smaller of 1 GiB and the
+ * budget; results beyond that go to pageable memory.
  * ------------------------------------------------------------------------ */
 
 typedef struct lbmep_server lbmep_server; /* opaque; owns its arena and streams */
@@ -392,7 +398,7 @@ typedef struct {
     size_t budget;           /* arena size */
 } lbmep_server_stats;
 
-/* Create a server: allocates the arena and two streams (default priority)
+/* Create a server: allocates the arena and three streams (default priority)
  * on cfg->device.  Errors: EINVAL (ranges), ENOMEM (arena), EDEVICE. */
 int lbmep_server_create(const lbmep_server_config *cfg, lbmep_server **out);
 
@@ -426,7 +432,8 @@ int lbmep_server_result(lbmep_server *srv, uint64_t id, double *F, double *M, do
                         double times[3]);
 
 /* Final fields rho[N], u[3N] (as lbmep_get_macro) of a request submitted with
- * keep_fields = 1.  Errors: ESTATE. */
+ * keep_fields = 1.  Arrays of 4 MiB and more are copied by up to four threads,
+ * which end before the call returns.  Errors: ESTATE. */
 int lbmep_server_fields(lbmep_server *srv, uint64_t id, double *rho, double *u);
 
 /* Forget a finished request's results. */

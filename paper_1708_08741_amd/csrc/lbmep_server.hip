@@ -6,7 +6,8 @@
 // (FIFO) when a slot is free and its device footprint fits the budget; its
 // lattice is then built inside one pre-allocated device arena, so admission
 // and retirement never call hipMalloc / hipFree (whose implicit device
-// synchronisation would drain the pipeline of the other simulations).  Set-up
+// synchronisation would drain the pipeline of the other simulations); the
+// fields of finished requests lie in pinned slabs that are kept.  Set-up
 // runs on its own stream while the resident simulations keep stepping.
 //
 // Resident simulations advance together in chunks of steps.  Every step of a
@@ -33,6 +34,7 @@
 #include <thread>
 #include <unordered_map>
 
+#include "first_fit.h"
 #include "lattice.h"
 
 using namespace lbmep;
@@ -40,117 +42,85 @@ using namespace lbmep::rt;
 
 namespace {
 
-// first-fit allocator over one device allocation; frees coalesce
+// the one device allocation that the lattices live in
 class Arena final : public DevHeap {
   public:
-    static constexpr size_t kAlign = 4096;
+    static constexpr size_t kAlign = FirstFit::kAlign;
 
     ~Arena() override {
         if (base_) hipFree(base_);
     }
     hipError_t init(size_t bytes) {
-        size_ = bytes / kAlign * kAlign;
-        hipError_t e = hipMalloc(&base_, size_);
-        if (e != hipSuccess) {
-            base_ = nullptr;
-            return e;
-        }
-        free_[0] = size_;
-        return hipSuccess;
+        fit_ = FirstFit(bytes);
+        const hipError_t e = hipMalloc(&base_, fit_.size());
+        if (e != hipSuccess) base_ = nullptr;
+        return e;
     }
     void *alloc(size_t bytes) override {
-        const size_t need = std::max<size_t>(kAlign, (bytes + kAlign - 1) / kAlign * kAlign);
-        for (auto it = free_.begin(); it != free_.end(); ++it) {
-            if (it->second < need) continue;
-            const size_t off = it->first, rest = it->second - need;
-            free_.erase(it);
-            if (rest) free_[off + need] = rest;
-            live_[off] = need;
-            used_ += need;
-            return base_ + off;
-        }
-        return nullptr;
+        const size_t off = fit_.alloc(bytes);
+        return off == FirstFit::kNone ? nullptr : base_ + off;
     }
     void release(void *p) override {
-        if (!p) return;
-        const size_t off = (size_t)(static_cast<char *>(p) - base_);
-        auto lv = live_.find(off);
-        if (lv == live_.end()) return;
-        size_t start = off, len = lv->second;
-        live_.erase(lv);
-        used_ -= len;
-        auto next = free_.lower_bound(start);
-        if (next != free_.end() && next->first == start + len) {
-            len += next->second;
-            next = free_.erase(next);
-        }
-        if (next != free_.begin()) {
-            auto prev = std::prev(next);
-            if (prev->first + prev->second == start) {
-                start = prev->first;
-                len += prev->second;
-                free_.erase(prev);
-            }
-        }
-        free_[start] = len;
+        if (p) fit_.release((size_t)(static_cast<char *>(p) - base_));
     }
-    size_t used() const { return used_; }
-    size_t size() const { return size_; }
+    size_t used() const { return fit_.used(); }
+    size_t size() const { return fit_.size(); }
 
   private:
     char *base_ = nullptr;
-    size_t size_ = 0, used_ = 0;
-    std::map<size_t, size_t> free_;             // offset -> length
-    std::unordered_map<size_t, size_t> live_;  // offset -> length
+    FirstFit fit_;
 };
 
-// Pinned host blocks for the results of one server.  A copy from the device
+// Pinned host memory for the results of one server.  A copy from the device
 // into pinned memory runs beside the host and the stepping at the link's rate
-// (32 MB: 0.6 ms; into fresh pageable memory 8 ms, with the host waiting; a
-// batch of eight with 30 MB each finished after 28 instead of 38-72 ms).
-// A block belongs to a request until that is released and then waits for the
-// next one that fits; all blocks together stay below `limit` (a result that
-// finds no room goes to pageable memory) and go back with the server.
+// (32 MB: 0.6 ms; into fresh pageable memory 8 ms, with the host waiting).
+// The memory is pinned in slabs of kSlab (or one result's size), each when the
+// results no longer fit in those there are, all together below `limit`; a
+// result that finds no room goes to pageable memory.  Pinning takes the
+// stepping thread's time, and the first read of a new slab too, so the first
+// results of a server pay for the slabs and later ones of whatever size use
+// them again.  A slab goes back with the server and not before: to free it
+// could wait for the device, in the middle of the stepping.  Eight FP32 requests
+// of 72^3 to 96^3 cells, waiting for them and reading their 8 to 28 MB each: into
+// pageable memory 51 + 11 ms; here the first batch of a process 37 + 28, of a
+// further server 13 + 19, every later one 13 + 6.  160 results of 0.4 to 12 MB,
+// 24 of them held, near the limit: 213 ms, and 257 with a block per result that
+// is freed to make room.
 class PinnedBlocks {
   public:
+    static constexpr size_t kSlab = size_t(32) << 20;
+
     ~PinnedBlocks() {
-        for (auto &b : all_) hipHostFree(b.first);
+        for (auto &s : slabs_) hipHostFree(s.first);
     }
     void set_limit(size_t bytes) { limit_ = bytes; }
     double *take(size_t bytes) {
-        const size_t need = round_up(bytes, size_t(1) << 20);
-        // the smallest waiting block of up to twice the size
-        auto it = idle_.lower_bound(need);
-        if (it != idle_.end() && it->first <= 2 * need) {
-            double *p = it->second;
-            idle_.erase(it);
-            return p;
+        for (auto &s : slabs_) {
+            const size_t off = s.second.alloc(bytes);
+            if (off != FirstFit::kNone) return reinterpret_cast<double *>(s.first + off);
         }
-        while (held_ + need > limit_ && !idle_.empty()) drop(std::prev(idle_.end()));
-        if (held_ + need > limit_) return nullptr;
+        const size_t need = round_up(bytes, FirstFit::kAlign);
+        const size_t room = limit_ > held_ ? limit_ - held_ : 0;
+        if (need > room) return nullptr;
+        const size_t slab = std::max(need, std::min(kSlab, room / FirstFit::kAlign * FirstFit::kAlign));
         void *p = nullptr;
-        if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(&p, slab, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        all_[static_cast<double *>(p)] = need;
-        held_ += need;
-        return static_cast<double *>(p);
+        FirstFit &f = slabs_.emplace(static_cast<char *>(p), FirstFit(slab)).first->second;
+        held_ += slab;
+        return reinterpret_cast<double *>(static_cast<char *>(p) + f.alloc(bytes));
     }
     void give(double *p) {
-        if (p) idle_.emplace(all_[p], p);
+        if (!p) return;
+        auto it = std::prev(slabs_.upper_bound(reinterpret_cast<char *>(p)));
+        it->second.release((size_t)(reinterpret_cast<char *>(p) - it->first));
     }
 
   private:
-    void drop(std::multimap<size_t, double *>::iterator it) {
-        held_ -= it->first;
-        all_.erase(it->second);
-        hipHostFree(it->second);
-        idle_.erase(it);
-    }
     size_t limit_ = 0, held_ = 0;
-    std::map<double *, size_t> all_;
-    std::multimap<size_t, double *> idle_;  // by size
+    std::map<char *, FirstFit> slabs_;
 };
 
 struct Request {

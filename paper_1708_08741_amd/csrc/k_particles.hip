@@ -198,7 +198,9 @@ uint32_t box_row_capacity(double r_max) {
     const double e = 2.0 * std::ceil(r_max) + 9.0;
     return e * e <= 1024.0 ? (uint32_t)(e * e) : 1024u;
 }
-uint32_t classify_lds(uint32_t box_rows) { return box_rows * 8u * kRowArrays + 64u + 4u * kRowCells; }
+uint32_t classify_lds(uint32_t box_rows, int threads) {
+    return box_rows * 8u * kRowArrays + 64u + 4u * row_cells(threads);
+}
 
 uint32_t link_capacity(double r_max) {
     const double e = 2.0 * std::ceil(r_max) + 3.0;
@@ -261,8 +263,8 @@ hipError_t launch_classify_all(const Grid &g, uint8_t *flag, uint32_t *wallmask,
 hipError_t launch_classify_boxes(const ParticleArgs &pa, const LevelMap &old, const LevelMap &now,
                                  hipStream_t s) {
     if (pa.np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_classify_boxes, row_grid((size_t)pa.np), dim3(kPartThreads), classify_lds(pa.box_rows), s,
-                       pa, old, now);
+    hipLaunchKernelGGL(k_classify_boxes, row_grid((size_t)pa.np), dim3(pa.box_threads),
+                       classify_lds(pa.box_rows, pa.box_threads), s, pa, old, now);
     return hipGetLastError();
 }
 

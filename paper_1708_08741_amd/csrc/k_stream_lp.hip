@@ -36,7 +36,7 @@ hipError_t launch_parts(int precision, const SweepArgs &a, const PartsArgs &q, h
 }
 
 hipError_t launch_sweep_packed_f64(int force_mode, const PackTable &t, hipStream_t s);
-hipError_t launch_parts_packed_f64(const PackTable &t, uint32_t lds, hipStream_t s);
+hipError_t launch_parts_packed_f64(const PackTable &t, int threads, uint32_t lds, hipStream_t s);
 
 hipError_t launch_sweep_packed(int precision, int force_mode, const PackTable &t, hipStream_t s) {
     if (precision == LBMEP_FP64) return launch_sweep_packed_f64(force_mode, t, s);
@@ -44,10 +44,12 @@ hipError_t launch_sweep_packed(int precision, int force_mode, const PackTable &t
     return sweep::launch_sweep_packed_typed<__half>(force_mode, t, s);
 }
 
-hipError_t launch_parts_packed(int precision, const PackTable &t, uint32_t lds, hipStream_t s) {
-    if (precision == LBMEP_FP64) return launch_parts_packed_f64(t, lds, s);
-    if (precision == LBMEP_FP32DEV) return sweep::launch_parts_packed_typed<float>(t, lds, s);
-    return sweep::launch_parts_packed_typed<__half>(t, lds, s);
+hipError_t launch_parts_packed(int precision, const PackTable &t, int threads, uint32_t lds,
+                               hipStream_t s) {
+    if (precision == LBMEP_FP64) return launch_parts_packed_f64(t, threads, lds, s);
+    if (precision == LBMEP_FP32DEV)
+        return sweep::launch_parts_packed_typed<float>(t, threads, lds, s);
+    return sweep::launch_parts_packed_typed<__half>(t, threads, lds, s);
 }
 
 }  // namespace lbmep

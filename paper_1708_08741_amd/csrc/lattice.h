@@ -46,6 +46,8 @@ struct lbmep_lattice {
     int lcur = 0;                     // list buffer of the current level
     uint32_t pcap = 0;                // list capacity per particle
     uint32_t box_rows = 0;            // rows of the classification's box in LDS
+    int part_threads = lbmep::kPartThreads;  // of a particle's workgroup
+    int box_threads = lbmep::kPartThreads;   // of the classification's
     size_t plist_entries = 0;         // allocated entries
     // maps of the previous, the current and (moving particles) the next level
     // by turns: map[cur_owner] is the current level's, the one before it

@@ -125,6 +125,8 @@ ParticleArgs particle_args(const lbmep_lattice *L) {
     pa.pcount = L->pcount_buf[L->lcur];
     pa.pcap = L->pcap;
     pa.box_rows = L->box_rows;
+    pa.threads = L->part_threads;
+    pa.box_threads = L->box_threads;
     return pa;
 }
 
@@ -708,6 +710,8 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
     L->pcap = pcap;
     // (without bitmaps every box is classified cell by cell)
     L->box_rows = n > 0 && !L->tight ? box_row_capacity(rmax) : 0;
+    L->part_threads = part_threads((size_t)n);
+    L->box_threads = box_threads((size_t)n, rmax);
     // boundary values of the potential and the dynamics belong to the
     // particle table they were given with
     dev_free(L, L->zeta);
@@ -1187,13 +1191,16 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
                                             : kSweepPull;
         const int c = L->cur_owner;
         PartsArgs q{};
-        q.wall_blocks = near_wall_blocks(L->g, L->has_walls);
+        q.wall_blocks = near_wall_blocks(L->g, L->has_walls, L->part_threads);
         q.pa = particle_args(L);
         MapSetArgs ms{};
+        // the classification in a launch of its own, after the particles'
+        const bool apart = moving && (dyn || L->tight || L->part_threads == kManyThreads);
         if (moving) {
             const bool split = L->overlap && !dyn;
             q.mode = L->tight ? (dyn ? kPartsMove : kPartsNear)
                      : dyn    ? kPartsDyn
+                     : apart  ? kPartsClear
                      : split  ? kPartsSplit
                               : kPartsOne;
             // the next level's link lists
@@ -1229,7 +1236,7 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
             HIP_TRY(launch_map_clear(q.pa, q.next, s));
             HIP_TRY(launch_map_set(q.pa, q.level, q.next, s));
         }
-        if (dyn || (moving && L->tight)) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
+        if (apart) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
         advance_state(L);
     }
     return LBMEP_OK;

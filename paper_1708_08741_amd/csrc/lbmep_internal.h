@@ -173,6 +173,8 @@ struct ParticleArgs {
     uint32_t *pcount;
     uint32_t pcap;
     uint32_t box_rows; // halo rows of a particle's box that the classification keeps in LDS
+    int threads;       // of a particle's workgroup (part_threads)
+    int box_threads;   // of the classification's in a launch of its own
 };
 
 // the map of one time level: owner of every obstacle cell (kNone elsewhere),
@@ -186,8 +188,26 @@ struct LevelMap {
 // words of a bitmap of N cells (two more are read past the last cell's)
 __host__ __device__ inline size_t map_words(size_t N) { return (N + 31) / 32 + 2; }
 
-// threads of the workgroups that work on one particle each in a step
-constexpr int kPartThreads = 512;
+// threads of the workgroups that work on one particle each in a step.  Up to
+// kManyParticles all of them are resident at once (256 CUs, four each), the
+// step waits for their chains of dependent loads, and the exchange, the
+// classification and the emptying of the map run side by side in one launch.
+// From there on the compute units' places are what counts: the exchange and
+// the emptying take kManyThreads each, and the classification, whose rows need
+// larger workgroups, has a launch of its own: half as large up to radius 4.
+// Step of moving spheres, FP32, one launch of 512 and now, R = 0.6 / 1 / 2 / 4:
+//   256^3, 60000   2020 / 2132 / 2455 / 3482 ->  917 / 1008 / 1477 / 2599 us
+//   256^3, 6000     625 /  652 /  741 / 1095 ->  499 /  511 /  561 /  773
+//   128^3, 5000     196 /  211 /  263 /  453 ->  109 /  116 /  145 /  238
+//   128^3, 800       84 /   87 /   91 /  111 against 80 /   83 /   91 /  119
+//   64^3, 30         16 /   16 /   18 /   22 against 21 /   22 /   25 /   37
+constexpr int kPartThreads = 512, kManyThreads = 128;
+constexpr int kManyParticles = 1024;
+inline int part_threads(size_t np) { return np < kManyParticles ? kPartThreads : kManyThreads; }
+// threads of the classification's workgroups
+inline int box_threads(size_t np, double r_max) {
+    return np >= kManyParticles && r_max <= 4.0 ? kPartThreads / 2 : kPartThreads;
+}
 
 // link-list capacity per particle for radii up to r_max: the cells whose
 // centre lies within one cell (per axis) of the ball, (2 ceil(R) + 3)^3
@@ -196,7 +216,7 @@ uint32_t link_capacity(double r_max);
 // radius up to r_max moving less than one cell per step, and the LDS bytes of
 // the classification with them
 uint32_t box_row_capacity(double r_max);
-uint32_t classify_lds(uint32_t box_rows);
+uint32_t classify_lds(uint32_t box_rows, int threads);
 
 // ---------------------------------------------------------------------------
 // Packed launches: one dispatch runs a kernel of the step for several
@@ -226,7 +246,9 @@ enum PartsMode {
     kPartsOne = 2,    // the same, one workgroup per particle (one set of lists)
     kPartsDyn = 3,    // the exchange, the particle's dynamics, its cells of the
                       // next level's map, the emptying of the previous level's
-    kPartsMove = 4    // the exchange and the particle's dynamics
+    kPartsMove = 4,   // the exchange and the particle's dynamics
+    kPartsClear = 5   // the exchange, and in other workgroups the emptying of the
+                      // previous level's map
 };
 struct PartsArgs {
     int mode;
@@ -298,11 +320,11 @@ hipError_t launch_sweep(int precision, int mode, int force_mode, const SweepArgs
 // particle over its link list and q.wall_blocks workgroups over the wall
 // list, with the next level's map as q.mode says
 hipError_t launch_parts(int precision, const SweepArgs &a, const PartsArgs &q, hipStream_t s);
-int near_wall_blocks(const Grid &g, bool walls);
-// all workgroups of the exchange kernel (particles, then wall links)
-int near_blocks(int np, const Grid &g, bool walls);
+int near_wall_blocks(const Grid &g, bool walls, int threads);
+// all workgroups of a step's particle launch (or of a lattice in a packed one)
+uint32_t parts_blocks(int mode, int np, int wall_blocks);
 // LDS bytes of the exchange
-uint32_t near_lds();
+uint32_t near_lds(int threads);
 // compact list, in cell order, of the cells with a wall link (wallmask != 0);
 // scratch of wall_list_scratch(g) entries
 int wall_list_blocks(const Grid &g);
@@ -430,6 +452,9 @@ hipError_t launch_import_flags(const Grid &g, const uint8_t *in, uint8_t *flag, 
 
 // packed launches (tables filled by the host; entries with no work omitted)
 hipError_t launch_sweep_packed(int precision, int force_mode, const PackTable &t, hipStream_t s);
-hipError_t launch_parts_packed(int precision, const PackTable &t, uint32_t lds, hipStream_t s);
+hipError_t launch_parts_packed(int precision, const PackTable &t, int threads, uint32_t lds,
+                               hipStream_t s);
+// (lattices of kManyParticles and more; box_threads of their lattices)
+hipError_t launch_classify_packed(const PackTable &t, int threads, uint32_t lds, hipStream_t s);
 
 }  // namespace lbmep

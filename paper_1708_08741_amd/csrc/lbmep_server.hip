@@ -290,7 +290,7 @@ int admit(lbmep_server *S, Slot &slot, Request *r) {
     h.pa = particle_args(L);
     for (int b = 0; b < 3; ++b) h.map[b] = L->map[b];
     h.map_blocks = map_blocks(L);
-    h.wall_blocks = near_wall_blocks(L->g, L->has_walls);
+    h.wall_blocks = near_wall_blocks(L->g, L->has_walls, L->part_threads);
     LatticeDev *d = nullptr;
     if (!L->tight) {
         d = static_cast<LatticeDev *>(S->arena.alloc(sizeof(LatticeDev)));
@@ -408,37 +408,61 @@ int enqueue_steps(lbmep_server *S, const std::vector<Slot *> &act, int k) {
     size_t bytes = 0;
     for (const Slot *sl : act) bytes += population_bytes(sl->L->g, sl->L->precision);
     for (int it = 0; it < k; ++it) {
-        // sweep and exchange, one packed launch pair per (precision, force mode)
+        // sweep and exchange, one packed launch pair per (precision, force
+        // mode); lattices of many particles apart, with a third launch for the
+        // classification
         for (int prec = LBMEP_FP64; prec <= LBMEP_FP16DEV; ++prec)
-            for (int fm = kForceNone; fm <= kForceCharge; ++fm) {
-                PackTable ts{}, tn{};
-                uint32_t lds = near_lds();
+            for (int kind = 0; kind < 2 * (kForceCharge + 1); ++kind) {
+                const int fm = kind >> 1;
+                const bool many = (kind & 1) != 0;
+                const int nt = many ? kManyThreads : kPartThreads;
+                PackTable ts{}, tn{}, tc{};
+                uint32_t lds = near_lds(nt), rows = 0;
+                int box = kPartThreads / 2;  // of the largest of the lattices
                 ts.xcd_swizzle = 1;
                 ts.cached = bytes < kInfinityCache;
                 auto flush = [&]() -> int {
                     if (ts.n == 0) return LBMEP_OK;
                     LBMEP_HIP_TRY(launch_sweep_packed(prec, fm, ts, s));
-                    LBMEP_HIP_TRY(launch_parts_packed(prec, tn, lds, s));
-                    S->st.packed_launches += 2;
-                    ts.n = tn.n = 0;
-                    ts.start[0] = tn.start[0] = 0;
-                    lds = near_lds();
+                    LBMEP_HIP_TRY(launch_parts_packed(prec, tn, nt, lds, s));
+                    if (tc.n) LBMEP_HIP_TRY(launch_classify_packed(tc, box, classify_lds(rows, box), s));
+                    S->st.packed_launches += tc.n ? 3 : 2;
+                    ts.n = tn.n = tc.n = 0;
+                    ts.start[0] = tn.start[0] = tc.start[0] = 0;
+                    lds = near_lds(nt);
+                    rows = 0;
+                    box = kPartThreads / 2;
                     return LBMEP_OK;
                 };
                 for (Slot *sl : act) {
                     lbmep_lattice *L = sl->L;
-                    if (L->tight || L->precision != prec || L->force_mode != fm) continue;
+                    if (L->tight || L->precision != prec || L->force_mode != fm ||
+                        (L->part_threads == kManyThreads) != many)
+                        continue;
+                    const bool moving = L->np > 0 && L->cfg.move_particles;
                     const uint32_t state = (uint32_t)(L->cur + 2 * L->cur_owner);
                     const uint32_t sb =
                         map_blocks(L) + (uint32_t)((L->g.N + kPackBlockX - 1) / kPackBlockX);
-                    if (map_blocks(L)) lds = std::max(lds, classify_lds(L->box_rows));
+                    if (moving && many) {
+                        box = std::max(box, L->box_threads);
+                        rows = std::max(rows, L->box_rows);
+                        tc.d[tc.n] = sl->d;
+                        tc.state[tc.n] = state;
+                        tc.start[tc.n + 1] = tc.start[tc.n] + (uint32_t)L->np;
+                        tc.n++;
+                    } else if (moving) {
+                        lds = std::max(lds, classify_lds(L->box_rows, nt));
+                    }
                     ts.d[ts.n] = tn.d[tn.n] = sl->d;
                     ts.state[ts.n] = tn.state[tn.n] = state;
                     ts.level[ts.n] = tn.level[tn.n] = L->level + 1;
                     ts.start[ts.n + 1] = ts.start[ts.n] + sb;
                     tn.start[tn.n + 1] =
-                        tn.start[tn.n] + (uint32_t)near_blocks(L->np, L->g, L->has_walls) +
-                        (L->overlap ? 2u * (uint32_t)L->np : 0u);
+                        tn.start[tn.n] + parts_blocks(!moving      ? kPartsNear
+                                                      : many       ? kPartsClear
+                                                      : L->overlap ? kPartsSplit
+                                                                   : kPartsOne,
+                                                      L->np, near_wall_blocks(L->g, L->has_walls, nt));
                     ts.n++;
                     tn.n++;
                     if (ts.n == kMaxPack) {

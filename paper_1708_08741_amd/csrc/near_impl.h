@@ -161,11 +161,11 @@ __device__ __forceinline__ void particle_link(const SweepArgs &a, int x, int y, 
     store_slot<ST, OFF>(a, q, s, fq, mw);
 }
 
-constexpr int kPartWaves = kPartThreads / 64;
-// LDS of near_particle: per pass the cells of kPartThreads list entries and
+// LDS of near_particle by NT threads: per pass the cells of NT list entries and
 // their links (at most 18 each) as entry | direction, then the sums
-constexpr uint32_t kNearLds = kPartThreads * 12 + kPartThreads * (Q - 1) * 2 +
-                              (kPartWaves + 1) * kAcc * 8 + 64;
+constexpr uint32_t near_lds_of(int nt) {
+    return (uint32_t)(nt * 12 + nt * (Q - 1) * 2 + (nt / 64 + 1) * kAcc * 8 + 64);
+}
 
 // All links of particle p (its list from the classification: cells with the
 // directions whose neighbour is an obstacle cell of p), one workgroup: the
@@ -178,14 +178,15 @@ constexpr uint32_t kNearLds = kPartThreads * 12 + kPartThreads * (Q - 1) * 2 +
 // (about 300 entries, 1200 links) should fit one pass of one round: with 256
 // threads and 128 entries per pass it took three passes of two rounds.
 // Returns the 12 sums in LDS.
-template <typename ST, typename OFF>
+template <typename ST, typename OFF, int NT>
 __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint32_t p,
                                                        unsigned char *lds) {
     using CT = typename Storage<ST>::CT;
-    double *part = reinterpret_cast<double *>(lds);      // [kPartWaves + 1][kAcc]
-    uint32_t *ecell = reinterpret_cast<uint32_t *>(part + (kPartWaves + 1) * kAcc);
-    uint32_t *ex = ecell + kPartThreads, *eyz = ex + kPartThreads;  // its coordinates
-    uint32_t *wsum = eyz + kPartThreads;
+    constexpr int NW = NT / 64;
+    double *part = reinterpret_cast<double *>(lds);      // [NW + 1][kAcc]
+    uint32_t *ecell = reinterpret_cast<uint32_t *>(part + (NW + 1) * kAcc);
+    uint32_t *ex = ecell + NT, *eyz = ex + NT;  // its coordinates
+    uint32_t *wsum = eyz + NT;
     uint16_t *link = reinterpret_cast<uint16_t *>(wsum + 16);
     const int tid = (int)threadIdx.x, lane = (int)__lane_id(), wave = tid / 64;
     const uint2 *list = a.plist + (size_t)p * a.pcap;
@@ -196,7 +197,7 @@ __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint3
     double acc[kAcc];
 #pragma unroll
     for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
-    for (uint32_t i0 = 0; i0 < n; i0 += kPartThreads) {
+    for (uint32_t i0 = 0; i0 < n; i0 += NT) {
         const uint32_t i = i0 + (uint32_t)tid;
         const uint2 e = i < n ? list[i] : make_uint2(0u, 0u);
         if (e.y) {  // one index decomposition per cell, not per link
@@ -210,13 +211,13 @@ __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint3
         for (uint32_t m = e.y; m; m &= m - 1u) link[pos++] = (uint16_t)(tid << 5 | __ffs((int)m));
         __syncthreads();
         constexpr int U = 3;
-        for (uint32_t k0 = (uint32_t)tid; k0 < total; k0 += U * kPartThreads) {
+        for (uint32_t k0 = (uint32_t)tid; k0 < total; k0 += U * NT) {
             uint32_t en[U];
             int q[U];
             CT fq[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t k = k0 + (uint32_t)u * kPartThreads;
+                const uint32_t k = k0 + (uint32_t)u * NT;
                 const uint32_t l = link[k < total ? k : k0];
                 en[u] = l >> 5;
                 q[u] = (int)(l & 31u);
@@ -224,7 +225,7 @@ __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint3
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (k0 + (uint32_t)u * kPartThreads < total) {
+                if (k0 + (uint32_t)u * NT < total) {
                     const uint32_t yz = eyz[en[u]];
                     particle_link<ST, OFF>(a, (int)ex[en[u]], (int)(yz & 0xFFFFu), (int)(yz >> 16), q[u],
                                            fq[u], Xp, Up, Wp, acc);
@@ -239,11 +240,11 @@ __device__ __forceinline__ const double *near_particle(const SweepArgs &a, uint3
         if (lane == 0) part[wave * kAcc + k] = t;
     }
     __syncthreads();
-    double *sum = part + kPartWaves * kAcc;
+    double *sum = part + NW * kAcc;
     if (tid < kAcc) {
         double t = part[tid];
 #pragma unroll
-        for (int w = 1; w < kPartWaves; ++w) t += part[w * kAcc + tid];
+        for (int w = 1; w < NW; ++w) t += part[w * kAcc + tid];
         sum[tid] = t;
         if (a.FM) a.FM[kAcc * (size_t)p + tid] = t;
     }
@@ -316,29 +317,32 @@ __device__ __forceinline__ void near_walls(const SweepArgs &a, uint32_t blk, uin
 }
 
 // LDS of a particle workgroup: the exchange or the classification
-inline uint32_t parts_lds(int mode, uint32_t box_rows) {
-    const uint32_t c = classify_lds(box_rows);
-    return mode != kPartsSplit && mode != kPartsOne ? kNearLds : c > kNearLds ? c : kNearLds;
+inline uint32_t parts_lds(int mode, uint32_t box_rows, int nt) {
+    const uint32_t c = classify_lds(box_rows, nt), n = near_lds_of(nt);
+    return mode != kPartsSplit && mode != kPartsOne ? n : c > n ? c : n;
 }
 
-// the particle workgroups of a step, blk of np (3 np when split) + wall
-// blocks.  The classification of the next level reads that level's map
+// the particle workgroups of a step, blk of np (3 np when split, 2 np with the
+// emptying beside the exchange) + wall blocks.  The classification of the next level reads that level's map
 // (complete since the sweep's launch), the current one and the walls, and
 // writes flags and the next level's link lists; the exchange reads the
 // current lists and the post-collision state; nothing reads the previous
 // level's map any more: they run side by side.  (DYN: lattices with dynamics
 // may come; its run-time component index would keep the arguments that a
 // packed launch loads in scratch memory.)
-template <typename ST, typename OFF, bool DYN>
+template <typename ST, typename OFF, bool DYN, int NT>
 __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs &q, uint32_t blk) {
     extern __shared__ __align__(16) unsigned char part_lds[];
     const uint32_t np = (uint32_t)a.np;
-    if (q.mode == kPartsSplit) {
-        if (blk < np) {  // first: these take longer
-            part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
-            return;
+    constexpr bool kMany = NT == kManyThreads;  // the classification is elsewhere
+    if (kMany ? q.mode == kPartsClear : q.mode == kPartsSplit) {
+        if constexpr (!kMany) {
+            if (blk < np) {  // first: these take longer
+                part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
+                return;
+            }
+            blk -= np;
         }
-        blk -= np;
         if (blk >= np + (uint32_t)q.wall_blocks) {
             part::map_clear(q.pa, (int)(blk - np - (uint32_t)q.wall_blocks), q.old);
             return;
@@ -348,8 +352,8 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
         near_walls<ST, OFF>(a, blk - np, (uint32_t)q.wall_blocks);
         return;
     }
-    const double *sum = near_particle<ST, OFF>(a, blk, part_lds);
-    if (q.mode == kPartsOne) {
+    const double *sum = near_particle<ST, OFF, NT>(a, blk, part_lds);
+    if (!kMany && q.mode == kPartsOne) {
         __syncthreads();  // part_lds is reused
         part::classify(q.pa, (int)blk, q.cur, q.next, part::box_rows(part_lds, q.pa.box_rows));
         part::map_clear(q.pa, (int)blk, q.old);
@@ -363,15 +367,15 @@ __device__ __forceinline__ void parts_block(const SweepArgs &a, const PartsArgs 
     }
 }
 
-template <typename ST, typename OFF>
-__global__ void __launch_bounds__(kPartThreads, 4) k_parts(SweepArgs a, PartsArgs q) {
+template <typename ST, typename OFF, int NT>
+__global__ void __launch_bounds__(NT, 4) k_parts(SweepArgs a, PartsArgs q) {
     const uint32_t blk = row_block();
-    if (blk < q.blocks) parts_block<ST, OFF, true>(a, q, blk);
+    if (blk < q.blocks) parts_block<ST, OFF, true, NT>(a, q, blk);
 }
 
 // one workgroup per particle for several lattices in one dispatch
-template <typename ST>
-__global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
+template <typename ST, int NT>
+__global__ void __launch_bounds__(NT, 4) k_parts_packed(PackTable t) {
     const uint32_t gb = row_block();
     if (gb >= t.start[t.n]) return;
     const int e = pack_find(t, gb);
@@ -383,7 +387,10 @@ __global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
     q.wall_blocks = load_uniform(&d->wall_blocks);
     q.pa = packed_args(&d->pa);
     const int split = load_uniform(&d->split);
-    q.mode = !q.pa.moving || q.pa.np == 0 ? kPartsNear : split ? kPartsSplit : kPartsOne;
+    q.mode = !q.pa.moving || q.pa.np == 0 ? kPartsNear
+             : NT == kManyThreads         ? kPartsClear
+             : split                      ? kPartsSplit
+                                          : kPartsOne;
     if (split) {
         q.pa.plist = as_global(load_uniform(&d->plist[st & 1u]));
         q.pa.pcount = as_global(load_uniform(&d->pcount[st & 1u]));
@@ -392,37 +399,47 @@ __global__ void __launch_bounds__(kPartThreads, 4) k_parts_packed(PackTable t) {
     q.cur = packed_args(&d->map[c]);
     q.next = packed_args(&d->map[c == 2 ? 0 : c + 1]);
     q.level = t.level[e];
-    parts_block<ST, uint32_t, false>(a, q, gb - t.start[e]);
+    parts_block<ST, uint32_t, false, NT>(a, q, gb - t.start[e]);
 }
 
 // workgroups of the wall pass (0 without wall cells)
-inline int near_wall_blocks(size_t N, bool walls) {
+inline int near_wall_blocks(size_t N, bool walls, int threads) {
     if (!walls) return 0;
     size_t b = (N / 256 + 255) / 256;
     if (b > 1024) b = 1024;
     if (b < 1) b = 1;
-    return (int)b;
+    return (int)b * (kPartThreads / threads);
 }
 
 template <typename ST>
-hipError_t launch_parts_packed_typed(const PackTable &t, uint32_t lds, hipStream_t s) {
+hipError_t launch_parts_packed_typed(const PackTable &t, int threads, uint32_t lds, hipStream_t s) {
     const uint32_t total = t.start[t.n];
     if (t.n == 0 || total == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_parts_packed<ST>), row_grid(total), dim3(kPartThreads), lds, s, t);
+    if (threads == kPartThreads)
+        hipLaunchKernelGGL((k_parts_packed<ST, kPartThreads>), row_grid(total), dim3(threads), lds, s, t);
+    else
+        hipLaunchKernelGGL((k_parts_packed<ST, kManyThreads>), row_grid(total), dim3(threads), lds, s, t);
     return hipGetLastError();
 }
 
 template <typename ST>
 hipError_t launch_parts_typed(const SweepArgs &a, PartsArgs q, hipStream_t s) {
-    q.blocks = (uint32_t)a.np * (q.mode == kPartsSplit ? 3u : 1u) + (uint32_t)q.wall_blocks;
+    q.blocks = parts_blocks(q.mode, a.np, q.wall_blocks);
     if (q.blocks == 0) return hipSuccess;
     const dim3 grid = row_grid(q.blocks);
-    const uint32_t lds = parts_lds(q.mode, q.pa.box_rows);
+    const int nt = q.pa.threads;
+    const uint32_t lds = parts_lds(q.mode, q.pa.box_rows, nt);
     const bool small = 2 * a.g.Ns * sizeof(ST) < (size_t(1) << 32) && 4 * a.g.Ns < (size_t(1) << 32);
-    if (small)
-        hipLaunchKernelGGL((k_parts<ST, uint32_t>), grid, dim3(kPartThreads), lds, s, a, q);
-    else
-        hipLaunchKernelGGL((k_parts<ST, uint64_t>), grid, dim3(kPartThreads), lds, s, a, q);
+#define LBMEP_PARTS(OFF)                                                                          \
+    do {                                                                                          \
+        if (nt == kPartThreads)                                                                   \
+            hipLaunchKernelGGL((k_parts<ST, OFF, kPartThreads>), grid, dim3(nt), lds, s, a, q);   \
+        else                                                                                      \
+            hipLaunchKernelGGL((k_parts<ST, OFF, kManyThreads>), grid, dim3(nt), lds, s, a, q);   \
+    } while (0)
+    if (small) LBMEP_PARTS(uint32_t);
+    else LBMEP_PARTS(uint64_t);
+#undef LBMEP_PARTS
     return hipGetLastError();
 }
 

@@ -26,8 +26,8 @@
 //
 // Three implementations of an iteration, bitwise identical:
 //   * one pass for one or two iterations (even nx, rows of a colour in at
-//     most four wavefronts; the default): k_sor_tile from psi into a second
-//     buffer (sor_tile_impl.h);
+//     most four wavefronts, where it is the faster one): k_sor_tile from psi
+//     into a second buffer (sor_tile_impl.h);
 //   * one pass per iteration (the other even rows of up to 2048 cells):
 //     k_sor_march from psi into a second buffer, every cell of both colours
 //     in one z-march (see k_sor_march);
@@ -1677,7 +1677,7 @@ hipError_t launch_sor_solve(int precision, const SorArgs &a, int max_iter, int c
 
 bool sor_tile_shape(int precision, const Grid &g, uint32_t mzc, int32_t shape[3]) {
     const TileShape t = precision == LBMEP_FP64 ? tile_shape<double>(g) : tile_shape<float>(g);
-    if (t.V == 0) return false;
+    if (!(precision == LBMEP_FP64 ? tile_pays<double>(g, t) : tile_pays<float>(g, t))) return false;
     shape[0] = 1;
     shape[1] = mzc > 0 ? (int32_t)std::min((uint32_t)g.nz, mzc) : (int32_t)g.nz;
     shape[2] = t.nwx;

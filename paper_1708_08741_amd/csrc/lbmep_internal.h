@@ -407,11 +407,11 @@ __host__ __device__ inline size_t sor_ibits_words_per_colour(size_t N) { return 
 // (even nx, rows of up to 2048 cells): one pass per iteration from psi into
 // psi2 and back; *swapped = 1 when the result ends in psi2 (the caller swaps
 // the buffers).  Otherwise one launch per colour in place.
+hipError_t launch_sor_solve(int precision, const SorArgs &a, int max_iter, int check_every,
+                            bool fused, hipStream_t s, int *swapped);
 // shape of the one-pass iteration for get_solver_shape: rows per thread,
 // planes per workgroup, wavefronts per row (false: not the tile form)
 bool sor_tile_shape(int precision, const Grid &g, uint32_t mzc, int32_t shape[3]);
-hipError_t launch_sor_solve(int precision, const SorArgs &a, int max_iter, int check_every,
-                            bool fused, hipStream_t s, int *swapped);
 hipError_t launch_potential_to_f64(int precision, const Grid &g, const void *psi, double *out,
                                    hipStream_t s);
 // psi given in cell order (LBMEP_DTYPE_F32 / F64, device memory) into the

@@ -1,7 +1,8 @@
 // sor_tile_impl.h -- K red-black SOR iterations of the Debye-Hueckel equation
 // in one pass over psi (arXiv:1708.08741, Sec. "Solver for Linear Elliptic
 // PDEs with Moving Boundaries"), for even nx with a row of one colour in at
-// most four wavefronts.  Included by k_potential.hip.
+// most four wavefronts (tile_pays: where it is the faster form).  Included by
+// k_potential.hip.
 //
 // Buffer A holds iterate n and is only read, buffer B receives iterate n + K.
 // A workgroup of 16 wavefronts holds `ns` consecutive rows (y) of one plane,
@@ -590,9 +591,7 @@ struct TileShape {
 // As many entries per lane as a 16-byte access holds, as long as the row
 // does not fit in the wavefront's lanes with fewer (idle lanes cost as much
 // as busy ones).  Rows of more than four wavefronts would leave fewer than
-// four rows per workgroup, of which two are halo rows computed twice: they
-// take k_sor_march (even rows of up to 2048 cells; 1024 x 200 x 100 in two
-// wavefronts, 6 of 8 rows kept: 0.85 -> 0.47 ms per 10 iterations).
+// four rows per workgroup, of which two are halo rows computed twice.
 template <typename CT>
 TileShape tile_shape(const Grid &g) {
     TileShape t;
@@ -607,6 +606,45 @@ TileShape tile_shape(const Grid &g) {
     t.nwx = nwx == 3 ? 4 : nwx;  // whole rows of slots (a fourth wavefront idles)
     t.ns = kTileSlots / t.nwx;
     return t;
+}
+
+// Up to how many rows (ny nz) of a shape the tile pass is taken; larger grids
+// take k_sor_march (even rows of up to 2048 cells).  The march has about 50 us
+// per iteration (FP64 70-80) to fill the chip whatever the grid, and costs less
+// per row than the tile pass where that computes many rows twice (two of four
+// per workgroup with four wavefronts per row, six of eight kept with two) or
+// holds one entry per lane.  March / tile pass, us per iteration, at 24.8 / 76.8
+// / 256 thousand rows (nx):
+//   FP32  V 1       32-128    53 / 19    54 / 36     63-71 / 88-90
+//         V 2, 4    256, 512  55 / 22, 58 / 26   59 / 40, 93 / 61   152 / 122, 258 / 161
+//         2 wavefronts, V 1   55 / 31    59 / 70     118-160 / 206-275
+//                       V 2   57 / 36    62 / 84     185-196 / 301-304
+//                       V 4   520: 60 / 42   130 / 125   341 / 361
+//                             640-1024: 62-69 / 44-48    128-173 / 128-166
+//         4 wavefronts        57-143 / 68-145        73-371 / 178-442
+//                       (3.1 thousand rows: 52-54 / 15-18)
+//   FP64  V 1       32-128    67-72 / 24-26   78 / 50-54   111-158 / 121-163
+//         V 2       256, 512  78 / 31, 90 / 49   120 / 87, 221 / 162   280 / 235, 571 / 501
+//         2 wavefronts, V 1   80 / 40    93-127 / 93-123   249-300 / 331-366
+//         4 wavefronts, V 1   88-90 / 93-95   219-229 / 296-309
+//                       V 2   516, 520: 94 / 103   305 / 318
+//                             640-1024: 105-167 / 103-151   317-413 / 326-460
+//                             (32 thousand: 125-168 / 148-180)
+template <typename CT>
+bool tile_pays(const Grid &g, const TileShape &t) {
+    constexpr size_t any = ~size_t(0);
+    const size_t rows = (size_t)g.ny * (size_t)g.nz;
+    const int hx = g.nx / 2;
+    size_t lim;
+    if (sizeof(CT) == 4)
+        lim = t.nwx == 1   ? (t.V == 1 ? 125000 : any)
+              : t.nwx == 2 ? (t.V == 1 ? 50000 : t.V == 2 ? 46000 : hx <= 320 ? 150000 : any)
+                           : 20000;
+    else
+        lim = t.nwx == 1   ? (t.V == 1 ? 200000 : any)
+              : t.nwx == 2 ? (t.V == 1 ? 76000 : any)
+                           : (t.V == 1 || hx < 320 ? 20000 : 28000);
+    return t.V > 0 && rows <= lim;
 }
 
 // what a solve needs to know of its tile passes
@@ -626,6 +664,7 @@ TilePlan tile_plan(const SorArgs &a, bool fused) {
     TilePlan t;
     if (!fused || !a.psi2 || !a.save || !a.codes) return t;
     t.shape = tile_shape<CT>(a.g);
+    if (!tile_pays<CT>(a.g, t.shape)) t.shape = TileShape{};
     t.pairs = sizeof(CT) == 4 && t.shape.V > 0 && t.shape.nwx == 1;
     return t;
 }

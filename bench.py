@@ -37,7 +37,7 @@ BYTES_PER_CELL = {"fp64": 304, "fp32dev": 152, "fp16dev": 76}
 DTYPE = {"fp64": "f64", "fp32dev": "f32", "fp16dev": "f32"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_stream_collide_512.json")
 # the gather / collide sweep instantiation timed per precision (storage type,
-# charge force, 32-bit offsets, streaming-hint mode, one cell per thread)
+# charge force, 32-bit offsets, streaming-hint mode)
 SWEEP_KERNEL = {"fp32dev": "k_sweep<float, 2, unsigned int, 4>",
                 "fp64": "k_sweep<double, 2, unsigned int, 4>",
                 "fp16dev": "k_sweep<__half, 2, unsigned int, 4>"}

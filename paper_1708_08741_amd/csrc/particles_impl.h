@@ -184,7 +184,9 @@ __device__ __forceinline__ void ball_rows(const Grid &g, const double *Xp, doubl
         const double r1 = min_image(((double)y + 0.5) - Xp[1], g.ny, g.per[1]);
         const double r2 = min_image(((double)z + 0.5) - Xp[2], g.nz, g.per[2]);
         const double h2 = R * R - (r1 * r1 + r2 * r2);
-        if (h2 < -1.0) continue;  // further than any rounding of the test
+        // (the sums of the test are monotonic in floating point too: where the
+        // other two axes alone exceed the radius, no x is inside)
+        if (h2 < -1.0) continue;
         const double h = h2 > 0.0 ? sqrt(h2) : 0.0;
         int l = max(first, min(last + 1, (int)ceil(Xp[0] - h - 0.5)));
         int e = min(last, max(l - 1, (int)floor(Xp[0] + h - 0.5)));

@@ -27,11 +27,11 @@
 // 0 whatever its neighbours hold (0 times an infinity or a NaN would not be 0,
 // and would reach the other side of the wall).
 //
-// What bounds it: the vector unit (about 265 vector instructions per
-// wavefront and step of 64 V entries in each of four stages, 0.48 of the
+// What bounds it: the vector unit (about 285 vector instructions per
+// wavefront and step of 64 V entries in each of four stages, half of the
 // time) and the step's chain of one barrier, four dependent stages and the
 // loads of the next step, with one workgroup per CU; 2.0 GB move per pair of
-// iterations at 512^3 FP32 (halo rows are re-read past L2) at 4.8 TB/s.  Why
+// iterations at 512^3 FP32 (halo rows are re-read past L2) at 4.9 TB/s.  Why
 // whole rows and 16 bytes of entries per lane: the x-neighbours of three of
 // four entries are the lane's own, so a row costs one DPP rotate, one 16-byte
 // load and store and two 16-byte LDS reads per 256 entries; the earlier
@@ -39,9 +39,9 @@
 // per cell and iteration and one pass over psi for each.  The (row block,
 // plane) space is cut into one equal range per resident workgroup, so the
 // last wave of workgroups is not nearly empty and small grids still use every
-// CU.  Measured, 29 iterations with boundaries: 512^3 FP32 with 4096 spheres
-// 8.91 -> 6.34 ms, 64^3 FP32 1.47 -> 0.28 ms, 144^3 FP64 3.03 -> 0.76 ms,
-// 256 x 200 x 300 FP64 3.11 -> 1.98 ms.  Two rows per wavefront (8 wavefronts,
+// CU.  Measured, a solve of 29 iterations with its set-up and boundaries:
+// 512^3 FP32 with 4096 spheres 8.72 -> 6.47 ms, 64^3 FP32 1.57 -> 0.30 ms,
+// 144^3 FP64 2.63 -> 0.75 ms, 256 x 200 x 300 FP64 3.34 -> 2.20 ms.  Two rows per wavefront (8 wavefronts,
 // half the scalar work per row) took 7.45 ms, reading the next stage's LDS
 // rows a stage early (spills) 6.73 ms.
 #pragma once
@@ -91,6 +91,16 @@ __device__ __forceinline__ double quot_const(double a, double d, double r) {
     return __builtin_fma(__builtin_fma(-q, d, a), r, q);
 }
 __device__ __forceinline__ float quot_const(float a, float, float r) { return a * r; }
+
+// a * b, and 0 where a factor is 0, whatever the other is (an infinity or a
+// NaN too); else the ordinary product, subnormal ones as well (checked against
+// it on 4 million pairs).  A comparison and a selection per entry instead made
+// the pass 3.7 % slower among 4096 spheres.
+__device__ __forceinline__ float mul_zero(float a, float b) {
+    float r;
+    asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 
 // the constants of a boundary row for one lane: right-hand sides and, FP32,
 // a code byte per entry (into the table of reciprocal diagonals), FP64, the
@@ -369,16 +379,16 @@ __global__ void __launch_bounds__(64 * kTileWaves)
                     } else if constexpr (sizeof(CT) == 4) {
 #pragma unroll
                         for (int v = 0; v < V; ++v) {
-                            const uint32_t k = (co[j].code >> (8 * v)) & 15u;
-                            const float r = om1 * old.v[v] + om * ((co[j].rhs.v[v] + s.v[v]) * rd[k]);
-                            nw.v[v] = k == kTileSolid ? 0.0f : r;
+                            // (a solid cell holds 0: 0 from this product is its result)
+                            const float r = rd[(co[j].code >> (8 * v)) & 15u];
+                            nw.v[v] = om1 * old.v[v] + om * mul_zero(co[j].rhs.v[v] + s.v[v], r);
                         }
                     } else {
 #pragma unroll
                         for (int v = 0; v < V; ++v) {
                             const double d = co[j].diag.v[v];  // a solid cell's is infinite
                             const double r = om1 * old.v[v] + om * ((co[j].rhs.v[v] + s.v[v]) / d);
-                            nw.v[v] = d > 0x1p1000 ? 0.0 : r;
+                            nw.v[v] = (__double2hiint(d) & 0x7ff00000) == 0x7ff00000 ? 0.0 : r;
                         }
                     }
                     if (j + 1 < S) {

@@ -414,8 +414,9 @@ int lbmep_server_request_footprint(const lbmep_request *req, size_t *bytes);
 
 /* Queue a request; every input array is copied before the call returns.
  * *id identifies it from then on.  Errors: EINVAL (bad configuration or
- * arrays, steps < 1, footprint above the budget, a grid whose two population
- * arrays reach 4 GiB), EBUSY (queue full). */
+ * arrays, steps < 1, footprint above the budget even without what
+ * lbmep_footprint names as dispensable, a grid whose two population arrays
+ * reach 4 GiB), EBUSY (queue full). */
 int lbmep_server_submit(lbmep_server *srv, const lbmep_request *req, uint64_t *id);
 
 /* Make progress (retire finished requests, admit queued ones, enqueue the

@@ -62,6 +62,7 @@ struct lbmep_lattice {
     uint32_t *wallbits = nullptr;     // wall cells, one bit per cell
     int cur_owner = 0;
     int ft_buf = 0;  // map of the last streamed time level
+    bool next_empty = false;  // the next level's map is known to be empty
     int np = 0;
     size_t np_cap = 0;
     double *X0 = nullptr, *R = nullptr, *U = nullptr, *W = nullptr, *FM = nullptr;

@@ -137,8 +137,12 @@ int remap_all(lbmep_lattice *L) {
     L->lcur = 0;
     const ParticleArgs pa = particle_args(L);
     if (L->np > 0) {
+        // the next level's map to its place; it is empty after a step
+        const LevelMap m[3] = {L->map[L->cur_owner], L->map[next_map(L, L->cur_owner)],
+                               L->map[old_map(L, L->cur_owner)]};
+        for (int b = 0; b < 3 && !L->tight; ++b) L->map[b] = m[b];
         for (int b = 0; b < 3; ++b) {
-            if (!L->map[b].owner) continue;
+            if (!L->map[b].owner || (b == 1 && L->next_empty)) continue;
             HIP_TRY(launch_fill_u32(L->map[b].owner, kNone, L->g.N, s));
             if (L->map[b].bits) HIP_TRY(launch_fill_u32(L->map[b].bits, 0u, map_words(L->g.N), s));
         }
@@ -148,6 +152,7 @@ int remap_all(lbmep_lattice *L) {
         HIP_TRY(launch_map_set(pa, L->level, L->map[2], s));
         L->cur_owner = 0;
         L->ft_buf = 0;
+        L->next_empty = L->map[1].owner != nullptr;
         HIP_TRY(launch_fill_f64(L->FM, 0.0, 18 * (size_t)L->np, s));
     }
     HIP_TRY(launch_classify_all(L->g, L->flag, L->wallmask, L->np > 0 ? L->map[0].owner : nullptr, s));
@@ -280,7 +285,10 @@ bool alloc_maps(lbmep_lattice *L) {
     for (int b = 0; b < 3; ++b) {
         if (b == 1 && (L->tight || !L->cfg.move_particles)) continue;
         LevelMap &m = L->map[b];
-        if (!m.owner && dev_alloc(L, (void **)&m.owner, 4 * L->g.N) != hipSuccess) return false;
+        if (!m.owner) {
+            if (dev_alloc(L, (void **)&m.owner, 4 * L->g.N) != hipSuccess) return false;
+            L->next_empty = false;
+        }
         if (!L->tight && !m.bits && dev_alloc(L, (void **)&m.bits, words) != hipSuccess) return false;
     }
     return L->tight || L->wallbits || dev_alloc(L, (void **)&L->wallbits, words) == hipSuccess;
@@ -1225,6 +1233,7 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
                 ms.level = q.level;
             }
         }
+        L->next_empty = false;  // until the step is launched
         HIP_TRY(launch_sweep(L->precision, mode, L->force_mode, a, L->block_x,
                              moving && !dyn && !L->tight ? &ms : nullptr, s));
         if (L->timing) HIP_TRY(hipEventRecord(e1, s));
@@ -1237,6 +1246,7 @@ int lbmep_step(lbmep_lattice *L, int32_t nsteps) {
             HIP_TRY(launch_map_set(q.pa, q.level, q.next, s));
         }
         if (apart) HIP_TRY(launch_classify_boxes(q.pa, q.cur, q.next, s));
+        L->next_empty = moving && !L->tight;
         advance_state(L);
     }
     return LBMEP_OK;

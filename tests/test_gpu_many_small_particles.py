@@ -1,6 +1,7 @@
 """Both sides of the number of particles from which a step's exchange takes
 smaller workgroups and the classification a launch of its own: against the
-oracle, in both stepping orders, with dynamics, and served."""
+oracle, in both stepping orders and the tight form, with dynamics, and
+served."""
 import numpy as np
 import pytest
 
@@ -39,8 +40,9 @@ def test_steps_follow_the_oracle(lb, oracle_mod, monkeypatch, n, R, walls):
     o.init_equilibrium(1.0, (1e-3, 0.0, -1e-3))
     o.set_particles(X, Rs, U, W, moving=True)
     out = []
-    for overlap in ("1", "0"):
+    for overlap, tight in (("1", "0"), ("0", "0"), ("1", "1")):
         monkeypatch.setenv("LBMEP_STEP_OVERLAP", overlap)
+        monkeypatch.setenv("LBMEP_STEP_TIGHT", tight)
         g = lb.Lattice(shape, per, precision=lb.FP64, move_particles=True)
         g.set_flags(fl)
         g.init_equilibrium(1.0, (1e-3, 0.0, -1e-3))
@@ -48,7 +50,7 @@ def test_steps_follow_the_oracle(lb, oracle_mod, monkeypatch, n, R, walls):
         res = []
         for k in (1, 1, 6):
             g.step(k)
-            if overlap == "1":
+            if not out:
                 o.step(k)
                 fo, oo = o.map()
                 fg, og = g.map()
@@ -62,9 +64,9 @@ def test_steps_follow_the_oracle(lb, oracle_mod, monkeypatch, n, R, walls):
             res.append((*g.map(), *g.ft(), g.get_pdfs()))
         out.append(res)
         g.close()
-    for a, b in zip(*out):
-        for x, y in zip(a, b):
-            assert (x == y).all()
+    for a, b, c in zip(*out):
+        for x, y, z in zip(a, b, c):
+            assert (x == y).all() and (x == z).all()
 
 
 @pytest.mark.parametrize("n", [1023, 1024])

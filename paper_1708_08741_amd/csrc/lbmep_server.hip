@@ -13,8 +13,9 @@
 // Resident simulations advance together in chunks of steps.  Every step of a
 // chunk is two packed launches per (precision, force mode): the sweep with the
 // mapping of the next level, and the bounce-back / exchange with its
-// classification, each over every resident lattice, a workgroup finding its
-// lattice through a block table in the kernel arguments.  A simulation whose last step is in a chunk has its results
+// classification (three with many particles), each over every resident
+// lattice, a workgroup finding its lattice through a block table in the kernel
+// arguments.  A simulation whose last step is in a chunk has its results
 // (force and torque of the last step, FP64 mass / momentum of the final
 // state, optionally the fields) computed right after that chunk on the same
 // stream; when the host sees the completion event it copies them out and

@@ -188,21 +188,25 @@ struct LevelMap {
 // words of a bitmap of N cells (two more are read past the last cell's)
 __host__ __device__ inline size_t map_words(size_t N) { return (N + 31) / 32 + 2; }
 
-// threads of the workgroups that work on one particle each in a step.  Up to
-// kManyParticles all of them are resident at once (256 CUs, four each), the
+// threads of the workgroups that work on one particle each in a step.  With
+// few particles all of them are resident at once (256 CUs, four each), the
 // step waits for their chains of dependent loads, and the exchange, the
 // classification and the emptying of the map run side by side in one launch.
-// From there on the compute units' places are what counts: the exchange and
-// the emptying take kManyThreads each, and the classification, whose rows need
+// With many the compute units' places are what counts: the exchange and the
+// emptying take kManyThreads each, and the classification, whose rows need
 // larger workgroups, has a launch of its own: half as large up to radius 4.
 // Step of moving spheres, FP32, one launch of 512 and now, R = 0.6 / 1 / 2 / 4:
 //   256^3, 60000   2020 / 2132 / 2455 / 3482 ->  917 / 1008 / 1477 / 2599 us
 //   256^3, 6000     625 /  652 /  741 / 1095 ->  499 /  511 /  561 /  773
 //   128^3, 5000     196 /  211 /  263 /  453 ->  109 /  116 /  145 /  238
-//   128^3, 800       84 /   87 /   91 /  111 against 80 /   83 /   91 /  119
-//   64^3, 30         16 /   16 /   18 /   22 against 21 /   22 /   25 /   37
+// The line lies where eight served lattices together still fill the places (64^3
+// each, 60 steps, R = 0.8 / 2 / 4: with 900 spheres 20.7 / 23.2 / 32.9 -> 10.9 /
+// 13.3 / 22.7 ms, with 600 15.9 / 17.3 / 24.5 -> 9.6 / 11.2 / 18.4, with 300 equal)
+// and a lattice of its own loses little: 128^3 with 800 84 / 87 / 91 / 111 and 80 /
+// 83 / 91 / 119 us a step, 64^3 with 600 29 / 30 / 33 / 45 and 26 / 27 / 32 / 51; with
+// 30 16 / 16 / 18 / 22 and 21 / 22 / 25 / 37.
 constexpr int kPartThreads = 512, kManyThreads = 128;
-constexpr int kManyParticles = 1024;
+constexpr int kManyParticles = 512;
 inline int part_threads(size_t np) { return np < kManyParticles ? kPartThreads : kManyThreads; }
 // threads of the classification's workgroups
 inline int box_threads(size_t np, double r_max) {

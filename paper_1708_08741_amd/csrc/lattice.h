@@ -59,6 +59,7 @@ struct lbmep_lattice {
     // previous level's map, maps and classifies the next level in launches of
     // their own.
     bool tight = false;
+    uint32_t *bitmaps = nullptr;      // what the maps' bits and wallbits lie in
     uint32_t *wallbits = nullptr;     // wall cells, one bit per cell
     int cur_owner = 0;
     int ft_buf = 0;  // map of the last streamed time level

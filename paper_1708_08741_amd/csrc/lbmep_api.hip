@@ -281,17 +281,25 @@ void free_particles(lbmep_lattice *L) {
 // maps of the current (0) and the previous level (2), with moving particles
 // of the next (1), their bitmaps and the walls'
 bool alloc_maps(lbmep_lattice *L) {
-    const size_t words = 4 * map_words(L->g.N);
+    const size_t words = map_words(L->g.N);
+    const bool third = L->cfg.move_particles && !L->tight;
     for (int b = 0; b < 3; ++b) {
-        if (b == 1 && (L->tight || !L->cfg.move_particles)) continue;
         LevelMap &m = L->map[b];
-        if (!m.owner) {
-            if (dev_alloc(L, (void **)&m.owner, 4 * L->g.N) != hipSuccess) return false;
-            L->next_empty = false;
-        }
-        if (!L->tight && !m.bits && dev_alloc(L, (void **)&m.bits, words) != hipSuccess) return false;
+        if (m.owner || (b == 1 && !third)) continue;
+        if (dev_alloc(L, (void **)&m.owner, 4 * L->g.N) != hipSuccess) return false;
+        L->next_empty = false;
     }
-    return L->tight || L->wallbits || dev_alloc(L, (void **)&L->wallbits, words) == hipSuccess;
+    if (L->tight || L->bitmaps) return true;
+    // one buffer for the bitmaps (freeing one waits for the device)
+    if (dev_alloc(L, (void **)&L->bitmaps, (third ? 4 : 3) * 4 * words) != hipSuccess) return false;
+    L->wallbits = L->bitmaps;
+    uint32_t *next = L->bitmaps + words;
+    for (int b = 0; b < 3; ++b)
+        if (L->map[b].owner) {
+            L->map[b].bits = next;
+            next += words;
+        }
+    return true;
 }
 
 // the particle table for n particles
@@ -328,14 +336,11 @@ bool alloc_lists(lbmep_lattice *L, size_t entries) {
 // lattice's or before the particles are set anew (their tables go too)
 void make_tight(lbmep_lattice *L) {
     free_particles(L);
-    for (int b = 0; b < 3; ++b) {
-        dev_free(L, L->map[b].bits);
-        L->map[b].bits = nullptr;
-    }
+    for (int b = 0; b < 3; ++b) L->map[b].bits = nullptr;
+    dev_free(L, L->bitmaps);
+    L->bitmaps = L->wallbits = nullptr;
     dev_free(L, L->map[1].owner);
     L->map[1].owner = nullptr;
-    dev_free(L, L->wallbits);
-    L->wallbits = nullptr;
     for (int r = 0; r < 2; ++r) {
         dev_free(L, L->plist_buf[r]);
         L->plist_buf[r] = nullptr;
@@ -445,11 +450,8 @@ int destroy_lattice(lbmep_lattice *L, bool sync) {
     dev_free(L, L->wall_count);
     dev_free(L, L->wall_scratch);
     for (int b = 0; b < 2; ++b) dev_free(L, L->plist_buf[b]);
-    for (int b = 0; b < 3; ++b) {
-        dev_free(L, L->map[b].owner);
-        dev_free(L, L->map[b].bits);
-    }
-    dev_free(L, L->wallbits);
+    for (int b = 0; b < 3; ++b) dev_free(L, L->map[b].owner);
+    dev_free(L, L->bitmaps);
     dev_free(L, L->force);
     dev_free(L, L->red);
     dev_free(L, L->zeta);

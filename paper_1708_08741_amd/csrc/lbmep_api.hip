@@ -731,6 +731,7 @@ int lbmep_set_particles(lbmep_lattice *L, int32_t n, const double *X, const doub
     L->q = nullptr;
     L->hq.clear();
     L->dynamic = false;
+    if (L->too_fast) HIP_TRY(hipMemset(L->too_fast, 0, 64));  // of the table before
     L->np = n;
     L->hX0.assign(X, X + 3 * (size_t)n);
     L->hR.assign(R, R + n);

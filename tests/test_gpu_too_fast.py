@@ -49,4 +49,7 @@ def test_a_component_of_one_cell_does_not_move_the_sphere(lb, E, prec):
         assert ((o >= -1) & (o < 2)).all() and (o >= 0).sum() >= (owner >= 0).sum() // 2
     with pytest.raises(lb.LbmepError, match="one cell per step"):
         g.particles()
+    # a new table starts anew
+    g.set_particles(X, [R, R], np.zeros((2, 3)))
+    assert (g.particles()[0] == X).all() and (g.map()[1] == owner).all()
     g.close()
